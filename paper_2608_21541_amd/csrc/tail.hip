@@ -6,13 +6,15 @@
 //   k* = sum_E s_j k_j / sum_E s_j,  v* likewise,  m = sum_E s_j / sum_j s_j.
 // When the totals sum_j s_j k_j and sum_j s_j v_j are already known (from the
 // scoring and curve kernels) the evicted sums are total minus kept, so only
-// the kept rows (about a tenth) are read.  If the evicted mass is below 1/64
-// of the total, the evicted rows are summed directly instead (cancellation
-// guard; rare).
+// the kept rows (about a tenth) are read.  Without the totals, or if the
+// evicted mass is below 1/64 of the total (cancellation guard), the evicted
+// rows are summed directly instead.
 //
-// gather    (nsplit workgroups per unit) copies a slice of the unit's kept
-//           rows into the packed cache and forms fp64 partial weighted sums;
 // mass      (standalone path only) partial total / evicted score mass;
+// gather    (nsplit workgroups per unit) copies a slice of the unit's kept
+//           rows into the packed cache and forms fp64 partial weighted sums,
+//           of those rows or, for a direct unit, of the evicted rows of a
+//           slice of positions;
 // finalize  (one workgroup per unit) adds the partials in split order,
 //           forms k*, v*, m and appends the slot row.
 #include "stages.h"
@@ -20,6 +22,7 @@
 namespace certkv {
 
 constexpr int kTailThreads = 256;
+constexpr int kListTile = 512;  // positions listed at a time by a direct unit's split
 constexpr double kComplementMinMass = 1.0 / 64.0;
 
 template <typename T>
@@ -51,17 +54,24 @@ __global__ void bitmap_clear_kernel(uint64_t* __restrict__ bm, int64_t words) {
   if (i < words) bm[i] = 0ull;
 }
 
-__global__ void bitmap_set_kernel(Geo g, SeqTab st, const int64_t* __restrict__ kept_offsets,
+// nsplit workgroups share a unit's kept entries: the atomics of one workgroup
+// per unit are a serial chain of round trips (two sequences of 65537 and 24001
+// keys, 8 heads: 247 us with one, 18 us with 33).
+__global__ void bitmap_set_kernel(Geo g, SeqTab st, int32_t nsplit,
+                                  const int64_t* __restrict__ kept_offsets,
                                   const int32_t* __restrict__ kept_idx, uint64_t* __restrict__ bm,
                                   int32_t bm_stride) {
-  const int h = blockIdx.x % g.H;
-  const int bl = blockIdx.x / g.H;
+  const int split = blockIdx.x % nsplit;
+  const int hb = blockIdx.x / nsplit;
+  const int h = hb % g.H;
+  const int bl = hb / g.H;
   const int l = blockIdx.y;
   if (bl >= st.count) return;
   const int n = st.len[bl];
   const int64_t u = unit_index(g, l, st.first + bl, h);
   const int64_t o0 = kept_offsets[u], o1 = kept_offsets[u + 1];
-  for (int64_t i = o0 + threadIdx.x; i < o1; i += blockDim.x) {
+  for (int64_t i = o0 + (int64_t)split * blockDim.x + threadIdx.x; i < o1;
+       i += (int64_t)nsplit * blockDim.x) {
     const int j = kept_idx[i];
     if (j >= 0 && j < n)
       atomicOr(reinterpret_cast<unsigned long long*>(&bm[u * bm_stride + (j >> 6)]),
@@ -114,11 +124,51 @@ __global__ __launch_bounds__(kTailThreads) void mass_kernel(Geo g, SeqTab st, in
   }
 }
 
+// A unit's masses and how its evicted sums are formed; the same values in
+// the gather (which sums) and in the finalize (which divides).
+struct TailMass {
+  double all, ev;   // sum of (s)_+ over every key and over the evicted ones
+  bool uniform;     // every score zero: uniform weights, masses are counts
+  bool direct;      // the evicted rows are summed (else totals minus kept)
+};
+__device__ __forceinline__ TailMass tail_masses(int64_t u, int n, int nk, int nsplit, bool totals,
+                                                const double* evicted_sum, const double* total_sum,
+                                                const double* mpart) {
+  TailMass t;
+  double nE;
+  if (evicted_sum && total_sum) {
+    t.all = total_sum[u];
+    t.ev = evicted_sum[u];
+    nE = (double)(n - nk);
+  } else {
+    t.all = t.ev = nE = 0.0;
+#pragma unroll 8
+    for (int sp = 0; sp < nsplit; ++sp) {
+      t.all += mpart[(u * nsplit + sp) * 3 + 0];
+      t.ev += mpart[(u * nsplit + sp) * 3 + 1];
+      nE += mpart[(u * nsplit + sp) * 3 + 2];
+    }
+  }
+  t.uniform = !(t.all > 0.0);
+  if (t.uniform) {
+    t.all = (double)n;
+    t.ev = nE;
+  }
+  t.direct = t.uniform || !totals || t.ev < kComplementMinMass * t.all;
+  return t;
+}
+
 // Copy a slice of kept rows to the packed cache and/or accumulate the fp64
-// partial weighted key and value sums of the slice.
+// partial weighted key and value sums of the slice.  A direct unit's evicted
+// rows are read here, by every split, and not by the unit's one finalize
+// workgroup: bound by the row gather (two sequences of 65537 and 24001 keys, 8
+// heads, no totals: 84 us for the gather and finalize, 6940 us with the
+// sums in the finalize kernel).
 template <int D, typename T, bool DO_TAIL, bool DO_COMPACT>
 __global__ __launch_bounds__(kTailThreads) void tail_gather_kernel(
-    Geo g, SeqTab st, int32_t nsplit, const float* __restrict__ scores, const T* __restrict__ kc,
+    Geo g, SeqTab st, int32_t nsplit, bool totals, const uint64_t* __restrict__ bm,
+    int32_t bm_stride, const double* __restrict__ mpart, const double* __restrict__ evicted_sum,
+    const double* __restrict__ total_sum, const float* __restrict__ scores, const T* __restrict__ kc,
     int64_t k_sl, int64_t k_st, int64_t k_sh, const T* __restrict__ vc, int64_t v_sl,
     int64_t v_st, int64_t v_sh, const int64_t* __restrict__ kept_offsets,
     const int32_t* __restrict__ kept_idx, double* __restrict__ kpart_out,
@@ -128,6 +178,9 @@ __global__ __launch_bounds__(kTailThreads) void tail_gather_kernel(
   constexpr int RPS = kTailThreads / LPR;  // rows per workgroup step
   __shared__ double redk[DO_TAIL ? RPS : 1][D];
   __shared__ double redv[DO_TAIL ? RPS : 1][D];
+  __shared__ int32_t lpos[DO_TAIL ? kListTile : 1];   // a direct unit's evicted positions
+  __shared__ double lwt[DO_TAIL ? kListTile : 1];     // and their weights
+  __shared__ int32_t lcnt[DO_TAIL ? kListTile / 64 : 1];
 
   const int split = blockIdx.x % nsplit;
   const int hb = blockIdx.x / nsplit;
@@ -156,7 +209,80 @@ __global__ __launch_bounds__(kTailThreads) void tail_gather_kernel(
   // Four rows per lane group per step: their indices, then their rows and
   // scores, are loaded together so that each step waits for two round trips.
   constexpr int UR = 4;
-  for (int i = i0 + ri; i < i1; i += RPS * UR) {
+  bool direct = false, uniform = false;
+  if (DO_TAIL) {
+    const TailMass tm = tail_masses(u, n, nk, nsplit, totals, evicted_sum, total_sum, mpart);
+    direct = tm.direct;
+    uniform = tm.uniform;
+  }
+  if (DO_TAIL && direct) {
+    // The evicted positions of this split's slice that carry weight, listed in
+    // position order a tile at a time (a ballot per round and wave, then the
+    // prefix of the (round, wave) counts), and their rows summed in list order.
+    constexpr int LR = kListTile / kTailThreads, LW = kTailThreads / 64;
+    const int lane = tid & 63, wave = tid >> 6;
+    const uint64_t* bmu = bm + u * bm_stride;
+    const int jper = (n + nsplit - 1) / nsplit;
+    const int js = min(n, split * jper), je = min(n, js + jper);
+    for (int j0 = js; j0 < je; j0 += kListTile) {
+      double w[LR];
+      uint64_t bal[LR];
+#pragma unroll
+      for (int r = 0; r < LR; ++r) {
+        const int j = j0 + r * kTailThreads + tid;
+        const int jc = min(j, n - 1);
+        const float s = scores[sbase + jc];
+        w[r] = uniform ? 1.0 : (s > 0.f ? (double)s : 0.0);
+        const bool take = j < je && w[r] != 0.0 && !is_kept(bmu, jc);
+        bal[r] = __ballot(take);
+        if (lane == 0) lcnt[r * LW + wave] = (int)__popcll(bal[r]);
+      }
+      __syncthreads();
+      int cnt = 0, start[LR];
+#pragma unroll
+      for (int r = 0; r < LR; ++r) {
+#pragma unroll
+        for (int x = 0; x < LW; ++x) {
+          if (x == wave) start[r] = cnt;
+          cnt += lcnt[r * LW + x];
+        }
+      }
+#pragma unroll
+      for (int r = 0; r < LR; ++r) {
+        if ((bal[r] >> lane) & 1ull) {
+          const int p = start[r] + (int)__builtin_amdgcn_mbcnt_hi(
+              (uint32_t)(bal[r] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal[r], 0u));
+          lpos[p] = j0 + r * kTailThreads + tid;
+          lwt[p] = w[r];
+        }
+      }
+      __syncthreads();
+      for (int i = ri; i < cnt; i += RPS * UR) {
+        // entries past the list read its last one again, with weight zero
+        uint4 kq[UR], vq[UR];
+        double ww[UR];
+#pragma unroll
+        for (int q = 0; q < UR; ++q) {
+          const int x = min(i + q * RPS, cnt - 1);
+          const int j = lpos[x];
+          ww[q] = i + q * RPS < cnt ? lwt[x] : 0.0;
+          kq[q] = *reinterpret_cast<const uint4*>(kb + (int64_t)j * k_st + ci * EPL);
+          vq[q] = *reinterpret_cast<const uint4*>(vb + (int64_t)j * v_st + ci * EPL);
+        }
+#pragma unroll
+        for (int q = 0; q < UR; ++q) {
+          if (i + q * RPS >= cnt) continue;
+#pragma unroll
+          for (int e = 0; e < EPL; ++e) {
+            ak[e] = fma(ww[q], (double)elem_f32<T>(kq[q], e), ak[e]);
+            av[e] = fma(ww[q], (double)elem_f32<T>(vq[q], e), av[e]);
+          }
+        }
+      }
+      __syncthreads();  // the list is read before the next tile rewrites it
+    }
+  }
+  if (DO_COMPACT || !direct) for (int i = i0 + ri; i < i1; i += RPS * UR) {
     // The entries past the run read a clamped one and fetch its row again,
     // unused: no load sits behind a branch, so none waits for itself.
     int j[UR];
@@ -180,7 +306,7 @@ __global__ __launch_bounds__(kTailThreads) void tail_gather_kernel(
         *reinterpret_cast<uint4*>(v_packed + (poff + ii) * D + ci * EPL) = vq[q];
         if (ci == 0) pos_packed[poff + ii] = j[q];
       }
-      if (DO_TAIL) {
+      if (DO_TAIL && !direct) {
         const double w = sv[q] > 0.f ? (double)sv[q] : 0.0;
 #pragma unroll
         for (int e = 0; e < EPL; ++e) {
@@ -212,20 +338,12 @@ __global__ __launch_bounds__(kTailThreads) void tail_gather_kernel(
 // Per unit: combine partials, form the slot, append it to the packed cache.
 template <int D, typename T, bool DO_TAIL, bool DO_COMPACT>
 __global__ __launch_bounds__(kTailThreads) void tail_finalize_kernel(
-    Geo g, SeqTab st, int32_t nsplit, const float* __restrict__ scores, const T* __restrict__ kc,
-    int64_t k_sl, int64_t k_st, int64_t k_sh, const T* __restrict__ vc, int64_t v_sl,
-    int64_t v_st, int64_t v_sh, const int64_t* __restrict__ kept_offsets,
-    const uint64_t* __restrict__ bm, int32_t bm_stride, const double* __restrict__ kpart,
-    const double* __restrict__ mpart, const double* __restrict__ evicted_sum,
-    const double* __restrict__ total_sum, const double* __restrict__ ksum,
-    const double* __restrict__ vsum, float* __restrict__ k_star, float* __restrict__ v_star,
-    double* __restrict__ tail_mass, T* __restrict__ k_packed, T* __restrict__ v_packed,
-    int32_t* __restrict__ pos_packed) {
-  constexpr int EPL = 16 / sizeof(T);
-  constexpr int LPR = D / EPL;
-  constexpr int RPS = kTailThreads / LPR;
-  __shared__ double redk[DO_TAIL ? RPS : 1][D];
-  __shared__ double redv[DO_TAIL ? RPS : 1][D];
+    Geo g, SeqTab st, int32_t nsplit, const int64_t* __restrict__ kept_offsets,
+    const double* __restrict__ kpart, const double* __restrict__ mpart,
+    const double* __restrict__ evicted_sum, const double* __restrict__ total_sum,
+    const double* __restrict__ ksum, const double* __restrict__ vsum, float* __restrict__ k_star,
+    float* __restrict__ v_star, double* __restrict__ tail_mass, T* __restrict__ k_packed,
+    T* __restrict__ v_packed, int32_t* __restrict__ pos_packed) {
   __shared__ float slot_k[D], slot_v[D];
 
   const int h = blockIdx.x % g.H;
@@ -234,91 +352,35 @@ __global__ __launch_bounds__(kTailThreads) void tail_finalize_kernel(
   if (bl >= st.count) return;
   const int b = st.first + bl;
   const int n = st.len[bl];
-  const int64_t tok0 = st.start[bl];
-  const int64_t sbase = lht_base(g, l, h, tok0);
   const int64_t u = unit_index(g, l, b, h);
   const int tid = threadIdx.x;
   const int64_t off = kept_offsets[u];
   const int nk = (int)(kept_offsets[u + 1] - off);
 
   if (DO_TAIL) {
-    double S_all, S_E, nE;
-    if (evicted_sum && total_sum) {
-      S_all = total_sum[u];
-      S_E = evicted_sum[u];
-      nE = (double)(n - nk);
-    } else {
-      S_all = S_E = nE = 0.0;
-#pragma unroll 8
-      for (int sp = 0; sp < nsplit; ++sp) {
-        S_all += mpart[(u * nsplit + sp) * 3 + 0];
-        S_E += mpart[(u * nsplit + sp) * 3 + 1];
-        nE += mpart[(u * nsplit + sp) * 3 + 2];
-      }
-    }
-    const bool uniform = !(S_all > 0.0);  // every score zero: uniform weights
-    if (uniform) {
-      S_all = (double)n;
-      S_E = nE;
-    }
-    const bool direct = uniform || !(ksum && vsum) || S_E < kComplementMinMass * S_all;
-    if (!direct) {
-      for (int d = tid; d < D; d += kTailThreads) {
-        double sk = 0.0, sv = 0.0;
-        // partials added in split order; unrolled so that the loads of 16
-        // splits are in flight together
+    const TailMass tm = tail_masses(u, n, nk, nsplit, ksum && vsum, evicted_sum, total_sum, mpart);
+    for (int d = tid; d < D; d += kTailThreads) {
+      double sk = 0.0, sv = 0.0;
+      // partials added in split order; unrolled so that the loads of 16
+      // splits are in flight together
 #pragma unroll 16
-        for (int sp = 0; sp < nsplit; ++sp) {
-          sk += kpart[((u * nsplit + sp) * 2 + 0) * D + d];
-          sv += kpart[((u * nsplit + sp) * 2 + 1) * D + d];
-        }
-        slot_k[d] = S_E > 0.0 ? (float)((ksum[u * D + d] - sk) / S_E) : 0.f;
-        slot_v[d] = S_E > 0.0 ? (float)((vsum[u * D + d] - sv) / S_E) : 0.f;
+      for (int sp = 0; sp < nsplit; ++sp) {
+        sk += kpart[((u * nsplit + sp) * 2 + 0) * D + d];
+        sv += kpart[((u * nsplit + sp) * 2 + 1) * D + d];
       }
-    } else {
-      // Direct weighted sums over the evicted rows of this unit.
-      const int ri = tid / LPR, ci = tid % LPR;
-      const T* kb = kc + (int64_t)l * k_sl + tok0 * k_st + (int64_t)h * k_sh;
-      const T* vb = vc + (int64_t)l * v_sl + tok0 * v_st + (int64_t)h * v_sh;
-      const uint64_t* bmu = bm + u * bm_stride;
-      double ak[EPL], av[EPL];
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) ak[e] = av[e] = 0.0;
-      for (int j = ri; j < n; j += RPS) {
-        if (is_kept(bmu, j)) continue;
-        const float s = scores[sbase + j];
-        const double w = uniform ? 1.0 : (s > 0.f ? (double)s : 0.0);
-        if (w == 0.0) continue;
-        const uint4 kq = *reinterpret_cast<const uint4*>(kb + (int64_t)j * k_st + ci * EPL);
-        const uint4 vq = *reinterpret_cast<const uint4*>(vb + (int64_t)j * v_st + ci * EPL);
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) {
-          ak[e] = fma(w, (double)elem_f32<T>(kq, e), ak[e]);
-          av[e] = fma(w, (double)elem_f32<T>(vq, e), av[e]);
-        }
+      if (!tm.direct) {
+        sk = ksum[u * D + d] - sk;
+        sv = vsum[u * D + d] - sv;
       }
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) {
-        redk[ri][ci * EPL + e] = ak[e];
-        redv[ri][ci * EPL + e] = av[e];
-      }
-      __syncthreads();
-      for (int d = tid; d < D; d += kTailThreads) {
-        double sk = 0.0, sv = 0.0;
-        for (int r = 0; r < RPS; ++r) {
-          sk += redk[r][d];
-          sv += redv[r][d];
-        }
-        slot_k[d] = S_E > 0.0 ? (float)(sk / S_E) : 0.f;
-        slot_v[d] = S_E > 0.0 ? (float)(sv / S_E) : 0.f;
-      }
+      slot_k[d] = tm.ev > 0.0 ? (float)(sk / tm.ev) : 0.f;
+      slot_v[d] = tm.ev > 0.0 ? (float)(sv / tm.ev) : 0.f;
     }
     __syncthreads();
     for (int d = tid; d < D; d += kTailThreads) {
       k_star[u * D + d] = slot_k[d];
       v_star[u * D + d] = slot_v[d];
     }
-    if (tid == 0) tail_mass[u] = S_E / S_all;
+    if (tid == 0) tail_mass[u] = tm.ev / tm.all;
   } else {
     for (int d = tid; d < D; d += kTailThreads) {
       slot_k[d] = k_star[u * D + d];
@@ -347,17 +409,16 @@ static certkv_status launch_tail(const TailArgs& a, const SeqTab& st, hipStream_
     CERTKV_LAUNCH("tail_mass", mass_kernel, grid_split, dim3(kTailThreads), 0, s, g, st, a.nsplit,
                   a.scores, (const uint64_t*)a.bitmap, a.bm_stride, a.mpart);
   CERTKV_LAUNCH(gname, (tail_gather_kernel<D, T, DT, DC>), grid_split, dim3(kTailThreads), 0, s, g,
-                st, a.nsplit, a.scores, static_cast<const T*>(a.k.ptr), a.k.s_layer, a.k.s_token,
-                a.k.s_head, static_cast<const T*>(a.v.ptr), a.v.s_layer, a.v.s_token, a.v.s_head,
+                st, a.nsplit, a.ksum && a.vsum, (const uint64_t*)a.bitmap, a.bm_stride,
+                (const double*)a.mpart, a.evicted_sum, a.total_sum, a.scores,
+                static_cast<const T*>(a.k.ptr), a.k.s_layer, a.k.s_token, a.k.s_head,
+                static_cast<const T*>(a.v.ptr), a.v.s_layer, a.v.s_token, a.v.s_head,
                 a.kept_offsets, a.kept_idx, a.kpart, static_cast<T*>(a.k_packed),
                 static_cast<T*>(a.v_packed), a.pos_packed);
   CERTKV_LAUNCH(fname, (tail_finalize_kernel<D, T, DT, DC>), grid_unit, dim3(kTailThreads), 0, s, g,
-                st, a.nsplit, a.scores, static_cast<const T*>(a.k.ptr), a.k.s_layer, a.k.s_token,
-                a.k.s_head, static_cast<const T*>(a.v.ptr), a.v.s_layer, a.v.s_token, a.v.s_head,
-                a.kept_offsets, (const uint64_t*)a.bitmap, a.bm_stride, (const double*)a.kpart,
-                (const double*)a.mpart, a.evicted_sum, a.total_sum, a.ksum, a.vsum, a.k_star,
-                a.v_star, a.tail_mass, static_cast<T*>(a.k_packed), static_cast<T*>(a.v_packed),
-                a.pos_packed);
+                st, a.nsplit, a.kept_offsets, (const double*)a.kpart, (const double*)a.mpart,
+                a.evicted_sum, a.total_sum, a.ksum, a.vsum, a.k_star, a.v_star, a.tail_mass,
+                static_cast<T*>(a.k_packed), static_cast<T*>(a.v_packed), a.pos_packed);
   return CERTKV_OK;
 }
 
@@ -373,8 +434,8 @@ certkv_status run_bitmap(const TailArgs& a, const SeqTab& st, int64_t words_tota
   if (clear)
     CERTKV_LAUNCH("kept_bitmap_clear", bitmap_clear_kernel, dim3((unsigned)((words_total + 255) / 256)),
                   dim3(256), 0, s, a.bitmap, words_total);
-  CERTKV_LAUNCH("kept_bitmap_set", bitmap_set_kernel, dim3(a.g.H * st.count, a.g.L), dim3(256), 0, s,
-                a.g, st, a.kept_offsets, a.kept_idx, a.bitmap, a.bm_stride);
+  CERTKV_LAUNCH("kept_bitmap_set", bitmap_set_kernel,
+                dim3(a.g.H * st.count * a.nsplit, a.g.L), dim3(256), 0, s, a.g, st, a.nsplit, a.kept_offsets, a.kept_idx, a.bitmap, a.bm_stride);
   return CERTKV_OK;
 }
 

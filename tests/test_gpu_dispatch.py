@@ -1,0 +1,64 @@
+"""Edges of the kernels' size rules: each test runs the sizes at which a
+stage changes its split of the work (tiles, remainders, the smallest and the
+largest of a range) against the oracle or a plain fp64 reference."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2608_21541_amd as ck
+import synth
+from _parity import spec_of
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    torch.cuda.init()
+
+
+def _scores(shape, seed):
+    rng = np.random.default_rng(seed)
+    return np.exp(rng.standard_normal(shape)).astype(np.float32)
+
+
+@pytest.mark.parametrize("name,lens", [("C2", [64, 511, 513, 2049, 5000]), ("C1", [16, 700, 4097])])
+def test_direct_tail_splits(name, lens):
+    # The evicted rows summed directly, split over a unit's slices of
+    # positions: slices of part of a list tile and of several, all-zero scores
+    # (uniform weights), and scores that leave whole slices without weight.
+    # fp64 sums rounded once to fp32: half an ulp plus the sums' own rounding.
+    cfg = synth.config(name, seqlens=lens)
+    cache = synth.make_cache(cfg, "cpu")
+    spec = spec_of(cfg)
+    s = _scores((1, cfg.kv_heads, sum(lens)), 3)
+    s[0, 0] = 0.0
+    s[0, 1, ::3] = 0.0
+    s[0, 2, 40:] = 0.0
+    st = torch.from_numpy(s).to(DEV)
+    k, v = cache["k"].to(DEV), cache["v"].to(DEV)
+    bud = torch.tensor([max(1, n // (2 + h)) for n in lens for h in range(cfg.kv_heads)],
+                       dtype=torch.int32, device=DEV)
+    _, off, idx = ck.select(spec, st, bud)
+    ks, vs, mass = ck.tail_summary(spec, st, k, v, off, idx)
+    off, idx = off.tolist(), idx.cpu()
+    t0 = 0
+    for b, n in enumerate(lens):
+        for h in range(cfg.kv_heads):
+            u = b * cfg.kv_heads + h
+            w = torch.from_numpy(s[0, h, t0:t0 + n]).double()
+            if w.sum() == 0:
+                w = torch.ones(n, dtype=torch.float64)
+            tot = w.sum()
+            w[idx[off[u]:off[u + 1]].long()] = 0.0
+            assert abs(mass[u].item() - (w.sum() / tot).item()) <= 1e-12
+            for got, x in ((ks[u], cache["k"]), (vs[u], cache["v"])):
+                rows = x[0, t0:t0 + n, h].double()
+                ref = (w @ rows) / w.sum() if w.sum() > 0 else torch.zeros(cfg.head_dim).double()
+                scale = (w.abs() @ rows.abs()) / max(w.sum().item(), 1e-300)
+                assert ((got.cpu().double() - ref).abs() <= 2.0 ** -24 * ref.abs() + 1e-13 * scale).all()
+        t0 += n
