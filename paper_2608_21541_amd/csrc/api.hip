@@ -424,7 +424,7 @@ static certkv_status do_allocate(const Plan& P, const float* curves, const int32
 static certkv_status do_select(const Plan& P, const float* scores, const uint32_t* sorted_keys,
                                const int32_t* perm, int32_t* budgets, int mode, double retain,
                                int64_t* kept_offsets, int64_t* packed_offsets, int32_t* kept_idx,
-                               int64_t capacity, const Bufs* fused, hipStream_t s) {
+                               int64_t capacity, uint8_t* mask, const Bufs* fused, hipStream_t s) {
   const auto tabs = make_tabs(P, nullptr, 0.f);
   for (const SeqTab& t : tabs) {
     if (mode == CERTKV_SELECT_COVERAGE)
@@ -447,6 +447,7 @@ static certkv_status do_select(const Plan& P, const float* scores, const uint32_
   a.total_sum = fused ? fused->total_sum : nullptr;
   a.bitmap = fused ? fused->bitmap : nullptr;
   a.bm_stride = P.bm_words;
+  a.mask = mask;
   for (const SeqTab& t : tabs) TRY(run_select(a, t, s));
   return CERTKV_OK;
 }
@@ -650,10 +651,8 @@ certkv_status certkv_select(const certkv_problem* p, const float* scores, int32_
   if (p->flags & CERTKV_DRY_RUN) return CERTKV_OK;
   hipStream_t s = (hipStream_t)stream;
   TRY(do_sort(P, scores, w.perm, w, s));
-  TRY(do_select(P, scores, w.keysA, w.perm, budgets_io, mode, retain_mass, kept_offsets, nullptr,
-                kept_idx, kept_capacity, nullptr, s));
-  if (kept_mask) TRY(run_mask(P.g, make_tabs(P, nullptr, 0.f), kept_offsets, kept_idx, kept_mask, s));
-  return CERTKV_OK;
+  return do_select(P, scores, w.keysA, w.perm, budgets_io, mode, retain_mass, kept_offsets, nullptr,
+                   kept_idx, kept_capacity, kept_mask, nullptr, s);
 }
 
 certkv_status certkv_tail_summary(const certkv_problem* p, const float* scores, certkv_tensor k,
@@ -876,13 +875,10 @@ certkv_status certkv_compress(const certkv_problem* p, certkv_tensor q_win, cert
   TRY(do_curves(P, v, pm, cv, w.vsum, w, s));
   TRY(do_allocate(P, cv, n_keep_host, alpha, steps, out->budgets, false, w, s, out->alloc_stats));
   TRY(do_select(P, out->scores, w.keysA, pm, out->budgets, CERTKV_SELECT_BUDGET, 0.0,
-                out->kept_offsets, out->packed_offsets, out->kept_idx, cap, &w, s));
+                out->kept_offsets, out->packed_offsets, out->kept_idx, cap, out->kept_mask, &w, s));
   TRY(do_tail(P, out->scores, k, v, out->kept_offsets, out->kept_idx, w.ksum, w.vsum, out->k_star,
               out->v_star, out->tail_mass, out->k_packed, out->v_packed, out->pos_packed, true, true,
               true, w, s));
-  if (out->kept_mask)
-    TRY(run_mask(P.g, make_tabs(P, nullptr, 0.f), out->kept_offsets, out->kept_idx, out->kept_mask,
-                 s));
   return CERTKV_OK;
 }
 

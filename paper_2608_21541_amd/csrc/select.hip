@@ -75,7 +75,7 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
     const int32_t* __restrict__ perm, const int32_t* __restrict__ budgets,
     const int64_t* __restrict__ kept_offsets, int32_t* __restrict__ kept_idx, int64_t capacity,
     double* __restrict__ evicted_sum, double* __restrict__ total_sum, uint64_t* __restrict__ bm,
-    int32_t bm_stride) {
+    int32_t bm_stride, uint8_t* __restrict__ mask) {
   // kept counts of each (round, wave) of a tile, then their exclusive prefix
   // in position order (round-major); the tile's total at the end
   __shared__ uint32_t kcnt[kSelRounds * kSelWaves + 1];
@@ -131,6 +131,7 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
       sa += sp;
       se += keep ? 0.0 : sp;
       bal[r] = __ballot(keep);
+      if (mask && valid) mask[base + j] = keep ? 1 : 0;  // 64 consecutive bytes per wave
       kmask |= (uint32_t)keep << r;
       if (lane == 0) {
         kcnt[r * kSelWaves + wave] = (uint32_t)__popcll(bal[r]);
@@ -196,10 +197,31 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
 
 // Coverage budget k_eta: the normalizer sum (s)_+ in position order, then the
 // rank-order prefix of a = (s)_+ / sum until it reaches retain, both summed
-// one term at a time in fp64 (one wave per unit, uniform accumulators).
-__global__ __launch_bounds__(64) void coverage_kernel(Geo g, SeqTab st, const float* __restrict__ scores,
-                                                      const uint32_t* __restrict__ sorted_keys,
-                                                      double retain, int32_t* __restrict__ budgets) {
+// one term at a time in fp64.  One 16-wave workgroup per unit.
+//
+// The serial sums are a chain of up to 2 n dependent additions, so the
+// workgroup first finds the crossing from sums taken in another order: the
+// total over all threads, then the rank range holding the crossing narrowed
+// 16-fold per step (each wave sums one part of it) down to one wave's 64
+// ranks.  With unit roundoff u = 2^-53, a prefix of at most n non-negative
+// terms adding up to at most 1 is within n u of its exact value when summed
+// serially, the total carries another n u into every term, the quotients u
+// each, and this kernel's own sums stay within n u likewise: a prefix
+// differs from the serial one by less than 4 n u.  If the prefixes on both
+// sides of the crossing clear retain by twice that, the serial sums cross at
+// the same rank.  Otherwise (prefixes tied with retain: flat or quantized
+// scores, retain = 1, a non-finite total) the serial sums decide.
+// Three sequences of 16384, 9999 and 30001 keys, two layers, 8 heads: 3740 us
+// with the serial sums alone, 13 us; flat scores, which fall back: 165 us.
+constexpr int kCovThreads = 1024;
+constexpr int kCovWaves = kCovThreads / 64;
+
+__global__ __launch_bounds__(kCovThreads) void coverage_kernel(
+    Geo g, SeqTab st, const float* __restrict__ scores, const uint32_t* __restrict__ sorted_keys,
+    double retain, int32_t* __restrict__ budgets) {
+  __shared__ double wsum[kCovWaves];
+  __shared__ double buf[2][kCovThreads];
+  __shared__ int32_t decided, hit_at[2];
   const int h = blockIdx.x % g.H;
   const int bl = blockIdx.x / g.H;
   const int l = blockIdx.y;
@@ -207,43 +229,173 @@ __global__ __launch_bounds__(64) void coverage_kernel(Geo g, SeqTab st, const fl
   const int b = st.first + bl;
   const int n = st.len[bl];
   const int64_t base = lht_base(g, l, h, st.start[bl]);
-  const int lane = threadIdx.x;
+  const int64_t u = unit_index(g, l, b, h);
+  const int tid = threadIdx.x;
+  const int lane = tid & 63, wave = tid >> 6;
+  const BufRsrc srs = make_rsrc(scores + base, (uint32_t)n * 4u);
+  const BufRsrc krs = make_rsrc(sorted_keys + base, (uint32_t)n * 4u);
+  auto pos_part = [](float s) { return s > 0.f ? (double)s : 0.0; };
+  // (s)_+ at rank r, zero from rank hi on (reads past n are range-checked)
+  auto at_rank = [&](int r, int hi) {
+    const double x = pos_part(desc_key_value(buf_load_u32(krs, (uint32_t)r * 4u)));
+    return r < hi ? x : 0.0;
+  };
+
+  // total, in any order
+  double part = 0.0;
+#pragma unroll 8
+  for (int j = tid; j < n; j += kCovThreads)
+    part += pos_part(__uint_as_float(buf_load_u32(srs, (uint32_t)j * 4u)));
+  part = wave_sum(part);
+  if (lane == 0) wsum[wave] = part;
+  __syncthreads();
   double tot = 0.0;
-  for (int j0 = 0; j0 < n; j0 += 64) {
-    const int j = j0 + lane;
-    const float s = j < n ? scores[base + j] : 0.f;
-    const double sp = s > 0.f ? (double)s : 0.0;
-    const int cnt = min(64, n - j0);
-    for (int i = 0; i < cnt; ++i) tot += __shfl(sp, i, 64);
-  }
-  const double inv_n = 1.0 / (double)n;
-  double p = 0.0;
-  int k = n;
-  bool done = false;
-  for (int r0 = 0; r0 < n && !done; r0 += 64) {
-    const int r = r0 + lane;
-    const float s = r < n ? desc_key_value(sorted_keys[base + r]) : 0.f;
-    const double a = tot > 0.0 ? (s > 0.f ? (double)s / tot : 0.0) : inv_n;
-    const int cnt = min(64, n - r0);
-    for (int i = 0; i < cnt; ++i) {
-      p += __shfl(a, i, 64);
-      if (p >= retain) {
-        k = r0 + i + 1;
-        done = true;
+  for (int w = 0; w < kCovWaves; ++w) tot += wsum[w];
+  __syncthreads();
+
+  // ranks [lo, hi) hold the crossing if there is one; below: the sum before lo
+  const double goal = retain * tot;
+  int lo = 0, hi = n;
+  double below = 0.0;
+  while (hi - lo > 64) {
+    const int per = ((hi - lo + kCovWaves - 1) / kCovWaves + 63) & ~63;
+    const int w0 = lo + wave * per, w1 = min(hi, w0 + per);
+    double x = 0.0;
+#pragma unroll 8
+    for (int r = w0 + lane; r < w1; r += 64) x += at_rank(r, w1);
+    x = wave_sum(x);
+    if (lane == 0) wsum[wave] = x;
+    __syncthreads();
+    int pick = kCovWaves - 1;  // no crossing: the last part, and on to rank n
+    double before = below;
+    for (int w = 0; w < kCovWaves; ++w) {
+      if (below + wsum[w] >= goal) {
+        pick = w;
         break;
       }
+      below += wsum[w];
+      if (w + 1 < kCovWaves) before = below;
     }
+    below = before;
+    const int nlo = min(hi, lo + pick * per);
+    hi = min(hi, nlo + per);
+    lo = nlo;
+    __syncthreads();
+  }
+  if (wave == 0) {
+    double incl = at_rank(lo + lane, hi);
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const double y = __shfl_up(incl, o, 64);
+      if (lane >= o) incl += y;
+    }
+    incl += below;
+    double prev = __shfl_up(incl, 1, 64);
+    if (lane == 0) prev = below;
+    const double eps = 8.0 * (double)n * 1.1102230246251565e-16 * tot;
+    // at most one lane: prefixes do not decrease.  A NaN decides nothing.
+    const bool here = lane < hi - lo && incl >= goal + eps && prev < goal - eps && tot > 0.0 &&
+                      tot < INFINITY;
+    const uint64_t m = __ballot(here);
+    if (lane == 0) decided = m ? lo + (int)__builtin_ctzll(m) + 1 : 0;
+  }
+  __syncthreads();
+  int k = decided;
+  if (k == 0) {
+    // Serial sums: every thread loads one term of the next 1024 into LDS while
+    // each thread adds up the current ones (the same additions everywhere: the
+    // operands are LDS broadcasts and the loop ends together).
+    double x[1];
+    tot = 0.0;
+    const int nt = (n + kCovThreads - 1) / kCovThreads;
+    x[0] = pos_part(__uint_as_float(buf_load_u32(srs, (uint32_t)tid * 4u)));
+    for (int t = 0; t < nt; ++t) {
+      buf[t & 1][tid] = x[0];
+      __syncthreads();
+      x[0] = pos_part(__uint_as_float(buf_load_u32(srs, (uint32_t)((t + 1) * kCovThreads + tid) * 4u)));
+      const int cnt = min(kCovThreads, n - t * kCovThreads);
+      const double* q = buf[t & 1];
+      if (wave == 0) {
+#pragma unroll 16
+        for (int i = 0; i < cnt; ++i) tot += q[i];
+      }
+    }
+    __syncthreads();
+    if (tid == 0) wsum[0] = tot;
+    __syncthreads();
+    tot = wsum[0];
+    const double inv_n = 1.0 / (double)n;
+    auto term = [&](int r) {
+      const float s = desc_key_value(buf_load_u32(krs, (uint32_t)r * 4u));
+      const double a = tot > 0.0 ? (s > 0.f ? (double)s / tot : 0.0) : inv_n;
+      return r < n ? a : 0.0;
+    };
+    double p = 0.0;
+    k = n;
+    if (tid < 2) hit_at[tid] = 0;
+    x[0] = term(tid);
+    // (tile t's hit goes to slot t % 2, which is not written again before
+    // every thread has passed the next barrier: all of them leave together)
+    int found = 0;
+    for (int t = 0; t < nt; ++t) {
+      buf[t & 1][tid] = x[0];
+      __syncthreads();
+      found = hit_at[(t & 1) ^ 1];
+      if (found) break;
+      x[0] = term((t + 1) * kCovThreads + tid);
+      const int cnt = min(kCovThreads, n - t * kCovThreads);
+      const double* q = buf[t & 1];
+      if (wave == 0) {
+        // blocks of 16 additions: the prefix is monotone, so a block whose
+        // end stays below retain holds no crossing
+        int i = 0;
+        bool hit = false;
+        for (; i + 16 <= cnt; i += 16) {
+          double e = p;
+#pragma unroll
+          for (int j = 0; j < 16; ++j) e += q[i + j];
+          if (!(e < retain)) {
+            hit = true;
+            break;
+          }
+          p = e;
+        }
+        if (hit || i < cnt) {
+          const int end = hit ? i + 16 : cnt;
+          hit = false;
+          for (; i < end; ++i) {
+            p += q[i];
+            if (p >= retain) {
+              hit = true;
+              break;
+            }
+          }
+          // (a block may stop without a crossing only if a term is NaN)
+          while (!hit && i < cnt) {
+            p += q[i++];
+            if (p >= retain) {
+              hit = true;
+              --i;
+            }
+          }
+        }
+        if (hit && lane == 0) hit_at[t & 1] = t * kCovThreads + i + 1;
+      }
+    }
+    __syncthreads();
+    if (!found) found = hit_at[(nt - 1) & 1];  // the last tile's
+    if (found) k = found;
   }
   // a kept window leads the order and is never cut
   if (g.keep_w) k = max(k, min(g.keep_w, n));
-  if (lane == 0) budgets[unit_index(g, l, b, h)] = k;
+  if (tid == 0) budgets[u] = k;
 }
 
 
 certkv_status run_coverage(const Geo& g, const SeqTab& st, const float* scores,
                            const uint32_t* sorted_keys, double retain, int32_t* budgets,
                            hipStream_t s) {
-  CERTKV_LAUNCH("coverage_budget", coverage_kernel, dim3(g.H * st.count, g.L), dim3(64), 0, s, g, st,
+  CERTKV_LAUNCH("coverage_budget", coverage_kernel, dim3(g.H * st.count, g.L), dim3(kCovThreads), 0, s, g, st,
                 scores, sorted_keys, retain, budgets);
   return CERTKV_OK;
 }
@@ -295,53 +447,11 @@ certkv_status run_uniform_budgets(const Geo& g, const SeqTab& st, int32_t* budge
   return CERTKV_OK;
 }
 
-// Kept mask [L][H][T] uint8: cleared with 16-byte stores (the mask base is
-// 16-byte aligned; the tail of the buffer byte by byte), then the kept
-// positions of every unit set to 1.
-__global__ __launch_bounds__(256) void mask_clear_kernel(uint8_t* __restrict__ mask, int64_t bytes) {
-  const int64_t nvec = bytes / 16;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nvec; i += stride)
-    reinterpret_cast<uint4*>(mask)[i] = make_uint4(0u, 0u, 0u, 0u);
-  if (blockIdx.x == 0)
-    for (int64_t i = nvec * 16 + threadIdx.x; i < bytes; i += blockDim.x) mask[i] = 0;
-}
-
-__global__ __launch_bounds__(256) void mask_set_kernel(Geo g, SeqTab st,
-                                                        const int64_t* __restrict__ kept_offsets,
-                                                        const int32_t* __restrict__ kept_idx,
-                                                        uint8_t* __restrict__ mask) {
-  const int h = blockIdx.x % g.H;
-  const int bl = blockIdx.x / g.H;
-  const int l = blockIdx.y;
-  if (bl >= st.count) return;
-  const int n = st.len[bl];
-  const int64_t u = unit_index(g, l, st.first + bl, h);
-  const int64_t base = lht_base(g, l, h, st.start[bl]);
-  const int64_t k0 = kept_offsets[u], k1 = kept_offsets[u + 1];
-  for (int64_t i = k0 + threadIdx.x; i < k1; i += blockDim.x) {
-    const int j = kept_idx[i];
-    if (j >= 0 && j < n) mask[base + j] = 1;
-  }
-}
-
-certkv_status run_mask(const Geo& g, const std::vector<SeqTab>& tabs, const int64_t* kept_offsets,
-                       const int32_t* kept_idx, uint8_t* mask, hipStream_t s) {
-  const int64_t bytes = (int64_t)g.L * g.H * g.T;
-  const int64_t nvec = bytes / 16;
-  const unsigned blocks = (unsigned)(nvec / 256 + 1 < 4096 ? nvec / 256 + 1 : 4096);
-  CERTKV_LAUNCH("kept_mask_clear", mask_clear_kernel, dim3(blocks), dim3(256), 0, s, mask, bytes);
-  for (const SeqTab& t : tabs)
-    CERTKV_LAUNCH("kept_mask_set", mask_set_kernel, dim3(g.H * t.count, g.L), dim3(256), 0, s, g, t,
-                  kept_offsets, kept_idx, mask);
-  return CERTKV_OK;
-}
-
 certkv_status run_select(const SelectArgs& a, const SeqTab& st, hipStream_t s) {
   CERTKV_LAUNCH("select", select_kernel, dim3(a.g.H * st.count, a.g.L), dim3(kSelThreads), 0, s, a.g, st,
                 a.scores, a.sorted_keys, a.perm, (const int32_t*)a.budgets,
                 (const int64_t*)a.kept_offsets, a.kept_idx, a.capacity, a.evicted_sum, a.total_sum,
-                a.bitmap, a.bm_stride);
+                a.bitmap, a.bm_stride, a.mask);
   return CERTKV_OK;
 }
 

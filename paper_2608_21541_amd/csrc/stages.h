@@ -83,6 +83,7 @@ struct SelectArgs {
   double* total_sum;
   uint64_t* bitmap;
   int32_t bm_stride;
+  uint8_t* mask;             // optional [L][H][T]: 1 at kept positions, else 0
 };
 certkv_status run_coverage(const Geo& g, const SeqTab& st, const float* scores,
                            const uint32_t* sorted_keys, double retain, int32_t* budgets,
@@ -92,9 +93,6 @@ certkv_status run_offsets(int64_t U, int32_t slot, const int32_t* budgets, int64
                           int64_t* packed_offsets, hipStream_t s);
 certkv_status run_uniform_budgets(const Geo& g, const SeqTab& st, int32_t* budgets, hipStream_t s);
 certkv_status run_select(const SelectArgs& a, const SeqTab& st, hipStream_t s);
-certkv_status run_mask(const Geo& g, const std::vector<SeqTab>& tabs, const int64_t* kept_offsets,
-                       const int32_t* kept_idx, uint8_t* mask, hipStream_t s);
-
 struct TailArgs {
   Geo g;
   int32_t dtype;

@@ -62,3 +62,35 @@ def test_direct_tail_splits(name, lens):
                 scale = (w.abs() @ rows.abs()) / max(w.sum().item(), 1e-300)
                 assert ((got.cpu().double() - ref).abs() <= 2.0 ** -24 * ref.abs() + 1e-13 * scale).all()
         t0 += n
+
+
+@pytest.mark.parametrize("n", [16, 63, 64, 65, 1023, 1024, 1025, 16385, 40001])
+def test_coverage_budget_sizes(n):
+    # Rank ranges narrowed once, twice, not at all; ties with the retained
+    # mass (flat and quantized scores, retain = 1), where the serial sums
+    # decide; an all-zero head.  Budgets and masks equal the oracle's.
+    cfg = synth.config("C1", seqlens=[n], layers=2)
+    spec = spec_of(cfg)
+    s = _scores((2, 4, n), n)
+    s[0, 0] = 0.25
+    s[0, 1] = np.round(s[0, 1] * 4) / 4
+    s[0, 2] = 0.0
+    s[0, 3, 0] = 1e6
+    s[1, 0, n // 2:] = 0.0
+    s[1, 1] = -s[1, 1]
+    s[1, 2, ::5] = -1.0
+    st = torch.from_numpy(s).to(DEV)
+    for retain in (1e-9, 0.5, 0.9, 0.999, 1.0):
+        bud, off, idx, mask = ck.select(spec, st, mode="coverage", retain_mass=retain,
+                                        with_mask=True)
+        bud, off, idx, mask = bud.cpu(), off.tolist(), idx.cpu().numpy(), mask.cpu().numpy()
+        for u in range(8):
+            sh = s[u // 4, u % 4]
+            perm = oracle.order(sh)
+            k = oracle.coverage(sh, perm, retain)
+            assert bud[u].item() == k, (retain, u)
+            kept = oracle.select(perm, k)
+            assert np.array_equal(idx[off[u]:off[u + 1]], kept)
+            ref = np.zeros(n, np.uint8)
+            ref[kept] = 1
+            assert np.array_equal(mask[u // 4, u % 4], ref)
