@@ -62,9 +62,47 @@ struct Plan {
   int nsub_max;      // 16-rank allocation sub-blocks per unit
   int bm_words;      // 64-bit bitmap words per unit
   int nsplit;        // tail gather workgroups per unit
+  int seg_chunks;    // curves: chunks per segment
+  int nseg_max;      // curves: segments of the longest sequence (1: unsplit)
   int alloc;         // allocator: 0 Lagrangian + repair, 1 uniform, 2 greedy marginal
   const int64_t* cu;
 };
+
+constexpr int kCUs = 256;  // compute units of the device the plans are sized for
+
+// Segments of the curves walk.  A walk takes a compute unit to itself, so up
+// to kCUs workgroups run at once: unsplit, the longest unit's chunks are the
+// time; split into the shortest segments that still start together, a segment
+// is, plus the totals kernel's gather of the same rows (0.6 of a walk) and
+// its launch (about one chunk).  Measured: one layer of 8 heads at 32768
+// tokens (64 chunks, segments of 2) 406 us unsplit, 15 + 25 us split; eight
+// sequences of 8192 to 65536 (segments of 17 of the longest's 128 chunks) 807
+// us and 137 + 239; with a compute unit per unit already (32 layers of 8
+// heads) nothing is split.
+static void curve_split(Plan& P) {
+  int64_t max_nch = 0;
+  auto chunks = [&](int b) {
+    return (P.cu[b + 1] - P.cu[b] + kCurveChunk - 1) / kCurveChunk;
+  };
+  int64_t total = 0;
+  for (int b = 0; b < P.g.B; ++b) {
+    const int64_t c = chunks(b);
+    total += c;
+    if (c > max_nch) max_nch = c;
+  }
+  const int64_t LH = (int64_t)P.g.L * P.g.H;
+  P.seg_chunks = (int)max_nch;
+  P.nseg_max = 1;
+  if (P.U > kCUs) return;
+  for (int64_t sc = (total * LH + kCUs - 1) / kCUs; 16 * sc + 10 < 9 * max_nch; ++sc) {
+    int64_t wgs = 0;
+    for (int b = 0; b < P.g.B; ++b) wgs += (chunks(b) + sc - 1) / sc;
+    if (wgs * LH > kCUs) continue;
+    P.seg_chunks = (int)sc;
+    P.nseg_max = (int)((max_nch + sc - 1) / sc);
+    return;
+  }
+}
 
 static certkv_status make_plan(const certkv_problem* p, Plan* pl) {
   if (!p) return CERTKV_EINVAL;
@@ -121,14 +159,13 @@ static certkv_status make_plan(const certkv_problem* p, Plan* pl) {
   // window queries and the per-block reduction.
   int kpb = 256, kpb2 = 256;
   if (P.dtype == CERTKV_BF16) {
-    constexpr int64_t kCUs = 256;
     auto grow = [&](int64_t min_wgs) {
       int k = 512;
       while (k < 65536 && P.U * ((max_len + 2 * k - 1) / (2 * k)) >= min_wgs) k *= 2;
       return k;
     };
-    kpb = grow(4 * 2 * kCUs);
-    kpb2 = grow(4 * kCUs);
+    kpb = grow(4 * 2 * (int64_t)kCUs);
+    kpb2 = grow(4 * (int64_t)kCUs);
   }
   P.kpb = kpb;
   P.nkb_max = (max_len + kpb - 1) / kpb;
@@ -141,6 +178,7 @@ static certkv_status make_plan(const certkv_problem* p, Plan* pl) {
   // (about 200 kept rows each at a tenth kept), at most 128 per unit
   P.nsplit = (max_len + 2047) / 2048;
   if (P.nsplit > 128) P.nsplit = 128;
+  curve_split(P);
   return CERTKV_OK;
 }
 
@@ -233,6 +271,7 @@ struct Bufs {
   int32_t* cpos = nullptr;
   double* dmax = nullptr;
   double* vsum = nullptr;
+  double* segtot = nullptr;
   int64_t* repairs = nullptr;
   int32_t* alloc_sync = nullptr;
   // select / tail
@@ -279,6 +318,8 @@ static size_t layout(const Plan& P, uint32_t need, void* ws, Bufs* b) {
   }
   if (need & NEED_PERM) b->perm = w.take<int32_t>(LHT);
   if (need & NEED_CURVEBUF) b->curves = w.take<float>(LHT);
+  if ((need & NEED_CURVES) && P.nseg_max > 1)
+    b->segtot = w.take<double>((size_t)P.U * P.nseg_max * 32 * (P.g.D / 32 + 2));
   if (need & (NEED_CURVES | NEED_MINMAX)) {
     b->cmin = w.take<float>((size_t)P.U * P.nblk_max * 2);
     b->cmaxb = w.take<float>((size_t)P.U * P.nblk_max);
@@ -392,6 +433,9 @@ static certkv_status do_curves(const Plan& P, certkv_tensor v, const int32_t* pe
   a.dtype = P.dtype;
   a.curves = curves;
   a.vsum = vsum;
+  a.seg_chunks = P.seg_chunks;
+  a.nseg_max = P.nseg_max;
+  a.segtot = w.segtot;
   for (const SeqTab& t : make_tabs(P, nullptr, 0.f)) TRY(run_curves(a, t, s));
   return CERTKV_OK;
 }

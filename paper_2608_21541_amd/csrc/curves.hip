@@ -29,6 +29,14 @@
 // of row registers, no copies), and the order/score entries of chunk k-2 are
 // fetched at the top of chunk k.  Also emitted: sum_j (s_j)_+ v_j (the value
 // total of the tail summary).
+//
+// One workgroup fills a compute unit, and a unit's walk is one serial chain
+// of chunks, so with few units most of the chip idles.  Then the unit's
+// chunks are cut into segments, one workgroup each: a first kernel forms the
+// segments' totals (one more gather of the value rows, with every row
+// independent), and a segment's walk starts from the totals of the segments
+// above it, added from the top (deterministic).  curve_split() in api.hip
+// holds the rule.
 #include "stages.h"
 
 namespace certkv {
@@ -38,7 +46,7 @@ constexpr int kCurveWaves = kCurveThreads / 64;
 constexpr int kLPR = 32;                       // lanes per rank (a half-wave)
 constexpr int kRPH = 16;                       // ranks per half-wave and chunk
 constexpr int kSubs = 2 * kCurveWaves;         // sub-ranges per chunk
-constexpr int kCurveChunk = kSubs * kRPH;      // 512 ranks
+static_assert(kCurveChunk == kSubs * kRPH, "ranks of a chunk");  // 512
 
 template <int DP, int RAW, bool BF16>
 __device__ __forceinline__ void unpack_dims(const uint32_t (&raw)[RAW], float (&v)[DP]) {
@@ -113,6 +121,110 @@ __device__ __forceinline__ double uniform_f64(double x) {
                   __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32)));
 }
 
+// Totals of a segment's ranks, one record per lane as the walk keeps its
+// carry: W of the lane's dims, its part of Q, and m.  Segments 1.. of each unit
+// (no segment lies below segment 0, so its totals are not needed).  Bound by
+// the gather of the rows: a half-wave's next 16 rows are in flight together,
+// two workgroups to a compute unit.
+template <int D, bool BF16>
+__global__ __launch_bounds__(kCurveThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void curve_totals_kernel(
+    Geo g, SeqTab st, const uint32_t* __restrict__ sorted_keys, const int32_t* __restrict__ perm,
+    const double* __restrict__ ssum, const void* __restrict__ vc, int64_t v_sl, int64_t v_st,
+    int64_t v_sh, int32_t seg_chunks, int32_t nseg_max, double* __restrict__ segtot) {
+  constexpr int DP = D / kLPR;
+  constexpr int E = BF16 ? 2 : 4;
+  constexpr int RAW = DP * E / 4;
+  constexpr int NR = DP + 2;
+  __shared__ double tR[kCurveWaves][kLPR * NR];
+  __shared__ double wa[kCurveWaves][2 * kRPH];
+  __shared__ uint32_t wo[kCurveWaves][2 * kRPH];
+  const int seg = 1 + (int)(blockIdx.x % (nseg_max - 1));
+  const int hb = blockIdx.x / (nseg_max - 1);
+  const int h = hb % g.H;
+  const int bl = hb / g.H;
+  const int l = blockIdx.y;
+  if (bl >= st.count) return;
+  const int b = st.first + bl;
+  const int n = st.len[bl];
+  const int r_lo = seg * seg_chunks * kCurveChunk;
+  if (r_lo >= n) return;
+  const int r_hi = min(n, r_lo + seg_chunks * kCurveChunk);
+  const int64_t tok0 = st.start[bl];
+  const int64_t base = lht_base(g, l, h, tok0);
+  const int64_t u = unit_index(g, l, b, h);
+  const int lane = threadIdx.x & 63;
+  const int wave = threadIdx.x >> 6;
+  const int hf = lane >> 5;
+  const int li = lane & (kLPR - 1);
+  const double tot = ssum[u];
+  const double wden = uniform_f64(tot > 0.0 ? tot : (double)n);
+  const BufRsrc vrs = make_rsrc(
+      static_cast<const char*>(vc) + ((int64_t)l * v_sl + tok0 * v_st + (int64_t)h * v_sh) * E,
+      (uint32_t)(((int64_t)(n - 1) * v_st + D) * E));
+  const uint32_t vrow_bytes = (uint32_t)(v_st * E);
+  const uint32_t vlane = (uint32_t)(li * DP * E);
+  const BufRsrc krs = make_rsrc(sorted_keys + base, (uint32_t)n * 4u);
+  const BufRsrc prs = make_rsrc(perm + base, (uint32_t)n * 4u);
+
+  double sW[DP], sq = 0.0, sm = 0.0;
+#pragma unroll
+  for (int t = 0; t < DP; ++t) sW[t] = 0.0;
+  // the wave's 32 ranks of a chunk: lanes 0-31 fetch one order entry each
+  uint32_t key, pos;
+  auto fetch = [&](int r0) {
+    const uint32_t off = (uint32_t)(r0 + wave * 2 * kRPH + li) * 4u;  // past n: zeros
+    key = buf_load_u32(krs, off);
+    pos = buf_load_u32(prs, off);
+  };
+  fetch(r_lo);
+  for (int r0 = r_lo; r0 < r_hi; r0 += kCurveChunk) {
+    if (lane < 2 * kRPH) {
+      const bool valid = r0 + wave * 2 * kRPH + li < r_hi;
+      const float x = desc_key_value(key);
+      const double num = tot > 0.0 ? (x > 0.f ? (double)x : 0.0) : 1.0;
+      wa[wave][li] = valid ? num / wden : 0.0;
+      wo[wave][li] = (uint32_t)(valid ? min(max((int)pos, 0), n - 1) : 0) * vrow_bytes;
+    }
+    __asm__ volatile("" ::: "memory");  // wave-private table, accesses in program order
+    uint32_t raw[kRPH][RAW];
+#pragma unroll
+    for (int r = 0; r < kRPH; ++r) load_words<RAW>(vrs, wo[wave][hf * kRPH + r] + vlane, raw[r]);
+    fetch(r0 + kCurveChunk);
+#pragma unroll
+    for (int r = 0; r < kRPH; ++r) {
+      const double ar = wa[wave][hf * kRPH + r];
+      float v[DP];
+      unpack_dims<DP, RAW, BF16>(raw[r], v);
+      double vv = 0.0;
+#pragma unroll
+      for (int t = 0; t < DP; ++t) {
+        const double vd = (double)v[t];
+        sW[t] = fma(ar, vd, sW[t]);
+        vv = fma(vd, vd, vv);
+      }
+      sq = fma(ar, vv, sq);
+      sm += ar;
+    }
+    __asm__ volatile("" ::: "memory");
+  }
+  double tp[NR], bt[NR];
+#pragma unroll
+  for (int t = 0; t < DP; ++t) halves(sW[t], tp[t], bt[t]);
+  halves(sq, tp[DP], bt[DP]);
+  halves(sm, tp[DP + 1], bt[DP + 1]);
+  if (hf == 0) {
+#pragma unroll
+    for (int t = 0; t < NR; ++t) tR[wave][li * NR + t] = tp[t] + bt[t];
+  }
+  __syncthreads();
+  if (threadIdx.x < kLPR * NR) {
+    double run = 0.0;
+#pragma unroll
+    for (int w = 0; w < kCurveWaves; ++w) run += tR[w][threadIdx.x];
+    segtot[(u * nseg_max + seg) * (kLPR * NR) + threadIdx.x] = run;
+  }
+}
+
 // STAT: the curve statistic (0 centered, 1 uncentered, 2 tail mass), fixed at
 // compile time so that the walk has no branch on it; -1 reads it from g.stat
 // at run time (not launched: each statistic has its own instantiation).
@@ -120,7 +232,8 @@ template <int D, bool BF16, int STAT>
 __global__ __launch_bounds__(kCurveThreads) void curves_kernel(
     Geo g, SeqTab st, const uint32_t* __restrict__ sorted_keys, const int32_t* __restrict__ perm,
     const double* __restrict__ ssum, const void* __restrict__ vc, int64_t v_sl, int64_t v_st,
-    int64_t v_sh, float* __restrict__ curves, double* __restrict__ vsum) {
+    int64_t v_sh, int32_t seg_chunks, int32_t nseg_max, const double* __restrict__ segtot,
+    float* __restrict__ curves, double* __restrict__ vsum) {
   constexpr int DP = D / kLPR;                 // dims per lane
   constexpr int E = BF16 ? 2 : 4;              // bytes per element
   constexpr int RAW = DP * E / 4;              // 32-bit words per lane per row
@@ -144,12 +257,18 @@ __global__ __launch_bounds__(kCurveThreads) void curves_kernel(
   // conflicts)
   __shared__ __align__(16) double red[kCurveWaves][64][9];
 
-  const int h = blockIdx.x % g.H;
-  const int bl = blockIdx.x / g.H;
+  const int seg = blockIdx.x % nseg_max;  // 0 of 1: the whole unit
+  const int hb = blockIdx.x / nseg_max;
+  const int h = hb % g.H;
+  const int bl = hb / g.H;
   const int l = blockIdx.y;
   if (bl >= st.count) return;
   const int b = st.first + bl;
   const int n = st.len[bl];
+  const int nch = (n + kCurveChunk - 1) / kCurveChunk;
+  const int k_lo = seg * seg_chunks;  // chunks [k_lo, k_hi) of the unit
+  if (k_lo >= nch) return;
+  const int k_hi = min(nch, k_lo + seg_chunks);
   const int64_t tok0 = st.start[bl];
   const int64_t base = lht_base(g, l, h, tok0);
   const int64_t u = unit_index(g, l, b, h);
@@ -179,7 +298,7 @@ __global__ __launch_bounds__(kCurveThreads) void curves_kernel(
   // that no branch splits the pipelined loads; `valid` marks real ranks.
   auto fetch_meta = [&](int k, uint32_t& key, int& pos, bool& valid) {
     const int rk = rank_of(k, 2 * wave + (li >> 4), li & (kRPH - 1));
-    valid = k >= 0 && rk < n;
+    valid = k >= k_lo && rk < n;
     const uint32_t idx = (uint32_t)min(max(rk, 0), n - 1) * 4u;
     key = buf_load_u32(krs, idx);
     pos = (int)buf_load_u32(prs, idx);
@@ -212,8 +331,14 @@ __global__ __launch_bounds__(kCurveThreads) void curves_kernel(
     return (r & 1) ? p.y : p.x;
   };
 
-  const int nch = (n + kCurveChunk - 1) / kCurveChunk;
-  for (int i = threadIdx.x; i < kLPR * NR; i += kCurveThreads) (&cR[0][0])[i] = 0.0;
+  // carry into the segment: the totals of the segments above it, from the top
+  if (threadIdx.x < kLPR * NR) {
+    double run = 0.0;
+    const double* t = segtot + u * nseg_max * (kLPR * NR) + threadIdx.x;
+#pragma unroll 8
+    for (int x = (nch - 1) / seg_chunks; x > seg; --x) run += t[x * (kLPR * NR)];
+    (&cR[0][0])[threadIdx.x] = run;
+  }
 
   uint32_t k_n1, k_n2;
   int p_n1, p_n2;
@@ -223,9 +348,9 @@ __global__ __launch_bounds__(kCurveThreads) void curves_kernel(
     uint32_t k0;
     int p0;
     bool ok0;
-    fetch_meta(nch - 1, k0, p0, ok0);
-    fetch_meta(nch - 2, k_n1, p_n1, ok_n1);
-    publish(nch - 1, k0, p0, ok0);
+    fetch_meta(k_hi - 1, k0, p0, ok0);
+    fetch_meta(k_hi - 2, k_n1, p_n1, ok_n1);
+    publish(k_hi - 1, k0, p0, ok0);
   }
   // The first chunk's rows one by one in step order, the order in which the
   // walk fetches them: with the same order on both paths into the loop, the
@@ -233,11 +358,11 @@ __global__ __launch_bounds__(kCurveThreads) void curves_kernel(
   // separately rather than for all of them.
 #pragma unroll
   for (int r = 0; r < kRPH; ++r) {
-    fetch_row((nch - 1) & 1, r, vcur[r]);
+    fetch_row((k_hi - 1) & 1, r, vcur[r]);
     __builtin_amdgcn_sched_barrier(0);
   }
 
-  for (int k = nch - 1; k >= 0; --k) {
+  for (int k = k_hi - 1; k >= k_lo; --k) {
     const int par = k & 1;
     // pipeline: order entries two chunks ahead; the table of chunk k-1 (slot
     // par ^ 1), whose rows the walk below fetches
@@ -384,20 +509,25 @@ __global__ __launch_bounds__(kCurveThreads) void curves_kernel(
     p_n1 = p_n2;
     ok_n1 = ok_n2;
   }
-  // the carry after the last chunk: the sums over every rank
+  // the carry after the unit's last chunk: the sums over every rank
   __syncthreads();
-  if (vsum && wave == 0) {
+  if (vsum && seg == 0 && wave == 0) {
     for (int i = lane; i < D; i += 64) vsum[u * D + i] = cR[i / DP][i % DP] * tot;
   }
 }
 
 template <int D, bool BF16>
 static certkv_status launch_curves(const CurveArgs& a, const SeqTab& st, hipStream_t s) {
-  const dim3 grid(a.g.H * st.count, a.g.L);
+  const dim3 grid(a.g.H * st.count * a.nseg_max, a.g.L);
+  if (a.nseg_max > 1)
+    CERTKV_LAUNCH("curve_totals", (curve_totals_kernel<D, BF16>),
+                  dim3(a.g.H * st.count * (a.nseg_max - 1), a.g.L), dim3(kCurveThreads), 0, s, a.g,
+                  st, a.sorted_keys, a.perm, a.ssum, a.v.ptr, a.v.s_layer, a.v.s_token, a.v.s_head,
+                  a.seg_chunks, a.nseg_max, a.segtot);
 #define CERTKV_CURVES(STAT)                                                                        \
   CERTKV_LAUNCH("curves", (curves_kernel<D, BF16, STAT>), grid, dim3(kCurveThreads), 0, s, a.g, st, \
                 a.sorted_keys, a.perm, a.ssum, a.v.ptr, a.v.s_layer, a.v.s_token, a.v.s_head,       \
-                a.curves, a.vsum)
+                a.seg_chunks, a.nseg_max, (const double*)a.segtot, a.curves, a.vsum)
   if (a.g.stat == 0)
     CERTKV_CURVES(0);
   else if (a.g.stat == 1)

@@ -41,6 +41,7 @@ struct SortArgs {
 };
 certkv_status run_sort(const SortArgs& a, const SeqTab& st, hipStream_t s);
 
+constexpr int kCurveChunk = 512;  // ranks a curves workgroup walks at a time
 struct CurveArgs {
   Geo g;
   const uint32_t* sorted_keys;
@@ -50,6 +51,9 @@ struct CurveArgs {
   int32_t dtype;
   float* curves;
   double* vsum;
+  int32_t seg_chunks;        // chunks per segment, and segments of the longest
+  int32_t nseg_max;          // sequence (1: one workgroup walks a whole unit)
+  double* segtot;            // [U][nseg_max][32][d/32 + 2] segment totals
 };
 certkv_status run_curves(const CurveArgs& a, const SeqTab& st, hipStream_t s);
 

@@ -94,3 +94,47 @@ def test_coverage_budget_sizes(n):
             ref = np.zeros(n, np.uint8)
             ref[kept] = 1
             assert np.array_equal(mask[u // 4, u % 4], ref)
+
+
+@pytest.mark.parametrize("lens,heads,layers", [
+    ([4096], 4, 1),                  # segments of one chunk
+    ([5120 + 1], 8, 1),              # one rank in the last chunk
+    ([20000, 1024, 513], 8, 1),      # units of forty chunks, two chunks and a rank, and two
+    ([40000, 511], 16, 2),           # segments of several chunks beside a unit of one
+])
+@pytest.mark.parametrize("name", ["C2", "C1"])
+def test_curve_segments(name, lens, heads, layers):
+    # A unit's curve walk cut into segments: curves, order, value totals and
+    # budgets against the oracle's one-piece sums.
+    cfg = synth.config(name, seqlens=lens, layers=layers)
+    cfg.kv_heads = heads
+    cache = synth.make_cache(cfg, "cpu")
+    spec = spec_of(cfg)
+    s = _scores((layers, heads, sum(lens)), 7)
+    s[0, 0] = 0.5                                # flat: every key ties
+    s[-1, 1, ::2] = 0.0
+    n_keep = [max(2, n // 10) for n in lens]
+    al = ck.allocate(spec, torch.from_numpy(s).to(DEV), cache["v"].to(DEV), n_keep,
+                     with_perm=True, with_curves=True, with_vsum=True)
+    al = {x: y.cpu().numpy() for x, y in al.items()}
+    v = cache["v"].double().numpy()
+    for l in range(layers):
+        t0 = 0
+        for b, n in enumerate(lens):
+            got = al["curves"][l, :, t0:t0 + n]
+            for h in range(heads):
+                perm = oracle.order(s[l, h, t0:t0 + n])
+                assert np.array_equal(al["perm"][l, h, t0:t0 + n], perm)
+                vh = v[l, t0:t0 + n, h]
+                c = oracle.curves(s[l, h, t0:t0 + n], perm, vh)[0]
+                # (the block checks' bound: fp64 sums in another order)
+                tol = 4.0 * np.spacing(c.astype(np.float32)).astype(np.float64) + 1e-6 * c.max()
+                assert (np.abs(got[h] - c) <= tol).all()
+                u = (l * len(lens) + b) * heads + h
+                w = np.maximum(s[l, h, t0:t0 + n], 0).astype(np.float64)
+                ref, scale = w @ vh, w @ np.abs(vh)
+                assert (np.abs(al["vsum"][u] - ref) <= n * 2.0 ** -51 * scale).all()
+            u0 = (l * len(lens) + b) * heads
+            ref, _ = oracle.allocate(got, n_keep[b])
+            assert np.array_equal(al["budgets"][u0:u0 + heads], ref)
+            t0 += n
