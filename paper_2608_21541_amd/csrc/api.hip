@@ -64,6 +64,8 @@ struct Plan {
   int nsplit;        // tail gather workgroups per unit
   int seg_chunks;    // curves: chunks per segment
   int nseg_max;      // curves: segments of the longest sequence (1: unsplit)
+  int sort_nb;       // sort: buckets of the longest sequence (0: not split)
+  int sort_ntile;    // sort: tiles of the longest sequence
   int alloc;         // allocator: 0 Lagrangian + repair, 1 uniform, 2 greedy marginal
   const int64_t* cu;
 };
@@ -102,6 +104,18 @@ static void curve_split(Plan& P) {
     P.nseg_max = (int)((max_nch + sc - 1) / sc);
     return;
   }
+}
+
+// Buckets of the longest sequence for the sort (see sort.hip); 0: one
+// workgroup per unit.  The bucket sort is the faster one wherever its samples
+// fit one LDS sort (up to 262144 keys): with one workgroup per unit and with
+// buckets, launch by launch, 8 units of 32768 keys 130 and 37 us, 64 of 65536
+// 254 and 91, 256 of 32768 150 and 136, 256 of 131072 716 and 500 (716 and 667
+// on scores with planted keys).  (256 of 8192: 45 and 58 with each launch timed
+// apart, which costs 4 us per launch.)
+static int sort_buckets(const Plan& P) {
+  const int nb = sort_nb(P.max_len);
+  return nb <= kSortNb ? nb : 0;
 }
 
 static certkv_status make_plan(const certkv_problem* p, Plan* pl) {
@@ -179,6 +193,8 @@ static certkv_status make_plan(const certkv_problem* p, Plan* pl) {
   P.nsplit = (max_len + 2047) / 2048;
   if (P.nsplit > 128) P.nsplit = 128;
   curve_split(P);
+  P.sort_nb = sort_buckets(P);
+  P.sort_ntile = (int)(((int64_t)max_len + kSortRun - 1) / kSortRun);
   return CERTKV_OK;
 }
 
@@ -265,6 +281,10 @@ struct Bufs {
   int32_t *valsA = nullptr, *valsB = nullptr;
   int32_t* perm = nullptr;
   double* ssum = nullptr;
+  uint64_t* splitters = nullptr;
+  uint2* windows = nullptr;
+  uint32_t *sort_counts = nullptr, *bucket_start = nullptr;
+  double* tile_sum = nullptr;
   float* curves = nullptr;
   float* cmin = nullptr;
   float* cmaxb = nullptr;
@@ -315,6 +335,13 @@ static size_t layout(const Plan& P, uint32_t need, void* ws, Bufs* b) {
     b->valsA = w.take<int32_t>(LHT);
     b->valsB = w.take<int32_t>(LHT);
     b->ssum = w.take<double>((size_t)P.U);
+    if (P.sort_nb > 1) {
+      b->splitters = w.take<uint64_t>((size_t)P.U * P.sort_nb);
+      b->windows = w.take<uint2>((size_t)P.U * P.sort_nb);
+      b->sort_counts = w.take<uint32_t>((size_t)P.U * P.sort_ntile * P.sort_nb);
+      b->bucket_start = w.take<uint32_t>((size_t)P.U * (P.sort_nb + 1));
+      b->tile_sum = w.take<double>((size_t)P.U * P.sort_ntile);
+    }
   }
   if (need & NEED_PERM) b->perm = w.take<int32_t>(LHT);
   if (need & NEED_CURVEBUF) b->curves = w.take<float>(LHT);
@@ -418,6 +445,13 @@ static certkv_status do_sort(const Plan& P, const float* scores, int32_t* perm, 
   a.valsB = w.valsB;
   a.perm_out = perm;
   a.ssum = w.ssum;
+  a.nb_max = P.sort_nb;
+  a.ntile_max = P.sort_ntile;
+  a.splitters = w.splitters;
+  a.windows = w.windows;
+  a.counts = w.sort_counts;
+  a.bucket_start = w.bucket_start;
+  a.tile_sum = w.tile_sum;
   for (const SeqTab& t : make_tabs(P, nullptr, 0.f)) TRY(run_sort(a, t, s));
   return CERTKV_OK;
 }

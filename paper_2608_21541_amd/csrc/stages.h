@@ -32,12 +32,30 @@ inline int score_nqt(int M) {
 }
 certkv_status run_score(const ScoreArgs& a, const SeqTab& st, int max_len, hipStream_t s);
 
+constexpr int kSortRun = 4096;  // elements a workgroup sorts in LDS at most
+constexpr int kSortOver = 32;   // samples per bucket
+constexpr int kSortNb = kSortRun / kSortOver;  // buckets of a unit at most
+// Buckets of a unit of n elements: one up to kSortRun, else of half of it on
+// average (a bucket spans the gaps between 32 samples, so with keys in no
+// particular order about 3 in a million exceed twice the average).
+__host__ __device__ inline int sort_nb(int n) {
+  return n <= kSortRun ? 1 : (int)((2 * (int64_t)n + kSortRun - 1) / kSortRun);
+}
 struct SortArgs {
   Geo g;
   const float* scores;
   uint32_t *keysA, *keysB, *keys_out;
   int32_t *valsA, *valsB, *perm_out;
   double* ssum;
+  // split by value into buckets (nb_max = buckets of the longest sequence; 1:
+  // every unit fits one LDS sort; 0: one workgroup sorts a unit through memory)
+  int32_t nb_max;
+  int32_t ntile_max;         // tiles of kSortRun elements of the longest sequence
+  uint64_t* splitters;       // [U][nb_max]
+  uint2* windows;            // [U][nb_max] keys that most of a bucket lies between
+  uint32_t* counts;          // [U][ntile_max][nb_max]
+  uint32_t* bucket_start;    // [U][nb_max + 1]
+  double* tile_sum;          // [U][ntile_max]
 };
 certkv_status run_sort(const SortArgs& a, const SeqTab& st, hipStream_t s);
 

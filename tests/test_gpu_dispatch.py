@@ -138,3 +138,42 @@ def test_curve_segments(name, lens, heads, layers):
             ref, _ = oracle.allocate(got, n_keep[b])
             assert np.array_equal(al["budgets"][u0:u0 + heads], ref)
             t0 += n
+
+
+@pytest.mark.parametrize("lens", [[16], [4095], [4096, 33], [4097, 4096], [8193], [32768, 100, 5000],
+                                  [32769], [70001, 33000], [262144], [262145]])
+@pytest.mark.parametrize("keep_window", [False, True])
+def test_sort_sizes(lens, keep_window):
+    # One LDS sort, buckets by value beside units of one, and the edges between
+    # them: random scores, ties (flat, quantized, signed zeros), order that
+    # follows the position, and keys that the evenly spaced samples miss (every
+    # sixteenth position and its neighbours loud), so that a bucket outgrows
+    # LDS and is sorted through memory.
+    cfg = synth.config("C1", seqlens=lens, layers=2)
+    n_all, w = sum(lens), cfg.window
+    s = _scores((2, 4, n_all), n_all)
+    s[0, 1] = 0.5
+    s[0, 2] = np.round(s[0, 2] * 2) / 2 - 1.0
+    s[0, 2, ::7] = -0.0
+    s[0, 3] = np.arange(n_all) / n_all
+    s[1, 0] = np.arange(n_all)[::-1] / n_all
+    s[1, 1, : n_all // 3] += 1e4
+    s[1, 2] = 1.0
+    s[1, 2, ::85] += 1.0 + _scores(len(s[1, 2, ::85]), 5)
+    s[1, 2, 1::85] += np.float32(1e-3) * _scores(len(s[1, 2, 1::85]), 6)
+    s[1, 3, : n_all // 2] = 0.25                 # one long tie across runs, then spread scores
+    spec = spec_of(cfg)
+    spec.keep_window = keep_window
+    v = torch.zeros((2, n_all, 4, 64), device=DEV)
+    if keep_window and min(lens) <= w:
+        pytest.skip("the window is the whole sequence: nothing to evict")
+    # (a kept window needs b_min = floor(alpha (n_keep - 1)) >= w)
+    perm = ck.allocate(spec, torch.from_numpy(s).to(DEV), v, list(lens), alpha=1.0,
+                       with_perm=True)["perm"].cpu().numpy()
+    for l in range(2):
+        for h in range(4):
+            t0 = 0
+            for n in lens:
+                ref = oracle.order(s[l, h, t0:t0 + n], keep_window=w if keep_window else 0)
+                assert np.array_equal(perm[l, h, t0:t0 + n], ref), (l, h, n)
+                t0 += n
