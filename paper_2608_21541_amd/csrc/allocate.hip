@@ -24,6 +24,23 @@
 // sum b_h: a bisection over the ordered bit patterns of fp64 keys finds it,
 // counting per head with block-level running maxima (LDS) and one scan of the
 // block where the running maximum crosses the threshold.
+//
+// Hull.  For any lambda >= 0 the smallest f lies on the lower convex hull of the
+// points (b, c(b)), b >= b_min: a few hundred of them, because the curves are
+// noisy.  So the points that can never be an argmin are dropped first: p
+// between a and c is dropped if it lies above their chord by more than the
+// rounding of f can hide (hull_above), which leaves every f of the argmin and
+// of its ties in place.  Two kernels filter (chunks of 2 or 8 blocks, then
+// a unit's chunks) and one workgroup per (layer, sequence) bisects over the
+// remaining points in LDS.  Its repair finds the R-th smallest key by value
+// among the block maxima and then in the few blocks where the running maxima
+// rise past it.  The searches above remain for curves whose hull is large
+// (convex without noise: tail masses; flat or linear ones) and for sizes beyond
+// LDS: the hull kernel leaves those (layer, sequence)s to them.
+// Block statistics and allocation, before and with the hull: one layer of 8
+// heads at 32768 tokens 13 + 212 us and 14 + 17 + 47 us, eight ragged sequences
+// 16 + 229 and 29 + 27 + 51, 32 layers at 131072 57 + 305 and 143 + 21 + 60; the
+// full search's launch that follows finds nothing to do in 2 us.
 #include <type_traits>
 
 #include "stages.h"
@@ -36,6 +53,14 @@ constexpr int kHeadGroup = kAllocThreads / 32;  // heads handled concurrently (3
 constexpr int kCandCap = 1024;    // candidate blocks evaluated per round
 constexpr int kBlk = 256;          // ranks per pruning block
 constexpr int kLdsItems = 8192;    // H * blocks handled from LDS
+// Hull points kept of a chunk (of 2 or 8 blocks), joined for a unit, and of a
+// unit; doubles of the hull kernel's LDS pool and its loaded blocks at most.
+constexpr int kChunkList = 512;    // of a chunk's list while it is filtered
+constexpr int kChunkCap = 128;
+constexpr int kMergeCap = 8192;
+constexpr int kUnitCap = 1024;
+constexpr int kHullPool = 15360;
+constexpr int kHullSlots = 64;
 constexpr int kRepairWin = 64;     // cached curve values per head (fallback repair)
 constexpr int kRcStride = kBlk + 4;  // a cached curve block of the repair search: kBlk + 1 values
 // Bisection across several workgroups per (layer, sequence): up to kTreeLev
@@ -52,6 +77,8 @@ constexpr size_t kSyncArg = kSyncSum + (size_t)kSyncGroups * 2 * kTreeMax * 2;
 constexpr size_t kSyncWords = kSyncArg + (size_t)kSyncGroups * 2 * kTreeMax * 64;
 
 size_t alloc_sync_words() { return kSyncWords; }
+size_t alloc_chunk_points() { return kChunkCap; }
+size_t alloc_unit_points() { return kUnitCap; }
 
 // Lanes below this one among those set in `mask`.
 __device__ __forceinline__ uint32_t count_below64(uint64_t mask) {
@@ -173,6 +200,45 @@ __device__ __forceinline__ BestFB wave_lexmin(double f, int b) {
   return BestFB{f, b};
 }
 
+// Minimum of a double, and sum of an int, over the wave, in every lane.
+__device__ __forceinline__ double wave_min_f64(double x) {
+  auto join = [](uint32_t lo, uint32_t hi) {
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+  };
+  auto dpp = [&](auto ctl) {
+    const uint64_t u = (uint64_t)__double_as_longlong(x);
+    const int lo = (int)(uint32_t)u, hi = (int)(uint32_t)(u >> 32);
+    x = fmin(x, join((uint32_t)__builtin_amdgcn_update_dpp(lo, lo, decltype(ctl)::value, 0xF, 0xF, false),
+                     (uint32_t)__builtin_amdgcn_update_dpp(hi, hi, decltype(ctl)::value, 0xF, 0xF, false)));
+  };
+  dpp(std::integral_constant<int, 0xB1>());
+  dpp(std::integral_constant<int, 0x4E>());
+  dpp(std::integral_constant<int, 0x141>());
+  dpp(std::integral_constant<int, 0x140>());
+  {
+    const uint64_t u = (uint64_t)__double_as_longlong(x);
+    const uint32_t lo = (uint32_t)u, hi = (uint32_t)(u >> 32);
+    const auto a = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto b = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    x = fmin(join(a[0], b[0]), join(a[1], b[1]));
+  }
+  const uint64_t u = (uint64_t)__double_as_longlong(x);
+  const uint32_t lo = (uint32_t)u, hi = (uint32_t)(u >> 32);
+  const auto a = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+  const auto b = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+  return fmin(join(a[0], b[0]), join(a[1], b[1]));
+}
+__device__ __forceinline__ int wave_sum_i32(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0xB1, 0xF, 0xF, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x4E, 0xF, 0xF, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x141, 0xF, 0xF, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x140, 0xF, 0xF, false);
+  const auto a = __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)x, false, false);
+  x = (int)a[0] + (int)a[1];
+  const auto b = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)x, false, false);
+  return (int)b[0] + (int)b[1];
+}
+
 // Monotone map between fp64 values and unsigned keys (total order of doubles).
 __device__ __forceinline__ uint64_t dkey(double x) {
   const uint64_t u = (uint64_t)__double_as_longlong(x);
@@ -187,11 +253,10 @@ __device__ __forceinline__ double dval(uint64_t k) {
 // each 256-rank block (+inf where a half is past the end), maximum of c over
 // the block, the smallest position holding the block minimum, and the
 // maximum marginal d(i) = c(i+1) - c(i) (fp64) over the i of the block with
-// i <= n-2.  One wave per kBsBlocks consecutive blocks, the loads of all of
+// i <= n-2.  One wave per NB consecutive blocks (a chunk), the loads of all of
 // them in flight at once (positions clamped into the segment, masked where
 // used); lane L covers positions 4L..4L+3 of a block (lanes 0-31 the first
 // half), and the wave reductions are DPP and lane-row exchanges.
-constexpr int kBsBlocks = 8;
 
 template <typename T, typename F>
 __device__ __forceinline__ T wave_reduce_dpp(T x, F op) {
@@ -217,18 +282,80 @@ __device__ __forceinline__ T wave_reduce_dpp(T x, F op) {
   return op(__builtin_bit_cast(T, b0), __builtin_bit_cast(T, b1));
 }
 
+// Whether point p = (b, c) lies above the chord of the points a and d around it
+// by more than rounding can hide, so that it is never an argmin.  Let s be the
+// chord's fall per rank and h the height above it.  For lambda >= s, f(p) - f(a)
+// = (lambda - s)(p - a) + h, and for lambda < s, f(p) - f(d) = (s - lambda)(d - p)
+// + h, both exactly; each f carries one rounding, u = 2^-53 of its size, and the
+// size at lambda = s, where the difference is smallest, is at most max(s, 0) p +
+// |c|.  So h above 2 u (max(s, 0) p + |c_p| + |c_a| + |c_d|) decides for every
+// lambda; the factor taken, 36 u, also covers the rounding of h here.  (A
+// non-finite value is never above anything, and nothing is above it.)
+__device__ __forceinline__ bool hull_above(int ba, float ca, int bp, float cp, int bd, float cd) {
+  const double da = (double)(bp - ba), dd = (double)(bd - bp);
+  const double xa = (double)ca, xp = (double)cp, xd = (double)cd;
+  const double rise = (xp - xa) * dd + (xp - xd) * da;  // h (d - a)
+  const double size = (fabs(xa) + fabs(xp) + fabs(xd)) * (da + dd) + fmax(xa - xd, 0.0) * (double)bp;
+  return rise > 4e-15 * size;
+}
+
+// Drop the points of an ascending list above the chord of their neighbours,
+// until none is left or `rounds` are done; the first and the last stay.  One
+// wave, 256 points at a time (four of a lane's in flight); the list is compacted
+// in place (a batch writes no place that a later one still reads as another
+// point).  Points dropped together may be each other's neighbours: each is
+// beaten at every lambda by some point of the list, and the argmin by none.
+__device__ __forceinline__ int hull_filter(uint2* pts, int m, int rounds, int lane) {
+  constexpr int Q = 4;
+  for (int it = 0; it < rounds && m > 2; ++it) {
+    int out = 0;
+    for (int r0 = 0; r0 < m; r0 += 64 * Q) {
+      uint2 a[Q], x[Q], d[Q];
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        const int i = r0 + 64 * q + lane;
+        a[q] = pts[min(max(i - 1, 0), m - 1)];
+        x[q] = pts[min(i, m - 1)];
+        d[q] = pts[min(i + 1, m - 1)];
+      }
+      __asm__ volatile("" ::: "memory");  // a wave's LDS accesses execute in order
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        const int i = r0 + 64 * q + lane;
+        if (r0 + 64 * q >= m) break;
+        const bool keep = i < m && (i == 0 || i == m - 1 ||
+                                    !hull_above((int)a[q].x, __uint_as_float(a[q].y), (int)x[q].x,
+                                                __uint_as_float(x[q].y), (int)d[q].x,
+                                                __uint_as_float(d[q].y)));
+        const uint64_t bal = __ballot(keep);
+        if (keep) pts[out + (int)count_below64(bal)] = x[q];
+        out += (int)__popcll(bal);
+      }
+      __asm__ volatile("" ::: "memory");
+    }
+    if (out == m) break;
+    m = out;
+  }
+  return m;
+}
+
+template <bool HULL, int NB>
 __global__ __launch_bounds__(256) void curve_blockstats_kernel(Geo g, SeqTab st, int32_t nblk_max,
                                                                const float* __restrict__ curves,
                                                                float* __restrict__ cmin,
                                                                float* __restrict__ cmaxb,
                                                                int32_t* __restrict__ cpos,
                                                                double* __restrict__ dmax,
-                                                               int32_t* __restrict__ sync, int32_t nsync) {
+                                                               int32_t* __restrict__ sync, int32_t nsync,
+                                                               int32_t nchunk_max,
+                                                               uint2* __restrict__ hull_pts,
+                                                               int32_t* __restrict__ hull_cnt) {
+  __shared__ __align__(16) uint2 hlist[HULL ? 4 : 1][HULL ? kChunkList : 1];
   // the allocation's exchange words (ticket, tagged sums) start at zero: the
   // first workgroup clears them for the allocation kernel launched next
   if (sync && blockIdx.x == 0 && blockIdx.y == 0)
     for (int i = threadIdx.x; i < nsync; i += 256) sync[i] = 0;
-  const int per_unit = (nblk_max + 4 * kBsBlocks - 1) / (4 * kBsBlocks);
+  const int per_unit = (nblk_max + 4 * NB - 1) / (4 * NB);
   const int wb = blockIdx.x % per_unit;
   const int hb = blockIdx.x / per_unit;
   const int h = hb % g.H;
@@ -238,13 +365,13 @@ __global__ __launch_bounds__(256) void curve_blockstats_kernel(Geo g, SeqTab st,
   const int n = st.len[bl];
   const int nblk = (n + kBlk - 1) / kBlk;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int k0 = (wb * 4 + wave) * kBsBlocks;
+  const int k0 = (wb * 4 + wave) * NB;
   if (k0 >= nblk) return;
   const int64_t u = unit_index(g, l, st.first + bl, h);
   const float* ch = curves + lht_base(g, l, h, st.start[bl]);
-  float c[kBsBlocks][5];
+  float c[NB][5];
 #pragma unroll
-  for (int j = 0; j < kBsBlocks; ++j) {
+  for (int j = 0; j < NB; ++j) {
     const int i0 = (k0 + j) * kBlk + lane * 4;
 #pragma unroll
     for (int e = 0; e < 5; ++e) c[j][e] = ch[min(i0 + e, n - 1)];
@@ -252,7 +379,7 @@ __global__ __launch_bounds__(256) void curve_blockstats_kernel(Geo g, SeqTab st,
   // a caller's non-finite curve values: reported, then read as cval() reads them
   bool bad = false;
 #pragma unroll
-  for (int j = 0; j < kBsBlocks; ++j) {
+  for (int j = 0; j < NB; ++j) {
 #pragma unroll
     for (int e = 0; e < 5; ++e) {
       bad |= !isfinite(c[j][e]);
@@ -261,7 +388,7 @@ __global__ __launch_bounds__(256) void curve_blockstats_kernel(Geo g, SeqTab st,
   }
   if (__ballot(bad) != 0ull && lane == 0) report_nonfinite(g);
 #pragma unroll
-  for (int j = 0; j < kBsBlocks; ++j) {
+  for (int j = 0; j < NB; ++j) {
     const int k = k0 + j;
     if (k >= nblk) break;
     const int i0 = k * kBlk + lane * 4;
@@ -293,13 +420,706 @@ __global__ __launch_bounds__(256) void curve_blockstats_kernel(Geo g, SeqTab st,
       dmax[u * nblk_max + k] = dm;
     }
   }
+  if constexpr (HULL) {
+    // The chunk's hull points.  An anchor per block, the point lowest against
+    // the chunk's mean fall (any point is a valid anchor), and the chunk's
+    // first and last points: nearly all the others lie above the chords between
+    // consecutive anchors.  The rest go to the wave's list, filtered as it
+    // fills and at the end.
+    const int bmin = st.b_min[bl];
+    const int c_lo = max(k0 * kBlk, bmin), c_hi = min((k0 + NB) * kBlk, n) - 1;
+    const bool over0 = __ballot(bad) != 0ull;
+    const int64_t ch_i = u * nchunk_max + (k0 / NB);
+    if (c_lo > c_hi || over0) {
+      if (lane == 0) hull_cnt[ch_i] = over0 ? -1 : 0;
+      return;
+    }
+    const float f_lo = cval(ch[c_lo]), f_hi = cval(ch[c_hi]);
+    const float fall = c_hi > c_lo ? (f_lo - f_hi) / (float)(c_hi - c_lo) : 0.f;
+    int tb[NB];    // each block's anchor (-1: no point of the block is in range)
+    float tc[NB];
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      const int i0 = (k0 + j) * kBlk + lane * 4;
+      float best = INFINITY, bc = 0.f;
+      int be = 0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const bool in = i0 + e >= c_lo && i0 + e <= c_hi;
+        const float v = in ? fmaf(fall, (float)(i0 + e - c_lo), c[j][e]) : INFINITY;
+        if (v < best) {
+          best = v;
+          bc = c[j][e];
+          be = e;
+        }
+      }
+      const float mn = wave_reduce_dpp(best, [](float x, float y) { return fminf(x, y); });
+      const uint64_t at = __ballot(best == mn && best < INFINITY);
+      tb[j] = -1;
+      tc[j] = 0.f;
+      if (at) {
+        const int src = (int)__builtin_ctzll(at);
+        tb[j] = (k0 + j) * kBlk + src * 4 + __builtin_amdgcn_readlane(be, src);
+        tc[j] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(bc), src));
+      }
+    }
+    uint2* list = hlist[wave];
+    int m = 0;
+    bool over = false;
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      if (tb[j] < 0) continue;
+      const int i0 = (k0 + j) * kBlk + lane * 4;
+      const bool hp = j > 0 && tb[j > 0 ? j - 1 : 0] >= 0;
+      const bool hn = j + 1 < NB && tb[j + 1 < NB ? j + 1 : j] >= 0;
+      const int pb = hp ? tb[j > 0 ? j - 1 : 0] : c_lo;
+      const float pc = hp ? tc[j > 0 ? j - 1 : 0] : f_lo;
+      const int nb = hn ? tb[j + 1 < NB ? j + 1 : j] : c_hi;
+      const float nc = hn ? tc[j + 1 < NB ? j + 1 : j] : f_hi;
+      // the chord on the lane's side of the anchor; with the anchor among its
+      // points, or none on that side, the lane keeps them all (hull_above's
+      // bound, doubled)
+      const bool left = i0 + 3 < tb[j], right = i0 > tb[j];
+      const int ba = left ? pb : tb[j], bd = left ? tb[j] : nb;
+      const double xa = (double)(left ? pc : tc[j]), xd = (double)(left ? tc[j] : nc);
+      const double slope = (xd - xa) / (double)(bd - ba);
+      const double t0 = 8e-15 * (fabs(xa) + fabs(xd) + fmax(-slope, 0.0) * (double)bd);
+      const double y0 = fma(slope, (double)(i0 - ba), xa);
+      bool keep[4];
+      uint64_t bal[4];
+      int below = 0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int i = i0 + e;
+        const double x = (double)c[j][e];
+        const double rise = x - fma(slope, (double)e, y0);
+        const bool drop = (left || right) && i > c_lo && i < c_hi && rise > fma(8e-15, fabs(x), t0);
+        keep[e] = i >= c_lo && i <= c_hi && !drop;
+        bal[e] = __ballot(keep[e]);
+        below += (int)count_below64(bal[e]);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (keep[e]) list[m + below++] = make_uint2((uint32_t)(i0 + e), __float_as_uint(c[j][e]));
+#pragma unroll
+      for (int e = 0; e < 4; ++e) m += (int)__popcll(bal[e]);
+      __asm__ volatile("" ::: "memory");
+      if (m > kChunkList - kBlk) m = hull_filter(list, m, 6, lane);
+      if (m > kChunkList - kBlk) {  // no room for another block: left to the full search
+        over = true;
+        m = 0;
+      }
+    }
+    m = hull_filter(list, m, 6, lane);
+    over = over || m > kChunkCap;
+    if (lane == 0) hull_cnt[ch_i] = over ? -1 : m;
+    if (!over)
+      for (int i = lane; i < m; i += 64) hull_pts[ch_i * kChunkCap + i] = list[i];
+  }
+}
+
+// A unit's chunk lists joined and filtered again, and its largest curve value.
+// Count -1: a chunk or the unit has too many points.
+constexpr int kMergeThreads = 256;
+__global__ __launch_bounds__(kMergeThreads) void hull_merge_kernel(
+    Geo g, SeqTab st, int32_t nblk_max, int32_t nb, int32_t nchunk_max,
+    const float* __restrict__ cmaxb, const uint2* __restrict__ hull_pts, const int32_t* __restrict__ hull_cnt,
+    uint2* __restrict__ unit_pts, int32_t* __restrict__ unit_cnt, float* __restrict__ unit_max) {
+  __shared__ __align__(16) uint2 list[kMergeCap];
+  __shared__ int32_t off[kLdsItems / 2 + 1];  // where each chunk's points go
+  __shared__ float mx_s[kMergeThreads / 64];
+  const int h = blockIdx.x % g.H;
+  const int bl = blockIdx.x / g.H;
+  const int l = blockIdx.y;
+  if (bl >= st.count) return;
+  const int n = st.len[bl];
+  const int64_t u = unit_index(g, l, st.first + bl, h);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int nblk = (n + kBlk - 1) / kBlk;
+  const int nchunk = (nblk + nb - 1) / nb;  // <= kLdsItems / 2
+  float mx = -INFINITY;
+#pragma unroll 4
+  for (int k = tid; k < nblk; k += kMergeThreads) mx = fmaxf(mx, cmaxb[u * nblk_max + k]);
+  mx = wave_max(mx);
+  if (lane == 0) mx_s[wave] = mx;
+  if (wave == 0) {
+    int run = 0;
+    for (int q0 = 0; q0 < nchunk; q0 += 64) {
+      int c = q0 + lane < nchunk ? hull_cnt[u * nchunk_max + q0 + lane] : 0;
+      if (__ballot(c < 0) != 0ull) c = kMergeCap + 1;  // a chunk overflowed: so does the unit
+      int incl = c;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int y = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += y;
+      }
+      if (q0 + lane < nchunk) off[q0 + lane + 1] = run + incl;
+      run += __shfl(incl, 63, 64);
+    }
+    if (lane == 0) off[0] = 0;
+  }
+  __syncthreads();
+  int m = off[nchunk];
+  const bool fits = m <= kMergeCap;
+  if (fits) {
+    // sixteen chunks of a wave in flight (64 of a chunk's points per load)
+    constexpr int Q = 16, W = kMergeThreads / 64;
+    for (int q0 = wave; q0 < nchunk; q0 += Q * W) {
+      uint2 x[Q];
+#pragma unroll
+      for (int j = 0; j < Q; ++j) {
+        const int q = min(q0 + j * W, nchunk - 1);
+        x[j] = hull_pts[(u * nchunk_max + q) * kChunkCap + lane];
+      }
+#pragma unroll
+      for (int j = 0; j < Q; ++j) {
+        const int q = q0 + j * W;
+        if (q < nchunk && lane < off[q + 1] - off[q]) list[off[q] + lane] = x[j];
+      }
+      for (int j = 0; j < Q; ++j) {  // the few chunks of more than 64
+        const int q = q0 + j * W;
+        if (q < nchunk)
+          for (int i = 64 + lane; i < off[q + 1] - off[q]; i += 64)
+            list[off[q] + i] = hull_pts[(u * nchunk_max + q) * kChunkCap + i];
+      }
+    }
+  }
+  __syncthreads();
+  if (wave != 0) return;
+  if (fits) m = hull_filter(list, m, 6, lane);
+  const bool over = !fits || m > kUnitCap;
+  if (!over)
+    for (int i = lane; i < m; i += 64) unit_pts[u * kUnitCap + i] = list[i];
+  if (lane == 0) {
+    unit_cnt[u] = over ? -1 : m;
+    for (int w = 0; w < kMergeThreads / 64; ++w) mx = fmaxf(mx, mx_s[w]);
+    unit_max[u] = mx;
+  }
+}
+
+// The allocation of one (layer, sequence) over its heads' hull points.  Bound
+// by its chain of about 40 + 10 dependent steps, each an LDS round trip and a
+// barrier.
+__global__ __launch_bounds__(kAllocThreads) void allocate_hull_kernel(
+    Geo g, SeqTab st, const float* __restrict__ curves, const double* __restrict__ dmax,
+    int32_t nblk_max, int32_t steps, const uint2* __restrict__ unit_pts,
+    const int32_t* __restrict__ unit_cnt, const float* __restrict__ unit_max,
+    int32_t* __restrict__ budgets, int64_t* __restrict__ stats, int32_t* __restrict__ done) {
+  // hull points; then block running maxima, and blocks of running maxima
+  __shared__ __align__(16) double pool[kHullPool];
+  __shared__ int16_t slot_of[kLdsItems];  // block -> loaded block (Stage B), by h nblk + k
+  __shared__ int32_t cnt_s[64], off_s[65];
+  __shared__ int32_t bh_s[64];
+  __shared__ double steep_s[64], size_s[64];
+  __shared__ int32_t s_s[64], ks_s[64], ke_s[64];  // start, its block, end of the head's blocks
+  __shared__ int32_t il[2][kHullSlots], ir[2][kHullSlots];  // candidate intervals per list
+  __shared__ int32_t pcount[2][kAllocThreads / 2];          // counts of the pivots
+  __shared__ uint64_t best_s[2], fail_s[2];
+  __shared__ int32_t open_s[2];
+  __shared__ int32_t nslot, sh_s[kHullSlots], sk_s[kHullSlots], after_s[kHullSlots];
+  __shared__ int32_t lt_s[64], le_s[64];
+  const int bl = blockIdx.x, l = blockIdx.y;
+  const int b = st.first + bl;
+  const int n = st.len[bl];
+  const int64_t tok0 = st.start[bl];
+  const int64_t B_real = st.b_real[bl];
+  const int bmin = st.b_min[bl];
+  const int H = g.H;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int nblk = (n + kBlk - 1) / kBlk;
+  const int64_t u0 = unit_index(g, l, b, 0);
+  const uint64_t t_start = wall_clock64();
+  int32_t* flag = done + (int64_t)l * g.B + b;
+
+  if (tid < H) cnt_s[tid] = unit_cnt[u0 + tid];
+  __syncthreads();
+  int total = 0;
+  bool ok = H * nblk <= kLdsItems;
+  float cmf = 0.f;
+  for (int h = 0; h < H; ++h) {
+    if (tid == 0) off_s[h] = total;
+    if (cnt_s[h] < 0) ok = false;
+    total += max(cnt_s[h], 0);
+    cmf = fmaxf(cmf, unit_max[u0 + h]);
+  }
+  ok = ok && total <= kHullPool;
+  if (!ok) {  // (the same for every thread)
+    if (tid == 0) *flag = 0;
+    return;
+  }
+  uint2* pts = reinterpret_cast<uint2*>(pool);
+  __syncthreads();
+  for (int h = wave; h < H; h += kAllocWaves) {
+    const int m = cnt_s[h];
+#pragma unroll 4
+    for (int i = lane; i < m; i += 64) pts[off_s[h] + i] = unit_pts[(u0 + h) * kUnitCap + i];
+  }
+  __syncthreads();
+
+  // Per head, the steepest chord from its first point (b_min) and the largest
+  // size of a value.
+  for (int h = wave; h < H; h += kAllocWaves) {
+    const uint2* p = pts + off_s[h];
+    const int m = cnt_s[h];
+    const double x0 = (double)__uint_as_float(p[0].y), b0 = (double)(int)p[0].x;
+    double steep = -INFINITY, size = fabs(x0);
+    for (int i = 1 + lane; i < m; i += 64) {
+      const double x = (double)__uint_as_float(p[i].y);
+      steep = fmax(steep, (x0 - x) / ((double)(int)p[i].x - b0));
+      size = fmax(size, fabs(x));
+    }
+    steep = -wave_min_f64(-steep);
+    size = -wave_min_f64(-size);
+    if (lane == 0) {
+      steep_s[h] = steep;
+      size_s[h] = size;
+    }
+  }
+  __syncthreads();
+  // The bisection, by one wave: no step has a barrier.  Each head has 64 / G
+  // lanes, which share out the points between its argmins at hi and at lo.
+  if (wave == 0) {
+    int G = 1, lph = 64;
+    while (G < H) {
+      G *= 2;
+      lph /= 2;
+    }
+    const int h = lane / lph, sub = lane - h * lph;
+    const bool act = h < H;
+    const uint2* p = pts + off_s[act ? h : 0];
+    const int m = act ? cnt_s[h] : 0;
+    double steep = -INFINITY, size = 0.0;
+    for (int x = 0; x < H; ++x) {
+      steep = fmax(steep, steep_s[x]);
+      size = fmax(size, size_s[x]);
+    }
+    // argmin over the points [ia, ib] of the lane's head: its b, and its index
+    auto argmin = [&](double lam, int ia, int ib, int& idx) -> int {
+      double f = INFINITY;
+      int bb = 0x7fffffff, at = ia;
+#pragma unroll 4
+      for (int i = ia + sub; i <= ib; i += lph) {
+        const uint2 x = p[i];
+        const double v = fma(lam, (double)(int)x.x, (double)__uint_as_float(x.y));
+        if (v < f) {
+          f = v;
+          bb = (int)x.x;
+          at = i;
+        }
+      }
+      float c = __int_as_float(at);
+      if (lph >= 2) lex_dpp<0xB1>(f, bb, c);
+      if (lph >= 4) lex_dpp<0x4E>(f, bb, c);
+      if (lph >= 8) lex_dpp<0x141>(f, bb, c);
+      if (lph >= 16) lex_dpp<0x140>(f, bb, c);
+      if (lph >= 32) lex_swap<16>(f, bb, c);
+      if (lph >= 64) lex_swap<32>(f, bb, c);
+      idx = __float_as_int(c);
+      return bb;
+    };
+    double lo = 0.0, hi = 2.0 * (double)cmf + 1.0;
+    int i_lo = m - 1, i_hi = 0;  // the argmins lie between these points
+    bool have = false;
+    int bh = bmin;
+    int t = 0;
+    // At twice the steepest chord every f(p) exceeds f(b_min) by lambda / 2 per
+    // rank at least, far more than rounding: every head's argmin is b_min, and
+    // H b_min <= B_real lowers hi.
+    const double far = fmax(2.0 * steep, 1e-12 * size);
+    for (; t < steps; ++t) {
+      const double lam = (lo + hi) / 2.0;
+      if (!(lam > far)) break;
+      hi = lam;
+      have = true;
+    }
+    for (; t < steps; ++t) {
+      const double lam = (lo + hi) / 2.0;
+      int idx;
+      const int bb = argmin(lam, i_hi, i_lo, idx);
+      // (sums of int32 argmins: H <= 64 heads of n < 2^31, two halves)
+      const int mine = act && sub == 0 ? bb : 0;
+      const int64_t sum = ((int64_t)wave_sum_i32(mine >> 16) << 16) + wave_sum_i32(mine & 0xffff);
+      if (sum > B_real)
+        lo = lam;
+      else {
+        hi = lam;
+        have = true;
+        bh = bb;
+      }
+      // A larger lambda has its argmin at the same b or below.  For two
+      // multipliers a distance w apart and points a rank apart, the exact
+      // difference of the f's grows by w at least, so the computed argmins keep
+      // that order while w is well above the f's roundings, 2^-53 of their size.
+      const double w = (hi - lo) / 2.0;
+      if (w > 1e-14 * (hi * (double)n + size)) {
+        if (sum > B_real)
+          i_lo = idx;
+        else
+          i_hi = idx;
+      } else {
+        i_lo = m - 1;
+        i_hi = 0;
+      }
+    }
+    if (!have) {
+      int idx;
+      bh = argmin(hi, 0, m - 1, idx);
+    }
+    if (act && sub == 0) bh_s[h] = bh;
+  }
+  __syncthreads();
+  const int32_t bh = tid < H ? bh_s[tid] : 0;
+  const uint64_t t_bisect = wall_clock64();
+  const int kmax = (n - 2) / kBlk;  // last block holding an increment i <= n-2
+  if (tid < H) {
+    s_s[tid] = bh;
+    ks_s[tid] = bh / kBlk;
+    ke_s[tid] = bh > n - 2 ? bh / kBlk : kmax + 1;
+  }
+  __syncthreads();
+  int64_t sum0 = 0;
+  for (int h = 0; h < H; ++h) sum0 += s_s[h];
+  const int64_t R = B_real - sum0;
+  if (R < 0) {
+    if (tid == 0) *flag = 0;
+    return;
+  }
+  if (R > 0) {
+    // Stage A.  Running maxima of the marginals at the ends of the blocks, as
+    // in the search of allocate_kernel.
+    double* pbm = pool;
+#pragma unroll 4
+    for (int i = tid; i < H * nblk; i += kAllocThreads) {
+      const int h = i / nblk, k = i - h * nblk;
+      pbm[i] = dmax[(u0 + h) * nblk_max + k];
+    }
+    __syncthreads();
+    for (int h = wave; h < H; h += kAllocWaves) {
+      const float* ch = curves + lht_base(g, l, h, tok0);
+      const int s = s_s[h], ks = ks_s[h], ke = ke_s[h];
+      double dm = -INFINITY;
+      if (ke > ks) {
+        const int e1 = min(ks * kBlk + kBlk - 1, n - 2);
+        for (int i = s + lane; i <= e1; i += 64)
+          dm = fmax(dm, (double)cval(ch[i + 1]) - (double)cval(ch[i]));
+      }
+#pragma unroll
+      for (int m = 32; m >= 1; m >>= 1) dm = fmax(dm, __shfl_xor(dm, m, 64));
+      double* ph = pbm + h * nblk;
+      double carry = -INFINITY;
+      for (int k0 = 0; k0 < nblk; k0 += 64) {
+        const int k = k0 + lane;
+        double x = -INFINITY;
+        if (k >= ks && k < ke) x = k == ks ? dm : ph[k];
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+          const double y = __shfl_up(x, o, 64);
+          if (lane >= o) x = fmax(x, y);
+        }
+        x = fmax(x, carry);
+        if (k < nblk) ph[k] = x;
+        carry = __shfl(x, 63, 64);
+      }
+    }
+    // increments of head h in its blocks below k
+    auto below = [&](int h, int k) -> int {
+      return k <= ks_s[h] ? 0 : min(k * kBlk, n - 1) - s_s[h];
+    };
+    // first block of head h in [a, e) whose running maximum is above v, and
+    // not below v
+    auto first_above = [&](int h, int a, int e, double v) {
+      const double* ph = pbm + h * nblk;
+      while (a < e) {
+        const int mid = (a + e) >> 1;
+        if (ph[mid] > v) e = mid;
+        else a = mid + 1;
+      }
+      return a;
+    };
+    auto first_not_below = [&](int h, int a, int e, double v) {
+      const double* ph = pbm + h * nblk;
+      while (a < e) {
+        const int mid = (a + e) >> 1;
+        if (ph[mid] >= v) e = mid;
+        else a = mid + 1;
+      }
+      return a;
+    };
+    // The smallest block maximum v such that the increments certainly keyed at
+    // or below it (whole blocks, q = 0) or possibly so (the crossing blocks
+    // too, q = 1) reach R: the R-th key T lies in (anything below the second,
+    // the first].  Pivots at even steps of the candidates, a thread per (pivot,
+    // head), until every candidate has been tried or the rest are equal.
+    int G = 1;
+    while (G < H) G *= 2;
+    const int NP = kAllocThreads / 2 / G;  // pivots of each question
+    if (tid < 2 * H) {
+      const int q = tid / H, h = tid - q * H;
+      il[q][h] = ks_s[h];
+      ir[q][h] = ke_s[h];
+    }
+    if (tid < 2) {
+      best_s[tid] = ~0ull;
+      fail_s[tid] = 0ull;
+      open_s[tid] = 1;
+    }
+    __syncthreads();
+    const int q = tid >> 9, pv = (tid & 511) / G, hq = (tid & 511) % G;
+    int rounds = 0;
+    while (open_s[0] | open_s[1]) {
+      if (++rounds > 64) {  // (not reached: every round tries a pivot)
+        if (tid == 0) *flag = 0;
+        return;
+      }
+      const bool open = open_s[q] != 0;
+      int cnt = 0;
+      for (int h = 0; h < H; ++h) cnt += ir[q][h] - il[q][h];
+      const int stride = (cnt + NP - 1) / NP;
+      (&pcount[0][0])[tid] = 0;
+      __syncthreads();
+      int idx = pv * stride;
+      const bool live = open && idx < cnt;
+      double v = 0.0;
+      if (live) {
+        int h = 0;
+        while (idx >= ir[q][h] - il[q][h]) {
+          idx -= ir[q][h] - il[q][h];
+          ++h;
+        }
+        v = pbm[h * nblk + il[q][h] + idx];
+        if (hq < H) {
+          const int k = first_above(hq, ks_s[hq], ke_s[hq], v);
+          atomicAdd(&pcount[q][pv], below(hq, q == 0 ? k : min(k + 1, ke_s[hq])));
+        }
+      }
+      __syncthreads();
+      if (live && hq == 0) {
+        if ((int64_t)(uint32_t)pcount[q][pv] >= R)
+          atomicMin((unsigned long long*)&best_s[q], (unsigned long long)dkey(v));
+        else
+          atomicMax((unsigned long long*)&fail_s[q], (unsigned long long)dkey(v));
+      }
+      __syncthreads();
+      // what is left: above every failure, up to the best
+      if (open && (tid & 511) < H) {
+        const int h = tid & 511;
+        int a = il[q][h], e = ir[q][h];
+        if (fail_s[q] != 0ull) a = first_above(h, a, e, dval(fail_s[q]));
+        if (best_s[q] != ~0ull) e = first_above(h, a, e, dval(best_s[q]));
+        il[q][h] = a;
+        ir[q][h] = e;
+      }
+      __syncthreads();
+      if ((tid & 511) == 0 && open) {
+        bool more = false;
+        if (stride > 1)
+          for (int h = 0; h < H; ++h)
+            if (il[q][h] < ir[q][h] && dkey(pbm[h * nblk + il[q][h]]) < best_s[q]) more = true;
+        open_s[q] = more ? 1 : 0;
+      }
+      __syncthreads();
+    }
+    const double p_hi = dval(best_s[0]), p_lo = dval(best_s[1]);
+    // Stage B.  The blocks that can hold T: those in which the running maximum
+    // rises, from the first that reaches p_lo to the one that passes p_hi.
+    // (Blocks in which it stands still hold the value it came in with.)
+    if (tid < H) {
+      const int a = first_not_below(tid, ks_s[tid], ke_s[tid], p_lo);
+      il[0][tid] = a;
+      ir[0][tid] = min(first_above(tid, a, ke_s[tid], p_hi) + 1, ke_s[tid]);
+      lt_s[tid] = below(tid, a);  // all of them keyed below T
+    }
+    if (tid == 0) nslot = 0;
+    __syncthreads();
+    for (int i = tid; i < H * nblk; i += kAllocThreads) {
+      const int h = i / nblk, k = i - h * nblk;
+      int sl = -1;
+      if (k >= il[0][h] && k < ir[0][h] && (k == ks_s[h] || pbm[i] > pbm[i - 1])) {
+        sl = atomicAdd(&nslot, 1);
+        if (sl < kHullSlots) {
+          sh_s[sl] = h;
+          sk_s[sl] = k;
+        }
+      }
+      slot_of[i] = (int16_t)min(sl, kHullSlots);
+    }
+    __syncthreads();
+    const int ns = nslot;
+    if (ns < 1 || ns > kHullSlots || H * nblk + ns * kBlk > kHullPool) {
+      if (tid == 0) *flag = 0;
+      return;
+    }
+    double* blk = pool + H * nblk;  // running maxima of the loaded blocks
+    for (int x = wave; x < ns; x += kAllocWaves) {
+      const int h = sh_s[x], k = sk_s[x];
+      const float* ch = curves + lht_base(g, l, h, tok0);
+      float c[5];
+#pragma unroll
+      for (int e = 0; e < 5; ++e) c[e] = cval(ch[min(k * kBlk + lane * 4 + e, n - 1)]);
+      double r[4], run = k > ks_s[h] ? pbm[h * nblk + k - 1] : -INFINITY;
+      double mx = -INFINITY;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int i = k * kBlk + lane * 4 + e;
+        const double d = i < s_s[h] ? -INFINITY
+                         : i > n - 2 ? INFINITY  // past the last increment: never counted
+                                     : (double)c[e + 1] - (double)c[e];
+        mx = fmax(mx, d);
+        r[e] = mx;
+      }
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const double y = __shfl_up(mx, o, 64);
+        if (lane >= o) mx = fmax(mx, y);
+      }
+      const double before = __shfl_up(mx, 1, 64);
+      if (lane > 0) run = fmax(run, before);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) blk[x * kBlk + lane * 4 + e] = fmax(run, r[e]);
+      // increments of the still blocks after this one, up to the next loaded
+      // one or the end of the range
+      int k2 = k + 1;
+      while (k2 < ir[0][h]) {
+        const uint64_t stop = __ballot(k2 + lane >= ir[0][h] ||
+                                       slot_of[min(h * nblk + k2 + lane, H * nblk - 1)] >= 0);
+        if (stop) {
+          k2 += (int)__builtin_ctzll(stop);
+          break;
+        }
+        k2 += 64;
+      }
+      if (lane == 0) after_s[x] = below(h, k2) - below(h, k + 1);
+    }
+    __syncthreads();
+    // Entries of loaded block x at or below v (strict: below v), without those
+    // before the head's start, and with the still blocks that follow.
+    auto entries = [&](int x, double v, bool strict) -> int {
+      const double* p = blk + x * kBlk;
+      int a = 0, e = kBlk;
+      while (a < e) {
+        const int mid = (a + e) >> 1;
+        if (strict ? p[mid] >= v : p[mid] > v) e = mid;
+        else a = mid + 1;
+      }
+      const int h = sh_s[x], k = sk_s[x];
+      const int skip = k == ks_s[h] ? s_s[h] - k * kBlk : 0;
+      const int real = min(kBlk, n - 1 - k * kBlk);  // increments up to n-2
+      return max(min(a, real) - skip, 0) + (a >= real ? after_s[x] : 0);
+    };
+    // Stage C.  T: the smallest entry such that those at or below it reach R.
+    int64_t base = 0;
+    for (int h = 0; h < H; ++h) base += lt_s[h];
+    int GS = 1;
+    while (GS < ns) GS *= 2;
+    const int NS = kAllocThreads / GS;
+    int32_t* pc = &pcount[0][0];
+    if (tid < ns) {
+      const int h = sh_s[tid], k = sk_s[tid];
+      il[0][tid] = k == ks_s[h] ? s_s[h] - k * kBlk : 0;
+      ir[0][tid] = min(kBlk, n - 1 - k * kBlk);
+    }
+    if (tid == 0) {
+      best_s[0] = ~0ull;
+      fail_s[0] = 0ull;
+      open_s[0] = 1;
+    }
+    __syncthreads();
+    const int sv = tid / GS, sx = tid % GS;
+    rounds = 0;
+    while (open_s[0]) {
+      if (++rounds > 64) {
+        if (tid == 0) *flag = 0;
+        return;
+      }
+      int cnt = 0;
+      for (int x = 0; x < ns; ++x) cnt += ir[0][x] - il[0][x];
+      const int stride = (cnt + NS - 1) / NS;
+      pc[tid] = 0;
+      __syncthreads();
+      int idx = sv * stride;
+      const bool live = idx < cnt;
+      double v = 0.0;
+      if (live) {
+        int x = 0;
+        while (idx >= ir[0][x] - il[0][x]) {
+          idx -= ir[0][x] - il[0][x];
+          ++x;
+        }
+        v = blk[x * kBlk + il[0][x] + idx];
+        if (sx < ns) atomicAdd(&pc[sv], entries(sx, v, false));
+      }
+      __syncthreads();
+      if (live && sx == 0) {
+        if (base + pc[sv] >= R)
+          atomicMin((unsigned long long*)&best_s[0], (unsigned long long)dkey(v));
+        else
+          atomicMax((unsigned long long*)&fail_s[0], (unsigned long long)dkey(v));
+      }
+      __syncthreads();
+      if (tid < ns) {
+        const double* p = blk + tid * kBlk;
+        auto above = [&](int a, int e, uint64_t key) {
+          while (a < e) {
+            const int mid = (a + e) >> 1;
+            if (dkey(p[mid]) > key) e = mid;
+            else a = mid + 1;
+          }
+          return a;
+        };
+        int a = il[0][tid], e = ir[0][tid];
+        if (fail_s[0] != 0ull) a = above(a, e, fail_s[0]);
+        if (best_s[0] != ~0ull) e = above(a, e, best_s[0]);
+        il[0][tid] = a;
+        ir[0][tid] = e;
+      }
+      __syncthreads();
+      if (tid == 0) {
+        bool more = false;
+        if (stride > 1)
+          for (int x = 0; x < ns; ++x)
+            if (il[0][x] < ir[0][x] && dkey(blk[x * kBlk + il[0][x]]) < best_s[0]) more = true;
+        open_s[0] = more ? 1 : 0;
+      }
+      __syncthreads();
+    }
+    // Budgets: everything keyed below T, then the increments keyed T, by head.
+    const double T = dval(best_s[0]);
+    if (tid < H) le_s[tid] = lt_s[tid];
+    __syncthreads();
+    if (tid < ns) {
+      atomicAdd(&lt_s[sh_s[tid]], entries(tid, T, true));
+      atomicAdd(&le_s[sh_s[tid]], entries(tid, T, false));
+    }
+    __syncthreads();
+    if (tid == 0) {
+      int64_t rem = R;
+      for (int h = 0; h < H; ++h) rem -= lt_s[h];
+      for (int h = 0; h < H; ++h) {
+        const int64_t eq = le_s[h] - lt_s[h];
+        const int64_t take = rem < eq ? rem : eq;
+        rem -= take;
+        s_s[h] += (int32_t)(lt_s[h] + take);
+      }
+    }
+    __syncthreads();
+  }
+  if (tid < H) budgets[u0 + tid] = s_s[tid];
+  if (tid == 0) {
+    *flag = 1;
+    if (stats) {
+      stats[((int64_t)l * g.B + b) * 3 + 0] = R;
+      stats[((int64_t)l * g.B + b) * 3 + 1] = (int64_t)(t_bisect - t_start);
+      stats[((int64_t)l * g.B + b) * 3 + 2] = (int64_t)(wall_clock64() - t_bisect);
+    }
+  }
 }
 
 __global__ __launch_bounds__(kAllocThreads) void allocate_kernel(
     Geo g, SeqTab st, const float* __restrict__ curves, const float* __restrict__ cmin,
     const float* __restrict__ cmaxb, const int32_t* __restrict__ cpos,
     const double* __restrict__ dmax, int32_t nblk_max, int32_t steps,
-    int32_t* __restrict__ budgets, int64_t* __restrict__ stats, int32_t K, int32_t* sync) {
+    int32_t* __restrict__ budgets, int64_t* __restrict__ stats, int32_t K, int32_t* sync,
+    const int32_t* __restrict__ done) {
   // 64 KB of LDS: the half-block minima during the bisection, the
   // block-level running maxima of the marginals during the repair.
   __shared__ __align__(16) unsigned char pool[kLdsItems * 8];
@@ -352,6 +1172,7 @@ __global__ __launch_bounds__(kAllocThreads) void allocate_kernel(
   }
   if (bl >= st.count || l >= g.L) return;
   const int b = st.first + bl;
+  if (done && done[(int64_t)l * g.B + b]) return;  // a whole group returns together
   const int n = st.len[bl];
   const int64_t tok0 = st.start[bl];
   const int64_t B_real = st.b_real[bl];
@@ -1142,20 +1963,44 @@ certkv_status run_allocate(const AllocArgs& a, const SeqTab& st, hipStream_t s) 
     const int cus = device_cus(dev);
     K = 7 * groups <= cus ? 7 : 3 * groups <= cus ? 3 : 1;
   }
-  const int per_unit = (a.nblk_max + 4 * kBsBlocks - 1) / (4 * kBsBlocks);
-  CERTKV_LAUNCH("curve_blockstats", curve_blockstats_kernel, dim3(a.g.H * st.count * per_unit, a.g.L),
-                dim3(256), 0, s, a.g, st, a.nblk_max, a.curves, a.cmin, a.cmaxb, a.cpos, a.dmax,
-                K > 1 ? a.sync : (int32_t*)nullptr, (int32_t)kSyncArg);
+  int32_t* sync = K > 1 ? a.sync : nullptr;
+  // Tail masses are convex without noise, all of them hull points: no filter.
+  const bool hull = a.hull_pts && a.g.stat != 2 && a.g.H * a.nblk_max <= kLdsItems;
+  const int nb = hull ? a.chunk_blocks : 8;
+  const int nchunk = (a.nblk_max + nb - 1) / nb;
+  const dim3 bgrid(a.g.H * st.count * ((nchunk + 3) / 4), a.g.L);
+#define CERTKV_BLOCKSTATS(HULL, NB)                                                                \
+  CERTKV_LAUNCH("curve_blockstats", (curve_blockstats_kernel<HULL, NB>), bgrid, dim3(256), 0, s,   \
+                a.g, st, a.nblk_max, a.curves, a.cmin, a.cmaxb, a.cpos, a.dmax, sync,              \
+                (int32_t)kSyncArg, nchunk, a.hull_pts, a.hull_cnt)
+  if (hull) {
+    if (nb == 8)
+      CERTKV_BLOCKSTATS(true, 8);
+    else
+      CERTKV_BLOCKSTATS(true, 2);
+    CERTKV_LAUNCH("hull_merge", hull_merge_kernel, dim3(a.g.H * st.count, a.g.L),
+                  dim3(kMergeThreads), 0, s, a.g, st, a.nblk_max, nb, nchunk,
+                  (const float*)a.cmaxb, (const uint2*)a.hull_pts, (const int32_t*)a.hull_cnt,
+                  a.unit_pts, a.unit_cnt, a.unit_max);
+    CERTKV_LAUNCH("allocate_hull", allocate_hull_kernel, dim3(st.count, a.g.L), dim3(kAllocThreads),
+                  0, s, a.g, st, a.curves, (const double*)a.dmax, a.nblk_max, a.steps,
+                  (const uint2*)a.unit_pts, (const int32_t*)a.unit_cnt, (const float*)a.unit_max,
+                  a.budgets, a.repairs, a.done);
+  } else {
+    CERTKV_BLOCKSTATS(false, 8);
+  }
+#undef CERTKV_BLOCKSTATS
+  const int32_t* done = hull ? a.done : nullptr;
   if (K > 1) {
     CERTKV_LAUNCH("allocate", allocate_kernel, dim3((unsigned)(K * groups)), dim3(kAllocThreads), 0,
                   s, a.g, st, a.curves, (const float*)a.cmin, (const float*)a.cmaxb,
                   (const int32_t*)a.cpos, (const double*)a.dmax, a.nblk_max, a.steps, a.budgets,
-                  a.repairs, K, a.sync);
+                  a.repairs, K, a.sync, done);
   } else {
     CERTKV_LAUNCH("allocate", allocate_kernel, dim3(st.count, a.g.L), dim3(kAllocThreads), 0, s,
                   a.g, st, a.curves, (const float*)a.cmin, (const float*)a.cmaxb,
                   (const int32_t*)a.cpos, (const double*)a.dmax, a.nblk_max, a.steps, a.budgets,
-                  a.repairs, 1, (int32_t*)nullptr);
+                  a.repairs, 1, (int32_t*)nullptr, done);
   }
   return CERTKV_OK;
 }

@@ -59,7 +59,7 @@ struct Plan {
   int kpb2;          // keys per scoring block, pass 2
   int nkb2_max;      // pass-2 scoring blocks per unit
   int nblk_max;      // 256-rank allocation blocks per unit
-  int nsub_max;      // 16-rank allocation sub-blocks per unit
+  int chunk_blocks;  // allocation blocks per chunk of the hull filter
   int bm_words;      // 64-bit bitmap words per unit
   int nsplit;        // tail gather workgroups per unit
   int seg_chunks;    // curves: chunks per segment
@@ -186,7 +186,10 @@ static certkv_status make_plan(const certkv_problem* p, Plan* pl) {
   P.kpb2 = kpb2;
   P.nkb2_max = (max_len + kpb2 - 1) / kpb2;
   P.nblk_max = (max_len + 255) / 256;
-  P.nsub_max = (max_len + 15) / 16;
+  // Chunks of 8 blocks share the filter's fixed work; with less than eight waves
+  // of them per SIMD (1024 SIMDs) chunks of 2 are done sooner (8 units of 32768
+  // ranks 14 us with chunks of 2 and 34 with 8, 64 ragged units 30 and 44).
+  P.chunk_blocks = P.U * ((P.nblk_max + 7) / 8) >= 8192 ? 8 : 2;
   P.bm_words = (max_len + 63) / 64;
   // tail gather: one workgroup per 2048 positions of the longest sequence
   // (about 200 kept rows each at a tenth kept), at most 128 per unit
@@ -294,6 +297,9 @@ struct Bufs {
   double* segtot = nullptr;
   int64_t* repairs = nullptr;
   int32_t* alloc_sync = nullptr;
+  uint2 *hull_pts = nullptr, *unit_pts = nullptr;
+  int32_t *hull_cnt = nullptr, *unit_cnt = nullptr, *alloc_done = nullptr;
+  float* unit_max = nullptr;
   // select / tail
   uint64_t* bitmap = nullptr;
   int64_t* kept_offsets = nullptr;
@@ -354,6 +360,13 @@ static size_t layout(const Plan& P, uint32_t need, void* ws, Bufs* b) {
     b->dmax = w.take<double>((size_t)P.U * P.nblk_max);
     b->repairs = w.take<int64_t>((size_t)P.g.L * P.g.B * 3);
     b->alloc_sync = w.take<int32_t>(alloc_sync_words());
+    const size_t chunks = (size_t)P.U * ((P.nblk_max + P.chunk_blocks - 1) / P.chunk_blocks);
+    b->hull_pts = w.take<uint2>(chunks * alloc_chunk_points());
+    b->hull_cnt = w.take<int32_t>(chunks);
+    b->unit_pts = w.take<uint2>((size_t)P.U * alloc_unit_points());
+    b->unit_cnt = w.take<int32_t>((size_t)P.U);
+    b->unit_max = w.take<float>((size_t)P.U);
+    b->alloc_done = w.take<int32_t>((size_t)P.g.L * P.g.B);
   }
   if (need & NEED_BITMAP) {
     b->bitmap = w.take<uint64_t>((size_t)P.U * P.bm_words);
@@ -489,6 +502,13 @@ static certkv_status do_allocate(const Plan& P, const float* curves, const int32
   a.budgets = budgets;
   a.repairs = stats ? stats : w.repairs;
   a.sync = w.alloc_sync;
+  a.chunk_blocks = P.chunk_blocks;
+  a.hull_pts = w.hull_pts;
+  a.hull_cnt = w.hull_cnt;
+  a.unit_pts = w.unit_pts;
+  a.unit_cnt = w.unit_cnt;
+  a.unit_max = w.unit_max;
+  a.done = w.alloc_done;
   (void)minmax;
   for (const SeqTab& t : make_tabs(P, n_keep, alpha)) {
     if (P.alloc == 1)

@@ -87,8 +87,17 @@ struct AllocArgs {
   int32_t* budgets;
   int64_t* repairs;
   int32_t* sync;    // alloc_sync_words() words: cross-workgroup bisection (optional)
+  int32_t chunk_blocks;  // blocks per chunk of the hull filter: 2 or 8
+  uint2* hull_pts;   // [U][chunks][alloc_chunk_points()] hull points of the chunks
+  int32_t* hull_cnt; // [U][chunks]
+  uint2* unit_pts;   // [U][alloc_unit_points()] hull points of the units
+  int32_t* unit_cnt; // [U]
+  float* unit_max;   // [U]
+  int32_t* done;     // [L*B] set where the hull kernel allocated
 };
 size_t alloc_sync_words();
+size_t alloc_chunk_points();
+size_t alloc_unit_points();
 certkv_status run_allocate(const AllocArgs& a, const SeqTab& st, hipStream_t s);
 
 struct SelectArgs {

@@ -177,3 +177,64 @@ def test_sort_sizes(lens, keep_window):
                 ref = oracle.order(s[l, h, t0:t0 + n], keep_window=w if keep_window else 0)
                 assert np.array_equal(perm[l, h, t0:t0 + n], ref), (l, h, n)
                 t0 += n
+
+
+def _curves(kind, H, n, rng):
+    x = np.arange(n, dtype=np.float64)[None]
+    scale = rng.uniform(0.1, 10, (H, 1))
+    if kind == "noisy_line":
+        d = rng.uniform(0.2, 1.8, (H, n))
+        c = np.cumsum(d[:, ::-1], 1)[:, ::-1] / n
+    elif kind == "noisy_power":
+        d = rng.uniform(0.2, 1.8, (H, n)) * (x + 1) ** -rng.uniform(0.3, 1.2, (H, 1))
+        c = np.cumsum(d[:, ::-1], 1)[:, ::-1]
+    elif kind == "walk":
+        c = np.abs(np.cumsum(rng.standard_normal((H, n)), 1))[:, ::-1]
+    elif kind == "quantized":  # ties of values, marginals and keys, long plateaus
+        c = np.round(np.cumsum(rng.uniform(0, 1, (H, n))[:, ::-1], 1)[:, ::-1] / 16)
+        scale = np.ones((H, 1))
+    elif kind == "rising":     # the argmin is b_min, the increments all positive
+        c = np.cumsum(rng.uniform(0, 1, (H, n)), 1)
+    else:                      # "convex": every point on the hull
+        c = 1.0 / (1.0 + x / 40.0) + 0 * scale
+    return np.ascontiguousarray(c * scale, np.float32)
+
+
+@pytest.mark.parametrize("kind", ["noisy_line", "noisy_power", "walk", "quantized", "rising",
+                                  "convex"])
+def test_hull_allocation(kind):
+    # Budgets over the hull points against the oracle's full scans: curves of
+    # one block and several, chunks of 2048 ranks and their edges, one head to
+    # more than a wave each, few and many bisection steps (past the point where
+    # the interval has no double inside), every budget size; curves that the
+    # hull kernel leaves to the full search among them.
+    rng = np.random.default_rng(11)
+    for n in (2, 3, 17, 256, 257, 258, 513, 2048, 2049, 2050, 9000):
+        for H in ((1, 8) if n != 513 else (3, 17, 40)):
+            c = _curves(kind, H, n, rng)
+            spec = ck.ProblemSpec(1, H, 1, 64, 1, [n], torch.bfloat16)
+            t = torch.from_numpy(c).reshape(1, H, n).to(DEV)
+            for n_keep in sorted({2, max(2, n // 10), max(2, n // 2), n}):
+                for steps, alpha in ((40, 0.2), (0, 0.2), (9, 0.0), (200, 0.2)):
+                    got = ck.allocate_curves(spec, t, [n_keep], steps=steps, alpha=alpha)
+                    want, _ = oracle.allocate(c, n_keep, steps=steps, alpha=alpha)
+                    assert np.array_equal(got.cpu().numpy(), want), (n, H, n_keep, steps)
+
+
+@pytest.mark.parametrize("layers", [2, 40, 100])
+def test_hull_allocation_beside_the_full_search(layers):
+    # One launch with (layer, sequence)s of either kind, for each width of the
+    # full search's groups of workgroups.
+    rng = np.random.default_rng(layers)
+    H, lens = 4, [700, 2333]
+    c = np.concatenate([np.stack([_curves("convex" if (li + b) % 3 == 0 else "noisy_power", H, n, rng)
+                                  for li in range(layers)]) for b, n in enumerate(lens)], -1)
+    spec = ck.ProblemSpec(layers, H, 2, 64, 16, lens, torch.bfloat16)
+    n_keep = [71, 240]
+    for steps in (0, 5, 40):
+        got = ck.allocate_curves(spec, torch.from_numpy(c).to(DEV), n_keep, steps=steps)
+        got = got.cpu().numpy().reshape(layers, 2, H)
+        for li in range(layers):
+            for b, (t0, n) in enumerate(zip((0, lens[0]), lens)):
+                want, _ = oracle.allocate(c[li, :, t0:t0 + n], n_keep[b], steps=steps)
+                assert np.array_equal(got[li, b], want), (steps, li, b)
