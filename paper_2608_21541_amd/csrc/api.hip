@@ -807,13 +807,17 @@ static int decode_rows_bound(const Plan& P, int32_t max_rows) {
 // Decode workspace: split partials (output rows, then (max, sum) pairs), the
 // work-item list and its length, each 256-byte aligned.
 struct DecodeWs {
+  int keys_min;
+  int64_t cover;
   int nsplit;
   size_t ml_off, items_off, count_off, total;
 };
 static DecodeWs decode_ws_layout(const Plan& P, int32_t tq, int32_t max_rows) {
   auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
   DecodeWs w;
-  w.nsplit = decode_nsplit(decode_rows_bound(P, max_rows));
+  w.keys_min = decode_keys_min(P.U, P.max_len, tq, P.g.G);
+  w.cover = decode_cover(decode_rows_bound(P, max_rows));
+  w.nsplit = (int)(w.cover / w.keys_min);
   const size_t rows = decode_partial_rows(P.U, w.nsplit, tq, P.g.G);
   w.ml_off = up(rows * (size_t)P.g.D * sizeof(float));
   w.items_off = up(w.ml_off + rows * sizeof(float2));
@@ -857,6 +861,8 @@ static certkv_status decode_impl(const certkv_problem* p, certkv_tensor q_new, i
   a.g = P.g;
   a.U = P.U;
   a.tq = tq;
+  a.keys_min = W.keys_min;
+  a.cover = W.cover;
   a.nsplit = W.nsplit;
   a.q = q_new;
   a.k_packed = k_packed;

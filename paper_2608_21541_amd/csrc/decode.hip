@@ -7,9 +7,10 @@
 // over the unit's packed segment:
 //   z_i = scale <q, k_i>,  out = sum_i softmax(z)_i v_i,  lse = log sum e^z.
 //
-// Split over keys: the work items are (unit, 4096-key chunk) pairs, listed on
-// the device and taken in a fixed stride by a persistent grid of as many
-// workgroups as stay resident.  A workgroup holds the unit's query tiles of
+// Split over keys: the work items are (unit, chunk) pairs, chunks of up to 4096
+// keys (dec_keys), taken in a fixed stride by a persistent grid of as many
+// workgroups as stay resident; a workgroup finds its item among the packed
+// offsets itself (up to kLocalUnits units) or in a list built on the device.  A workgroup holds the unit's query tiles of
 // 32 rows, one wave each; with fewer than four tiles, two or four waves share
 // a tile and split its output dims.  Key and value tiles of 32 rows go from
 // memory straight into LDS (wave-wide 16-byte LDS-DMA loads into a ring of
@@ -31,7 +32,8 @@
 
 namespace certkv {
 
-constexpr int kDecKeys = 4096;  // keys per work item (one split)
+constexpr int kDecKeys = 4096;    // keys per work item (one split) at most
+constexpr int kDecKeysMin = 128;  // and at least
 constexpr int kDecTile = 32;    // keys per tile
 
 typedef __bf16 dec_bf16x8 __attribute__((__vector_size__(8 * sizeof(__bf16))));
@@ -139,23 +141,35 @@ __device__ __forceinline__ uint32_t dec_lds_addr(const void* p) {
 typedef short dec_s16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) dec_s16x4 dec_lds_s16x4;
 
+// Keys per chunk: the same for every unit, a power of two in [keys_min, 4096],
+// from the packed rows alone.  Long chunks amortize the start of an item (its
+// queries, the first tiles' latency) and its partials; with few rows they leave
+// compute units idle, so chunks are halved while there would be fewer than 512
+// (the resident workgroups).  One layer of 8 heads at 32768 tokens, 26216 rows,
+// one query: 100 us in 4096-key chunks, 11 us in 128-key ones; all 32
+// layers at 131072 keep 4096.
+__device__ __forceinline__ int dec_keys(const int64_t* __restrict__ poff, int64_t U, int keys_min) {
+  const int64_t rows = poff[U] - poff[0];
+  int k = keys_min;
+  while (k < kDecKeys && (int64_t)k * 1024 <= rows) k *= 2;
+  return k;
+}
+
 // The work items of a decode: every (unit, chunk) pair whose chunk starts
-// inside the unit's segment (at most nsplit chunks per unit), unit-major.  One
+// inside the unit's segment (at most cover rows of it), unit-major.  One
 // workgroup scans the per-unit chunk counts in rounds of kItemThreads units.
 constexpr int kItemThreads = 1024;
 __global__ __launch_bounds__(kItemThreads) void decode_items_kernel(
-    int64_t U, int32_t nsplit, const int64_t* __restrict__ poff, int2* __restrict__ items,
-    int32_t* __restrict__ count) {
+    int64_t U, int64_t cover, int32_t keys_min, const int64_t* __restrict__ poff,
+    int2* __restrict__ items, int32_t* __restrict__ count) {
   __shared__ int scan[kItemThreads];
   const int t = threadIdx.x;
+  const int keys = dec_keys(poff, U, keys_min);
   int base = 0;  // items of the earlier rounds
   for (int64_t u0 = 0; u0 < U; u0 += kItemThreads) {
     const int64_t u = u0 + t;
     int n = 0;
-    if (u < U) {
-      const int64_t len = poff[u + 1] - poff[u];
-      n = (int)min((int64_t)nsplit, (len + kDecKeys - 1) / kDecKeys);
-    }
+    if (u < U) n = (int)((min(cover, poff[u + 1] - poff[u]) + keys - 1) / keys);
     scan[t] = n;
     __syncthreads();
     for (int d = 1; d < kItemThreads; d <<= 1) {  // inclusive scan
@@ -169,15 +183,38 @@ __global__ __launch_bounds__(kItemThreads) void decode_items_kernel(
     base += scan[kItemThreads - 1];
     __syncthreads();  // scan[] is rewritten by the next round
   }
-  if (t == 0) *count = base;
+  if (t == 0) {
+    count[0] = base;
+    count[1] = keys;
+  }
 }
 
-// Two waves per SIMD: the register cap keeps the accumulators out of AGPRs.
-template <int D, int NQT>
-__global__ __launch_bounds__((64 * DecShape<D, NQT>::NW))
-__attribute__((amdgpu_waves_per_eu(2))) void decode_kernel(
-    Geo g, const int2* __restrict__ items, const int32_t* __restrict__ item_count,
-    int32_t tq, int32_t nsplit, int32_t mp,
+// The same list without a launch of its own: item `item` of the list, found by
+// a wave from the offsets (a unit per lane); x = -1 past its end.  With more
+// units, or many items to a workgroup, the launch costs less than the searches
+// (256 units, three items each: 5 us in all, a launch 3 us).
+constexpr int kLocalUnits = 64;
+__device__ __forceinline__ int2 dec_find_item(const int64_t* __restrict__ poff, int U,
+                                              int64_t cover, int keys, int item, int lane) {
+  const int64_t len = poff[min(lane + 1, U)] - poff[min(lane, U)];
+  const int c = (int)((min(cover, len) + keys - 1) / keys);
+  int incl = c;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int y = __shfl_up(incl, d, 64);
+    if (lane >= d) incl += y;
+  }
+  const uint64_t at = __ballot(item < incl && item >= incl - c);
+  if (at == 0) return make_int2(-1, 0);
+  const int u = (int)__builtin_ctzll(at);
+  return make_int2(u, item - __builtin_amdgcn_readlane(incl - c, u));
+}
+
+// LOCAL: the items are found from the offsets (else read from the list).
+template <int D, int NQT, bool LOCAL>
+__device__ __forceinline__ void decode_body(
+    const Geo& g, int64_t U, int64_t cover, int32_t keys_min, const int2* __restrict__ items,
+    const int32_t* __restrict__ item_count, int32_t tq, int32_t nsplit, int32_t mp,
     const uint16_t* __restrict__ qn, int64_t q_sl, int64_t q_st, int64_t q_sh,
     const uint16_t* __restrict__ kp, const uint16_t* __restrict__ vp,
     const int64_t* __restrict__ poff, float* __restrict__ part_o, float2* __restrict__ part_ml) {
@@ -196,9 +233,16 @@ __attribute__((amdgpu_waves_per_eu(2))) void decode_kernel(
 
   // A persistent grid over the work items (unit, chunk), taken in a fixed
   // stride: consecutive chunks of a long segment go to different workgroups.
-  const int nitems = *item_count;
+  const int keys = LOCAL ? dec_keys(poff, U, keys_min) : item_count[1];
+  const int nitems = LOCAL ? 0x7fffffff : item_count[0];
   for (int item = blockIdx.x; item < nitems; item += gridDim.x) {
-  const int2 it = items[item];
+  int2 it;
+  if constexpr (LOCAL) {
+    it = dec_find_item(poff, (int)U, cover, keys, item, threadIdx.x & 63);
+    if (it.x < 0) break;  // whole workgroup: past the last item
+  } else {
+    it = items[item];
+  }
   const int64_t u = it.x;
   const int split = it.y;
   const int h = (int)(u % g.H);
@@ -207,9 +251,9 @@ __attribute__((amdgpu_waves_per_eu(2))) void decode_kernel(
   const int l = (int)(lb / g.B);
   const int64_t p0 = poff[u];
   const int len = (int)(poff[u + 1] - p0);
-  const int c0 = split * kDecKeys;
+  const int c0 = split * keys;
   if (c0 >= len) continue;  // whole workgroup: this unit has fewer chunks
-  const int c1 = min(len, c0 + kDecKeys);
+  const int c1 = min(len, c0 + keys);
   const int ntiles = (c1 - c0 + kDecTile - 1) / kDecTile;
   const int M = tq * g.G;
   const int lane = threadIdx.x & 63;
@@ -393,6 +437,24 @@ __attribute__((amdgpu_waves_per_eu(2))) void decode_kernel(
   }
 }
 
+// Two waves per SIMD: the register cap keeps the accumulators out of AGPRs.
+#define CERTKV_DECODE_KERNEL(NAME, LOCAL)                                                          \
+  template <int D, int NQT>                                                                        \
+  __global__ __launch_bounds__((64 * DecShape<D, NQT>::NW))                                        \
+  __attribute__((amdgpu_waves_per_eu(2))) void NAME(                                               \
+      Geo g, int64_t U, int64_t cover, int32_t keys_min, const int2* __restrict__ items,           \
+      const int32_t* __restrict__ item_count, int32_t tq, int32_t nsplit, int32_t mp,              \
+      const uint16_t* __restrict__ qn, int64_t q_sl, int64_t q_st, int64_t q_sh,                   \
+      const uint16_t* __restrict__ kp, const uint16_t* __restrict__ vp,                            \
+      const int64_t* __restrict__ poff, float* __restrict__ part_o,                                \
+      float2* __restrict__ part_ml) {                                                              \
+    decode_body<D, NQT, LOCAL>(g, U, cover, keys_min, items, item_count, tq, nsplit, mp, qn, q_sl, \
+                               q_st, q_sh, kp, vp, poff, part_o, part_ml);                         \
+  }
+CERTKV_DECODE_KERNEL(decode_kernel, false)
+CERTKV_DECODE_KERNEL(decode_local_kernel, true)
+#undef CERTKV_DECODE_KERNEL
+
 // Combine the chunk partials of each (unit, row): one workgroup per row, the
 // partial slots dealt round-robin to groups of D/4 threads (four output dims
 // per thread, 16-byte loads).  Each group folds its slots in order with an
@@ -403,7 +465,9 @@ constexpr int kCombThreads = 256;
 // With clustered tail summaries (CL), the m cluster terms n_g e^{lbar_g}
 // (lbar_g = scale <q, kbar_g>) and n_g e^{lbar_g} vbar_g join the kept rows'
 // sums (the ratio estimator of the clustered-summary bound), and the row's
-// runtime certificate is evaluated from the stored summaries: with r_g =
+// runtime certificate is evaluated from the stored summaries, a cluster to a
+// lane (two layers, 16 clusters, 16 rows a head: 20 us with the dot products
+// and the certificate one cluster after the other, 11 us): with r_g =
 // scale |q| R_g and zeta_g = n_g e^{lbar_g} / Zhat,
 //   D_Z / Zhat = sum_g (e^r_g - 1) e^r_g zeta_g,
 //   D_N / Zhat = sum_g e^r_g zeta_g ((e^r_g - 1) |vbar_g| + rho_g),
@@ -412,12 +476,13 @@ constexpr int kCombThreads = 256;
 // bound is infinite).
 template <int D, bool CL>
 __global__ __launch_bounds__(kCombThreads) void decode_combine_kernel(
-    Geo g, int32_t tq, int32_t nsplit, int32_t mp, const int64_t* __restrict__ poff,
-    const float* __restrict__ part_o, const float2* __restrict__ part_ml, float* __restrict__ out,
-    float* __restrict__ lse, DecodeClusters cl, const uint16_t* __restrict__ qn, int64_t q_sl,
+    Geo g, int64_t U, int64_t cover, int32_t keys_min, int32_t tq, int32_t nsplit, int32_t mp,
+    const int64_t* __restrict__ poff, const float* __restrict__ part_o,
+    const float2* __restrict__ part_ml, float* __restrict__ out, float* __restrict__ lse,
+    DecodeClusters cl, const uint16_t* __restrict__ qn, int64_t q_sl,
     int64_t q_st, int64_t q_sh) {
   constexpr int kMaxCl = 64;
-  __shared__ float zc_s[CL ? kMaxCl : 1], vn_s[CL ? kMaxCl : 1];
+  __shared__ float zc_s[CL ? kMaxCl : 1], vn_s[CL ? kMaxCl : 1], wc_s[CL ? kMaxCl : 1];
   __shared__ float qn_s;
   constexpr int C4 = D / 4;                // threads per slot row
   constexpr int S = kCombThreads / C4;     // slot groups
@@ -428,8 +493,9 @@ __global__ __launch_bounds__(kCombThreads) void decode_combine_kernel(
   const int sg = threadIdx.x / C4;
   const int c4 = threadIdx.x % C4;
   const int len = (int)(poff[u + 1] - poff[u]);
-  const int nv = min(nsplit, (len + kDecKeys - 1) / kDecKeys);
-  if (len > nsplit * kDecKeys && row == 0 && threadIdx.x == 0) report_range(g);
+  const int keys = dec_keys(poff, U, keys_min);
+  const int nv = (int)((min(cover, (int64_t)len) + keys - 1) / keys);
+  if (len > cover && row == 0 && threadIdx.x == 0) report_range(g);
   const int64_t base = (int64_t)u * nsplit * mp + row;  // + slot * mp
   float m = -INFINITY, L = 0.f;
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -472,28 +538,44 @@ __global__ __launch_bounds__(kCombThreads) void decode_combine_kernel(
   const int t = row / g.G, gq = row % g.G;
   const int64_t orow = ((int64_t)l * g.B * tq + (int64_t)b * tq + t) * Hq + h * g.G + gq;
   const float c2 = g.scale * kDecLog2e;
-  if (CL && threadIdx.x < cl.m) {
-    // cluster logits in log2 units (with log2 n_g) and value norms
-    const int gi = threadIdx.x;
-    const uint16_t* qr = qn + (int64_t)l * q_sl + (int64_t)(b * tq + t) * q_st +
-                         (int64_t)(h * g.G + gq) * q_sh;
-    const uint16_t* kr = cl.kbar + (u * cl.m + gi) * D;
-    const uint16_t* vr = cl.vbar + (u * cl.m + gi) * D;
-    float dot = 0.f, vv = 0.f, qq = 0.f;
-    for (int e = 0; e < D; ++e) {
-      const float qe = bf16_to_f32(qr[e]);
-      dot = fmaf(qe, bf16_to_f32(kr[e]), dot);
-      const float ve = bf16_to_f32(vr[e]);
-      vv = fmaf(ve, ve, vv);
-      qq = fmaf(qe, qe, qq);
+  if (CL) {
+    // cluster logits in log2 units (with log2 n_g) and value norms: D / 8 lanes
+    // per cluster, 8 dims each
+    constexpr int LC = D / 8;
+    const uint4 qv = reinterpret_cast<const uint4*>(
+        qn + (int64_t)l * q_sl + (int64_t)(b * tq + t) * q_st +
+        (int64_t)(h * g.G + gq) * q_sh)[threadIdx.x % LC];
+    auto at8 = [](const uint4& x, int e) {
+      const uint32_t w = (&x.x)[e >> 1];
+      return e & 1 ? bf16_hi(w) : bf16_lo(w);
+    };
+    for (int g0 = 0; g0 < cl.m; g0 += kCombThreads / LC) {
+      const int gi = min(g0 + (int)threadIdx.x / LC, cl.m - 1);
+      const uint4 kv = reinterpret_cast<const uint4*>(cl.kbar + (u * cl.m + gi) * D)[threadIdx.x % LC];
+      const uint4 vv = reinterpret_cast<const uint4*>(cl.vbar + (u * cl.m + gi) * D)[threadIdx.x % LC];
+      float dot = 0.f, nv2 = 0.f, nq2 = 0.f;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float qe = at8(qv, e), ve = at8(vv, e);
+        dot = fmaf(qe, at8(kv, e), dot);
+        nv2 = fmaf(ve, ve, nv2);
+        nq2 = fmaf(qe, qe, nq2);
+      }
+#pragma unroll
+      for (int o = LC / 2; o > 0; o >>= 1) {
+        dot += __shfl_xor(dot, o, 64);
+        nv2 += __shfl_xor(nv2, o, 64);
+        nq2 += __shfl_xor(nq2, o, 64);
+      }
+      if (threadIdx.x % LC == 0 && g0 + (int)threadIdx.x / LC < cl.m) {
+        const int cnt = cl.count[u * cl.m + gi];
+        zc_s[gi] = cnt > 0 ? dot * c2 + __builtin_amdgcn_logf((float)cnt) : -INFINITY;
+        vn_s[gi] = sqrtf(nv2);
+        if (gi == 0) qn_s = sqrtf(nq2);
+      }
     }
-    const int cnt = cl.count[u * cl.m + gi];
-    zc_s[gi] = cnt > 0 ? dot * c2 + __builtin_amdgcn_logf((float)cnt) : -INFINITY;
-    vn_s[gi] = sqrtf(vv);
-    if (gi == 0) qn_s = sqrtf(qq);
   }
   __syncthreads();
-  if (threadIdx.x >= D) return;
   const int dd = threadIdx.x;
   float mx = -INFINITY;
 #pragma unroll
@@ -505,41 +587,110 @@ __global__ __launch_bounds__(kCombThreads) void decode_combine_kernel(
     if (mk.x == -INFINITY) continue;
     const float w = __builtin_amdgcn_exp2f(mk.x - mx);
     Lt += mk.y * w;
-    at += reinterpret_cast<const float*>(&acc_s[k][0])[dd] * w;
+    if (dd < D) at += reinterpret_cast<const float*>(&acc_s[k][0])[dd] * w;
   }
   if (CL) {
     float mc = mx;
     for (int gi = 0; gi < cl.m; ++gi) mc = fmaxf(mc, zc_s[gi]);
     const float a = mx == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mx - mc);
-    const float Ls = Lt * a;  // the kept rows' share, relative to 2^mc
-    Lt = Ls;
+    Lt *= a;  // the kept rows' share, relative to 2^mc
     at *= a;
-    for (int gi = 0; gi < cl.m; ++gi) {
-      if (zc_s[gi] == -INFINITY) continue;
-      const float w = __builtin_amdgcn_exp2f(zc_s[gi] - mc);
-      Lt += w;
-      at = fmaf(w, bf16_to_f32(cl.vbar[(u * cl.m + gi) * D + dd]), at);
-    }
     mx = mc;
-    if (dd == 0 && cl.bound) {
-      const double rq = (double)g.scale * (double)qn_s;
-      double dz = 0.0, dn = 0.0, vmax = (double)cl.vmax_kept[u];
+    if (dd < cl.m) wc_s[dd] = __builtin_amdgcn_exp2f(zc_s[dd] - mc);  // 0 for an empty cluster
+    __syncthreads();
+    for (int gi = 0; gi < cl.m; ++gi) Lt += wc_s[gi];
+    if (dd < D) {
+#pragma unroll 8
       for (int gi = 0; gi < cl.m; ++gi)
-        if (zc_s[gi] != -INFINITY) vmax = fmax(vmax, (double)vn_s[gi] + (double)cl.rv[u * cl.m + gi]);
-      for (int gi = 0; gi < cl.m; ++gi) {
-        if (zc_s[gi] == -INFINITY) continue;
-        const double zeta = exp2((double)zc_s[gi] - (double)mc) / (double)Lt;
-        const double er = exp(rq * (double)cl.rk[u * cl.m + gi]);
-        dz += (er - 1.0) * er * zeta;
-        dn += er * zeta * ((er - 1.0) * (double)vn_s[gi] + (double)cl.rv[u * cl.m + gi]);
+        at = fmaf(wc_s[gi], wc_s[gi] > 0.f ? bf16_to_f32(cl.vbar[(u * cl.m + gi) * D + dd]) : 0.f, at);
+    }
+    if (dd < 64 && cl.bound) {
+      // the certificate: a cluster per lane of the first wave
+      const bool on = dd < cl.m && zc_s[dd < cl.m ? dd : 0] != -INFINITY;
+      double dz = 0.0, dn = 0.0, vmax = (double)cl.vmax_kept[u];
+      if (on) {
+        const double rq = (double)g.scale * (double)qn_s;
+        const double vn = (double)vn_s[dd], rv = (double)cl.rv[u * cl.m + dd];
+        const double zeta = exp2((double)zc_s[dd] - (double)mc) / (double)Lt;
+        const double er = exp(rq * (double)cl.rk[u * cl.m + dd]);
+        dz = (er - 1.0) * er * zeta;
+        dn = er * zeta * ((er - 1.0) * vn + rv);
+        vmax = fmax(vmax, vn + rv);
       }
-      cl.bound[orow] = dz <= 1.0 / 3.0 ? (float)(3.0 * (dn + vmax * dz)) : INFINITY;
+      dz = wave_sum(dz);
+      dn = wave_sum(dn);
+      vmax = wave_max(vmax);
+      if (dd == 0) cl.bound[orow] = dz <= 1.0 / 3.0 ? (float)(3.0 * (dn + vmax * dz)) : INFINITY;
     }
   }
+  if (dd >= D) return;
   const float o = at / Lt;
   if (!isfinite(o)) report_nonfinite(g);
   out[orow * D + dd] = o;
   if (lse && dd == 0) lse[orow] = (mx + __builtin_amdgcn_logf(Lt)) * kDecLn2;
+}
+
+// The combine for many rows: D / 4 threads take a row, so that a workgroup has
+// 1024 / D rows and no barrier, and the slots of a row are folded in order.
+// With a workgroup per row the launch is bound by starting workgroups: 32
+// layers of 8 heads, 128 rows a head, 54 us; 27 us here.  With few rows the
+// many slots of one are better dealt to the workgroup.
+template <int D>
+__global__ __launch_bounds__(kCombThreads) void decode_combine_rows_kernel(
+    Geo g, int64_t U, int64_t cover, int32_t keys_min, int32_t tq, int32_t nsplit, int32_t mp,
+    const int64_t* __restrict__ poff, const float* __restrict__ part_o,
+    const float2* __restrict__ part_ml, float* __restrict__ out, float* __restrict__ lse) {
+  constexpr int C4 = D / 4;
+  constexpr int RW = kCombThreads / C4;
+  const int64_t u = blockIdx.x;
+  const int row = blockIdx.y * RW + threadIdx.x / C4;
+  const int c4 = threadIdx.x % C4;
+  const int len = (int)(poff[u + 1] - poff[u]);
+  const int keys = dec_keys(poff, U, keys_min);
+  const int nv = (int)((min(cover, (int64_t)len) + keys - 1) / keys);
+  if (len > cover && blockIdx.y == 0 && threadIdx.x == 0) report_range(g);
+  if (row >= tq * g.G) return;
+  const int64_t base = u * nsplit * mp + row;  // + slot * mp
+  float m = -INFINITY, L = 0.f;
+  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+  constexpr int Q = 4;  // slots in flight; those past the last are read again and not folded
+  for (int s0 = 0; s0 < nv; s0 += Q) {
+    float2 ml[Q];
+    float4 o[Q];
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+      const int64_t pr = base + (int64_t)min(s0 + i, nv - 1) * mp;
+      ml[i] = part_ml[pr];
+      o[i] = reinterpret_cast<const float4*>(part_o + pr * D)[c4];
+    }
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+      if (s0 + i >= nv || ml[i].x == -INFINITY) continue;
+      const float mn = fmaxf(m, ml[i].x);
+      const float a = __builtin_amdgcn_exp2f(m - mn);  // 0 while m is -inf
+      const float w = __builtin_amdgcn_exp2f(ml[i].x - mn);
+      m = mn;
+      L = fmaf(L, a, ml[i].y * w);
+      acc.x = fmaf(acc.x, a, o[i].x * w);
+      acc.y = fmaf(acc.y, a, o[i].y * w);
+      acc.z = fmaf(acc.z, a, o[i].z * w);
+      acc.w = fmaf(acc.w, a, o[i].w * w);
+    }
+  }
+  const int h = (int)(u % g.H);
+  const int64_t lb = u / g.H;
+  const int b = (int)(lb % g.B);
+  const int l = (int)(lb / g.B);
+  const int t = row / g.G, gq = row % g.G;
+  const int64_t orow = ((int64_t)l * g.B * tq + (int64_t)b * tq + t) * (g.H * g.G) + h * g.G + gq;
+  acc.x /= L;
+  acc.y /= L;
+  acc.z /= L;
+  acc.w /= L;
+  if (!(isfinite(acc.x) && isfinite(acc.y) && isfinite(acc.z) && isfinite(acc.w)))
+    report_nonfinite(g);
+  reinterpret_cast<float4*>(out + orow * D)[c4] = acc;
+  if (lse && c4 == 0) lse[orow] = (m + __builtin_amdgcn_logf(L)) * kDecLn2;
 }
 
 template <int D, int NQT>
@@ -568,22 +719,36 @@ static certkv_status launch_decode(const DecodeArgs& a, hipStream_t s) {
   const uint16_t* q = static_cast<const uint16_t*>(a.q.ptr);
   const uint16_t* kp = static_cast<const uint16_t*>(a.k_packed);
   const uint16_t* vp = static_cast<const uint16_t*>(a.v_packed);
-  CERTKV_LAUNCH("decode_items", decode_items_kernel, dim3(1), dim3(kItemThreads), 0, s, a.U,
-                a.nsplit, a.packed_offsets, a.items, a.item_count);
-  CERTKV_LAUNCH("decode", (decode_kernel<D, NQT>), dim3(grid), dim3(NT), 0, s, g, a.items,
-                a.item_count, a.tq, a.nsplit, mp, q, a.q.s_layer, a.q.s_token, a.q.s_head, kp, vp,
-                a.packed_offsets, a.part_o, a.part_ml);
+#define CERTKV_DECODE(KERNEL)                                                                      \
+  CERTKV_LAUNCH("decode", (KERNEL<D, NQT>), dim3(grid), dim3(NT), 0, s, g, a.U,      \
+                a.cover, a.keys_min, (const int2*)a.items, (const int32_t*)a.item_count, a.tq,     \
+                a.nsplit, mp, q, a.q.s_layer, a.q.s_token, a.q.s_head, kp, vp, a.packed_offsets,   \
+                a.part_o, a.part_ml)
+  if (a.U <= kLocalUnits) {
+    CERTKV_DECODE(decode_local_kernel);
+  } else {
+    CERTKV_LAUNCH("decode_items", decode_items_kernel, dim3(1), dim3(kItemThreads), 0, s, a.U,
+                  a.cover, a.keys_min, a.packed_offsets, a.items, a.item_count);
+    CERTKV_DECODE(decode_kernel);
+  }
+#undef CERTKV_DECODE
   const int M = a.tq * g.G;
+  constexpr int RW = 4 * kCombThreads / D;
+#define CERTKV_COMBINE(CL)                                                                         \
+  CERTKV_LAUNCH("decode_combine", (decode_combine_kernel<D, CL>), dim3((unsigned)a.U, (unsigned)M), \
+                dim3(kCombThreads), 0, s, g, a.U, a.cover, a.keys_min, a.tq, a.nsplit, mp,         \
+                a.packed_offsets, (const float*)a.part_o, (const float2*)a.part_ml, a.out, a.lse,  \
+                a.cl, q, a.q.s_layer, a.q.s_token, a.q.s_head)
   if (a.cl.m > 0)
-    CERTKV_LAUNCH("decode_combine", (decode_combine_kernel<D, true>),
-                  dim3((unsigned)a.U, (unsigned)M), dim3(kCombThreads), 0, s, g, a.tq, a.nsplit, mp,
-                  a.packed_offsets, (const float*)a.part_o, (const float2*)a.part_ml, a.out, a.lse,
-                  a.cl, q, a.q.s_layer, a.q.s_token, a.q.s_head);
+    CERTKV_COMBINE(true);
+  else if (a.U * M < 8192)
+    CERTKV_COMBINE(false);
   else
-    CERTKV_LAUNCH("decode_combine", (decode_combine_kernel<D, false>),
-                  dim3((unsigned)a.U, (unsigned)M), dim3(kCombThreads), 0, s, g, a.tq, a.nsplit, mp,
-                  a.packed_offsets, (const float*)a.part_o, (const float2*)a.part_ml, a.out, a.lse,
-                  a.cl, q, a.q.s_layer, a.q.s_token, a.q.s_head);
+    CERTKV_LAUNCH("decode_combine", (decode_combine_rows_kernel<D>),
+                  dim3((unsigned)a.U, (unsigned)((M + RW - 1) / RW)), dim3(kCombThreads), 0, s, g,
+                  a.U, a.cover, a.keys_min, a.tq, a.nsplit, mp, a.packed_offsets,
+                  (const float*)a.part_o, (const float2*)a.part_ml, a.out, a.lse);
+#undef CERTKV_COMBINE
   return CERTKV_OK;
 }
 
@@ -602,10 +767,24 @@ certkv_status run_decode(const DecodeArgs& a, hipStream_t s) {
   return a.g.D == 128 ? launch_decode_d<128>(a, s) : launch_decode_d<64>(a, s);
 }
 
+// Rows of partials: [U][nsplit][32 NQT].
 size_t decode_partial_rows(int64_t U, int nsplit, int tq, int G) {
   return (size_t)U * nsplit * decode_nqt(tq * G) * 32;
 }
 
-int decode_nsplit(int max_len) { return (max_len + kDecKeys - 1) / kDecKeys; }
+// The shortest chunk whose partials take up to 2^17 rows for units of max_len
+// (64 MB of outputs at 128 dims), else 4096 keys.  (Not from a caller's tighter
+// row bound: the chunks, and so the bits, are the same under any bound.)
+int decode_keys_min(int64_t U, int max_len, int tq, int G) {
+  const int64_t rows = ((int64_t)max_len + kDecKeys - 1) / kDecKeys * kDecKeys;
+  int k = kDecKeysMin;
+  while (k < kDecKeys && U * (rows / k) * decode_nqt(tq * G) * 32 > (1 << 17)) k *= 2;
+  return k;
+}
+
+// Rows of a unit that the chunks cover: the bound, up to whole 4096s.
+int64_t decode_cover(int max_rows) {
+  return ((int64_t)max_rows + kDecKeys - 1) / kDecKeys * kDecKeys;
+}
 
 }  // namespace certkv

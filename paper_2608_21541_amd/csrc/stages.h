@@ -186,7 +186,9 @@ struct DecodeArgs {
   Geo g;
   int64_t U;
   int32_t tq;                   // new queries per sequence
-  int32_t nsplit;               // 1024-key chunks of the longest segment allowed
+  int32_t keys_min;             // shortest chunk the workspace has slots for
+  int64_t cover;                // rows of a segment that the chunks cover
+  int32_t nsplit;               // slots per unit: cover / keys_min
   certkv_tensor q;              // [L][B*tq][Hq][d] bf16
   const void* k_packed;         // [P][d] bf16
   const void* v_packed;
@@ -207,7 +209,8 @@ inline int decode_nqt(int M) {
 }
 certkv_status run_decode(const DecodeArgs& a, hipStream_t s);
 size_t decode_partial_rows(int64_t U, int nsplit, int tq, int G);
-int decode_nsplit(int max_len);
+int decode_keys_min(int64_t U, int max_len, int tq, int G);
+int64_t decode_cover(int max_rows);
 
 certkv_status run_packed_from_kept(int64_t U, int32_t slot, const int64_t* kept_offsets,
                                    int64_t* packed_offsets, hipStream_t s);

@@ -238,3 +238,32 @@ def test_hull_allocation_beside_the_full_search(layers):
             for b, (t0, n) in enumerate(zip((0, lens[0]), lens)):
                 want, _ = oracle.allocate(c[li, :, t0:t0 + n], n_keep[b], steps=steps)
                 assert np.array_equal(got[li, b], want), (steps, li, b)
+
+
+@pytest.mark.parametrize("dim,group,tq", [(128, 4, 1), (128, 4, 33), (64, 1, 1), (128, 8, 8)])
+@pytest.mark.parametrize("rows", [[1, 2, 31, 127, 128, 129, 4097, 700], [9000] * 4 + [3] * 5,
+                                  [37] * 300, [150000, 10, 4096, 0, 65536]])
+def test_decode_chunks(rows, dim, group, tq):
+    # Chunk lengths from 128 to 4096 keys, segments of a row to many chunks and
+    # an empty one, units found by the workgroups and from the list, both
+    # combines.  Rows within 1e-4 of fp64 attention, as the decode tests.
+    if len(rows) == 300 and dim == 64:
+        rows = rows * 30                       # many rows: the row combine
+    n = max(max(rows), 16)
+    spec = ck.ProblemSpec(1, 1, group, dim, 16, [n] * len(rows))
+    gen = torch.Generator(device=DEV).manual_seed(sum(rows) + tq)
+    off = torch.tensor([0] + list(np.cumsum(rows)), dtype=torch.int64, device=DEV)
+    kp, vp = (torch.randn((sum(rows), dim), generator=gen, device=DEV).bfloat16() for _ in range(2))
+    q = torch.randn((1, len(rows) * tq, group, dim), generator=gen, device=DEV).bfloat16()
+    out, lse = ck.decode(spec, q, kp, vp, off, tq, with_lse=True, max_rows=max(rows))
+    for u in range(0, len(rows), 1 if len(rows) < 50 else 97):
+        a, b = int(off[u]), int(off[u + 1])
+        if a == b:
+            continue
+        x = q[0, u * tq:(u + 1) * tq].double().reshape(tq * group, dim)
+        z = (x @ kp[a:b].double().t().contiguous()) / dim ** 0.5
+        ref = torch.softmax(z, 1) @ vp[a:b].double()
+        got = out[0, u * tq:(u + 1) * tq].double().reshape(tq * group, dim)
+        assert ((got - ref).norm(dim=1) <= 1e-4 * ref.norm(dim=1)).all(), u
+        err = lse[0, u * tq:(u + 1) * tq].double().reshape(-1) - torch.logsumexp(z, 1)
+        assert err.abs().max() <= 1e-4
