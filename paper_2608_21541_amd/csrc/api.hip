@@ -173,13 +173,20 @@ static certkv_status make_plan(const certkv_problem* p, Plan* pl) {
   // window queries and the per-block reduction.
   int kpb = 256, kpb2 = 256;
   if (P.dtype == CERTKV_BF16) {
-    auto grow = [&](int64_t min_wgs) {
+    auto grow = [&](int64_t min_wgs, auto blocks) {
       int k = 512;
-      while (k < 65536 && P.U * ((max_len + 2 * k - 1) / (2 * k)) >= min_wgs) k *= 2;
+      while (k < 65536 && P.g.L * P.g.H * blocks(2 * k) >= min_wgs) k *= 2;
       return k;
     };
-    kpb = grow(4 * 2 * (int64_t)kCUs);
-    kpb2 = grow(4 * (int64_t)kCUs);
+    // Pass 1's blocks are part of the order of its sums, and so of the scores'
+    // bits: they are counted as if every sequence were the longest.
+    kpb = grow(4 * 2 * (int64_t)kCUs,
+               [&](int64_t k) { return P.g.B * ((max_len + k - 1) / k); });
+    kpb2 = grow(4 * (int64_t)kCUs, [&](int64_t k) {
+      int64_t c = 0;
+      for (int b = 0; b < P.g.B; ++b) c += (cu[b + 1] - cu[b] + k - 1) / k;
+      return c;
+    });
   }
   P.kpb = kpb;
   P.nkb_max = (max_len + kpb - 1) / kpb;

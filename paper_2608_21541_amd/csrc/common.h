@@ -70,6 +70,35 @@ __device__ __forceinline__ int64_t lht_base(const Geo& g, int l, int h, int64_t 
   return ((int64_t)l * g.H + h) * g.T + tok0;
 }
 
+// Work items of a launch whose units have different numbers of parts: numbered
+// by sequence, head and part, so that only parts that exist are launched and
+// consecutive workgroups, which go to the XCDs in turn, load them evenly.
+// Item x -> its sequence (returned; st.count past the end), head and part;
+// parts(bl) is the number of parts of a unit of sequence bl.
+template <typename F>
+__device__ __forceinline__ int locate_part(const Geo& g, const SeqTab& st, int x, F parts, int& h,
+                                           int& part) {
+  int bl = 0;
+  h = part = 0;
+  for (; bl < st.count; ++bl) {
+    const int c = parts(bl);
+    if (x < c * g.H) {
+      h = x / c;
+      part = x - h * c;
+      break;
+    }
+    x -= c * g.H;
+  }
+  return bl;
+}
+// Items of such a launch per layer.
+template <typename F>
+inline unsigned count_parts(const Geo& g, const SeqTab& st, F parts) {
+  int64_t c = 0;
+  for (int bl = 0; bl < st.count; ++bl) c += parts(bl);
+  return (unsigned)(c * g.H);
+}
+
 // Raw buffer resource over [base, base + bytes): loads through it take a
 // uniform 64-bit base and a 32-bit per-lane byte offset, and return zero for
 // offsets at or beyond `bytes` (hardware range check).

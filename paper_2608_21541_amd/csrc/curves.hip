@@ -48,6 +48,12 @@ constexpr int kRPH = 16;                       // ranks per half-wave and chunk
 constexpr int kSubs = 2 * kCurveWaves;         // sub-ranges per chunk
 static_assert(kCurveChunk == kSubs * kRPH, "ranks of a chunk");  // 512
 
+// Segments of a unit of n ranks.
+__host__ __device__ inline int curve_segments(int n, int seg_chunks) {
+  const int nch = (n + kCurveChunk - 1) / kCurveChunk;
+  return (nch + seg_chunks - 1) / seg_chunks;
+}
+
 template <int DP, int RAW, bool BF16>
 __device__ __forceinline__ void unpack_dims(const uint32_t (&raw)[RAW], float (&v)[DP]) {
 #pragma unroll
@@ -138,16 +144,15 @@ __global__ __launch_bounds__(kCurveThreads) __attribute__((amdgpu_waves_per_eu(8
   __shared__ double tR[kCurveWaves][kLPR * NR];
   __shared__ double wa[kCurveWaves][2 * kRPH];
   __shared__ uint32_t wo[kCurveWaves][2 * kRPH];
-  const int seg = 1 + (int)(blockIdx.x % (nseg_max - 1));
-  const int hb = blockIdx.x / (nseg_max - 1);
-  const int h = hb % g.H;
-  const int bl = hb / g.H;
+  int h, seg;
+  const int bl = locate_part(
+      g, st, blockIdx.x, [&](int i) { return curve_segments(st.len[i], seg_chunks) - 1; }, h, seg);
+  ++seg;
   const int l = blockIdx.y;
   if (bl >= st.count) return;
   const int b = st.first + bl;
   const int n = st.len[bl];
   const int r_lo = seg * seg_chunks * kCurveChunk;
-  if (r_lo >= n) return;
   const int r_hi = min(n, r_lo + seg_chunks * kCurveChunk);
   const int64_t tok0 = st.start[bl];
   const int64_t base = lht_base(g, l, h, tok0);
@@ -257,17 +262,15 @@ __global__ __launch_bounds__(kCurveThreads) void curves_kernel(
   // conflicts)
   __shared__ __align__(16) double red[kCurveWaves][64][9];
 
-  const int seg = blockIdx.x % nseg_max;  // 0 of 1: the whole unit
-  const int hb = blockIdx.x / nseg_max;
-  const int h = hb % g.H;
-  const int bl = hb / g.H;
+  int h, seg;  // 0 of 1: the whole unit
+  const int bl = locate_part(
+      g, st, blockIdx.x, [&](int i) { return curve_segments(st.len[i], seg_chunks); }, h, seg);
   const int l = blockIdx.y;
   if (bl >= st.count) return;
   const int b = st.first + bl;
   const int n = st.len[bl];
   const int nch = (n + kCurveChunk - 1) / kCurveChunk;
   const int k_lo = seg * seg_chunks;  // chunks [k_lo, k_hi) of the unit
-  if (k_lo >= nch) return;
   const int k_hi = min(nch, k_lo + seg_chunks);
   const int64_t tok0 = st.start[bl];
   const int64_t base = lht_base(g, l, h, tok0);
@@ -518,11 +521,12 @@ __global__ __launch_bounds__(kCurveThreads) void curves_kernel(
 
 template <int D, bool BF16>
 static certkv_status launch_curves(const CurveArgs& a, const SeqTab& st, hipStream_t s) {
-  const dim3 grid(a.g.H * st.count * a.nseg_max, a.g.L);
-  if (a.nseg_max > 1)
-    CERTKV_LAUNCH("curve_totals", (curve_totals_kernel<D, BF16>),
-                  dim3(a.g.H * st.count * (a.nseg_max - 1), a.g.L), dim3(kCurveThreads), 0, s, a.g,
-                  st, a.sorted_keys, a.perm, a.ssum, a.v.ptr, a.v.s_layer, a.v.s_token, a.v.s_head,
+  auto segments = [&](int i) { return curve_segments(st.len[i], a.seg_chunks); };
+  const dim3 grid(count_parts(a.g, st, segments), a.g.L);
+  const unsigned above = count_parts(a.g, st, [&](int i) { return segments(i) - 1; });
+  if (above > 0)
+    CERTKV_LAUNCH("curve_totals", (curve_totals_kernel<D, BF16>), dim3(above, a.g.L),
+                  dim3(kCurveThreads), 0, s, a.g, st, a.sorted_keys, a.perm, a.ssum, a.v.ptr, a.v.s_layer, a.v.s_token, a.v.s_head,
                   a.seg_chunks, a.nseg_max, a.segtot);
 #define CERTKV_CURVES(STAT)                                                                        \
   CERTKV_LAUNCH("curves", (curves_kernel<D, BF16, STAT>), grid, dim3(kCurveThreads), 0, s, a.g, st, \

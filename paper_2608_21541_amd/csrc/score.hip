@@ -46,6 +46,19 @@ struct ScoreSmem {
 
 enum { kPass1Sum = 0, kPass1Max = 1 };
 
+// Block x of a launch -> its sequence (returned), head and key block.  Only the
+// blocks that exist are numbered (locate_part): with the longest sequence's
+// blocks for every one, short sequences' blocks fell to the first XCDs alone
+// (eight ragged sequences: pass 1 171 us, 122 us so; pass 2 220 and 152).  With
+// the heads of a block next to each other, each XCD reading one head of the
+// same tokens, uniform lengths were slower (64 units of 32768 keys, 128 rows:
+// pass 1 130 us against 121, 32 rows 115 against 102).
+__device__ __forceinline__ int score_block(const Geo& g, const SeqTab& st, int32_t keys_per_block,
+                                           int x, int& kb, int& h) {
+  return locate_part(
+      g, st, x, [&](int bl) { return (st.len[bl] + keys_per_block - 1) / keys_per_block; }, h, kb);
+}
+
 // One round of a transpose-reduce over lane bit M: lanes with that bit set
 // keep the upper HALF of their 2*HALF values, the others the lower HALF, and
 // each adds its partner's copy of the half it keeps.  The rounds recurse at
@@ -83,10 +96,9 @@ __global__ __launch_bounds__(kScoreThreads) __attribute__((amdgpu_waves_per_eu(N
   extern __shared__ __align__(16) unsigned char smem_raw[];
   uint16_t* q_lds = reinterpret_cast<uint16_t*>(smem_raw);
 
-  const int kb = blockIdx.x;
-  const int h = blockIdx.y % g.H;
-  const int bl = blockIdx.y / g.H;
-  const int l = blockIdx.z;
+  const int l = blockIdx.y;
+  int kb, h;
+  const int bl = score_block(g, st, keys_per_block, blockIdx.x, kb, h);
   if (bl >= st.count) return;
   const int b = st.first + bl;
   const int n = st.len[bl];
@@ -326,10 +338,9 @@ __global__ __launch_bounds__(kScoreThreads) __attribute__((amdgpu_waves_per_eu((
   extern __shared__ __align__(16) unsigned char smem_raw[];
   uint16_t* q_lds = reinterpret_cast<uint16_t*>(smem_raw);
 
-  const int kb = blockIdx.x;
-  const int h = blockIdx.y % g.H;
-  const int bl = blockIdx.y / g.H;
-  const int l = blockIdx.z;
+  const int l = blockIdx.y;
+  int kb, h;
+  const int bl = score_block(g, st, keys_per_block, blockIdx.x, kb, h);
   if (bl >= st.count) return;
   const int b = st.first + bl;
   const int n = st.len[bl];
@@ -585,10 +596,9 @@ __global__ __launch_bounds__(kP2Threads) __attribute__((amdgpu_waves_per_eu(4, 8
   int* lim_lds = reinterpret_cast<int*>(smem_raw + SM::lim);
   float* red_lds = reinterpret_cast<float*>(smem_raw);
 
-  const int kb = blockIdx.x;
-  const int h = blockIdx.y % g.H;
-  const int bl = blockIdx.y / g.H;
-  const int l = blockIdx.z;
+  const int l = blockIdx.y;
+  int kb, h;
+  const int bl = score_block(g, st, keys_per_block, blockIdx.x, kb, h);
   if (bl >= st.count) return;
   const int b = st.first + bl;
   const int n = st.len[bl];
@@ -828,7 +838,10 @@ __global__ __launch_bounds__(256) void lse_combine_kernel(Geo g, SeqTab st, int3
   __syncthreads();
   for (int rho = threadIdx.x; rho < M; rho += blockDim.x) {
     if (SUM_FORMAT) {
+      // added in block order; unrolled so that 16 blocks' loads are in flight
+      // (64 blocks a unit: 20 us without, 7 us so)
       float s = 0.f;
+#pragma unroll 16
       for (int kb = 0; kb < nkb; ++kb) s += part[(u * nkb_max + kb) * M + rho].x;
       if (!(s >= kSumLo && s <= kSumHi)) bad = 1;
       lse2[u * M + rho] = __builtin_amdgcn_logf(s);
@@ -893,6 +906,7 @@ __global__ __launch_bounds__(128) void ksum_reduce_kernel(Geo g, SeqTab st, int3
   const int64_t u = unit_index(g, l, b, h);
   for (int dd = threadIdx.x; dd < g.D; dd += blockDim.x) {
     double s = 0.0;
+#pragma unroll 16
     for (int kb = 0; kb < nkb; ++kb) s += (double)kpart[(u * nkb_max + kb) * g.D + dd];
     ksum[u * g.D + dd] = s;
   }
@@ -997,13 +1011,13 @@ size_t score_smem_bytes(const Geo& g, int32_t dtype) {
 }
 
 template <int D, int NQT>
-static certkv_status launch_mfma(const ScoreArgs& a, const SeqTab& st, int max_len,
-                                 hipStream_t s) {
+static certkv_status launch_mfma(const ScoreArgs& a, const SeqTab& st, hipStream_t s) {
   const Geo& g = a.g;
-  const int nkb = (max_len + a.keys_per_block - 1) / a.keys_per_block;
-  const int nkb2 = (max_len + a.keys_per_block2 - 1) / a.keys_per_block2;
-  dim3 grid(nkb, g.H * st.count, g.L);
-  dim3 grid2(nkb2, g.H * st.count, g.L);
+  auto blocks = [&](int32_t keys) {
+    return count_parts(g, st, [&](int bl) { return ((int64_t)st.len[bl] + keys - 1) / keys; });
+  };
+  dim3 grid(blocks(a.keys_per_block), g.L);
+  dim3 grid2(blocks(a.keys_per_block2), g.L);
   size_t smem = score_smem_bytes(g, CERTKV_BF16);
   static bool attr_set = false;
   if (!attr_set) {
@@ -1110,21 +1124,21 @@ static certkv_status launch_f32(const ScoreArgs& a, const SeqTab& st, int max_le
 }
 
 template <int D>
-static certkv_status dispatch_nqt(const ScoreArgs& a, const SeqTab& st, int max_len, hipStream_t s) {
+static certkv_status dispatch_nqt(const ScoreArgs& a, const SeqTab& st, hipStream_t s) {
   switch (score_nqt(a.g.w * a.g.G)) {
-    case 1: return launch_mfma<D, 1>(a, st, max_len, s);
-    case 2: return launch_mfma<D, 2>(a, st, max_len, s);
-    case 4: return launch_mfma<D, 4>(a, st, max_len, s);
-    case 8: return launch_mfma<D, 8>(a, st, max_len, s);
-    default: return launch_mfma<D, 16>(a, st, max_len, s);
+    case 1: return launch_mfma<D, 1>(a, st, s);
+    case 2: return launch_mfma<D, 2>(a, st, s);
+    case 4: return launch_mfma<D, 4>(a, st, s);
+    case 8: return launch_mfma<D, 8>(a, st, s);
+    default: return launch_mfma<D, 16>(a, st, s);
   }
 }
 
 certkv_status run_score(const ScoreArgs& a, const SeqTab& st, int max_len, hipStream_t s) {
   if (a.dtype == CERTKV_F32)
     return a.g.D == 128 ? launch_f32<128>(a, st, max_len, s) : launch_f32<64>(a, st, max_len, s);
-  if (a.g.D == 128) return dispatch_nqt<128>(a, st, max_len, s);
-  return dispatch_nqt<64>(a, st, max_len, s);
+  if (a.g.D == 128) return dispatch_nqt<128>(a, st, s);
+  return dispatch_nqt<64>(a, st, s);
 }
 
 }  // namespace certkv

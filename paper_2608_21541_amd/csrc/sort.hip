@@ -42,6 +42,11 @@
 
 namespace certkv {
 
+// Tiles of a unit of n elements.
+__host__ __device__ inline int sort_tiles(int n) {
+  return (int)(((int64_t)n + kSortRun - 1) / kSortRun);
+}
+
 constexpr int kSortThreads = 1024;
 constexpr int kSortWaves = kSortThreads / 64;
 constexpr int kSortRounds = 8;
@@ -667,15 +672,13 @@ __global__ __launch_bounds__(kSortThreads) void sort_count_kernel(
   __shared__ uint64_t sp[256];
   __shared__ uint32_t cnt_s[256];
   __shared__ double red[kSortWaves];
-  const int tile = blockIdx.x % ntile_max;
-  const int hb = blockIdx.x / ntile_max;
-  const int h = hb % g.H;
-  const int bl = hb / g.H;
+  int h, tile;
+  const int bl = locate_part(
+      g, st, blockIdx.x, [&](int i) { return sort_tiles(st.len[i]); }, h, tile);
   const int l = blockIdx.y;
   if (bl >= st.count) return;
   const int n = st.len[bl];
   const int e0 = tile * kSortRun;
-  if (e0 >= n) return;
   const int nb = sort_nb(n);
   const int64_t base = lht_base(g, l, h, st.start[bl]);
   const int64_t u = unit_index(g, l, st.first + bl, h);
@@ -726,15 +729,13 @@ __global__ __launch_bounds__(kSortThreads) void sort_scatter_kernel(
   __shared__ uint16_t soff[kSortRun];   // position within the tile
   __shared__ uint8_t sid[kSortRun];
   __shared__ uint32_t bstart[256], before[256];
-  const int tile = blockIdx.x % ntile_max;
-  const int hb = blockIdx.x / ntile_max;
-  const int h = hb % g.H;
-  const int bl = hb / g.H;
+  int h, tile;
+  const int bl = locate_part(
+      g, st, blockIdx.x, [&](int i) { return sort_tiles(st.len[i]); }, h, tile);
   const int l = blockIdx.y;
   if (bl >= st.count) return;
   const int n = st.len[bl];
   const int e0 = tile * kSortRun;
-  if (e0 >= n) return;
   const int nb = sort_nb(n);
   const int ntile = (n + kSortRun - 1) / kSortRun;
   const int cnt = min(kSortRun, n - e0);
@@ -811,15 +812,13 @@ __attribute__((amdgpu_waves_per_eu(8, 8))) void sort_buckets_kernel(
   __shared__ OrderLds so;
   RankLds& rk = so.rk;
   __shared__ uint32_t place[256];  // next place of each digit (sorts through memory)
-  const int bk = blockIdx.x % nb_max;
-  const int hb = blockIdx.x / nb_max;
-  const int h = hb % g.H;
-  const int bl = hb / g.H;
+  int h, bk;
+  const int bl = locate_part(
+      g, st, blockIdx.x, [&](int i) { return sort_nb(st.len[i]); }, h, bk);
   const int l = blockIdx.y;
   if (bl >= st.count) return;
   const int n = st.len[bl];
   const int nb = sort_nb(n);
-  if (bk >= nb) return;
   const int64_t base = lht_base(g, l, h, st.start[bl]);
   const int64_t u = unit_index(g, l, st.first + bl, h);
   const int lo = (int)bucket_start[u * (nb_max + 1) + bk];
@@ -919,7 +918,7 @@ certkv_status run_sort(const SortArgs& a, const SeqTab& st, hipStream_t s) {
     return CERTKV_OK;
   }
   uint8_t* ids = reinterpret_cast<uint8_t*>(a.valsA);  // dead before the buckets are written
-  const dim3 tiles(g.H * st.count * a.ntile_max, g.L);
+  const dim3 tiles(count_parts(g, st, [&](int i) { return sort_tiles(st.len[i]); }), g.L);
   CERTKV_LAUNCH("sort_splitters", sort_splitters_kernel, units, dim3(kSortThreads), 0, s, g, st,
                 a.nb_max, a.scores, a.splitters, a.windows);
   CERTKV_LAUNCH("sort_count", sort_count_kernel, tiles, dim3(kSortThreads), 0, s, g, st,
@@ -928,7 +927,8 @@ certkv_status run_sort(const SortArgs& a, const SeqTab& st, hipStream_t s) {
   CERTKV_LAUNCH("sort_scatter", sort_scatter_kernel, tiles, dim3(kSortThreads), 0, s, g, st,
                 a.ntile_max, a.nb_max, a.scores, (const uint8_t*)ids, (const uint32_t*)a.counts,
                 (const double*)a.tile_sum, a.keysB, a.valsB, a.bucket_start, a.ssum);
-  CERTKV_LAUNCH("sort_buckets", sort_buckets_kernel, dim3(g.H * st.count * a.nb_max, g.L),
+  CERTKV_LAUNCH("sort_buckets", sort_buckets_kernel,
+                dim3(count_parts(g, st, [&](int i) { return sort_nb(st.len[i]); }), g.L),
                 dim3(kSortThreads), 0, s, g, st, a.nb_max, a.scores, a.keysB, a.valsB,
                 (const uint32_t*)a.bucket_start, (const uint2*)a.windows, a.keys_out, a.perm_out);
   return CERTKV_OK;
