@@ -187,6 +187,8 @@ static certkv_status make_plan(const certkv_problem* p, Plan* pl) {
       for (int b = 0; b < P.g.B; ++b) c += (cu[b + 1] - cu[b] + k - 1) / k;
       return c;
     });
+  } else if (P.U * ((max_len + 255) / 256) < 2 * kCUs) {
+    kpb2 = 64;  // fp32 pass 2: blocks of one wave where blocks of four are under two per CU
   }
   P.kpb = kpb;
   P.nkb_max = (max_len + kpb - 1) / kpb;
@@ -443,8 +445,8 @@ static certkv_status do_score(const Plan& P, certkv_tensor q, certkv_tensor k,
   a.flag = w.flag;
   a.keys_per_block = P.dtype == CERTKV_BF16 ? P.kpb : 256;
   a.nkb_max = P.dtype == CERTKV_BF16 ? P.nkb_max : (P.max_len + 255) / 256;
-  a.keys_per_block2 = P.dtype == CERTKV_BF16 ? P.kpb2 : 256;
-  a.nkb2_max = P.dtype == CERTKV_BF16 ? P.nkb2_max : (P.max_len + 255) / 256;
+  a.keys_per_block2 = P.kpb2;
+  a.nkb2_max = P.nkb2_max;
   for (const SeqTab& t : make_tabs(P, nullptr, 0.f)) {
     int ml = 0;
     for (int i = 0; i < t.count; ++i) ml = t.len[i] > ml ? t.len[i] : ml;

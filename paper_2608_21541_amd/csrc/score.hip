@@ -914,15 +914,26 @@ __global__ __launch_bounds__(128) void ksum_reduce_kernel(Geo g, SeqTab st, int3
 
 // ---------------------------------------------------------------------------
 // fp32 inputs: one key per thread, window queries in LDS, VALU dot products.
-template <int D, bool P2>
-__global__ __launch_bounds__(256) void score_f32_kernel(
+//
+// A row's dot product is a chain of D dependent FMAs and its block sum two
+// reductions, so rows go kF32Rows at a time: independent chains side by side,
+// and two barriers for all of them.  Pass 1's rows are shared out over rsplit
+// workgroups per key block and pass 2's blocks hold KB = 64 keys instead of
+// 256 where whole blocks would leave the chip idle; neither changes the order
+// in which a row sum or a score is added up.  Bound by latency at small sizes:
+// 1024 keys, 16 rows, 4 heads of 64: 22 + 25 us one row at a time in 16
+// workgroups, 9 + 13 us.
+constexpr int kF32Rows = 4;
+template <int D, bool P2, int KB>
+__global__ __launch_bounds__(KB) void score_f32_kernel(
     Geo g, SeqTab st, const float* __restrict__ qw, int64_t q_sl, int64_t q_st, int64_t q_sh,
     const float* __restrict__ kc, int64_t k_sl, int64_t k_st, int64_t k_sh, int32_t nkb_max,
-    float2* __restrict__ part, const float* __restrict__ lse2, float* __restrict__ scores,
-    float* __restrict__ kpart) {
+    int32_t rsplit, float2* __restrict__ part, const float* __restrict__ lse2,
+    float* __restrict__ scores, float* __restrict__ kpart) {
+  constexpr int NW = KB / 64, R = kF32Rows;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   float* q_lds = reinterpret_cast<float*>(smem_raw);
-  const int kb = blockIdx.x;
+  const int kb = blockIdx.x / rsplit;
   const int h = blockIdx.y % g.H;
   const int bl = blockIdx.y / g.H;
   const int l = blockIdx.z;
@@ -930,67 +941,128 @@ __global__ __launch_bounds__(256) void score_f32_kernel(
   const int b = st.first + bl;
   const int n = st.len[bl];
   const int64_t tok0 = st.start[bl];
-  if (kb * 256 >= n) return;
+  if (kb * KB >= n) return;
   const int M = g.w * g.G;
+  // this workgroup's rows (all of them in pass 2: rsplit = 1)
+  const int per = ((M + rsplit - 1) / rsplit + R - 1) / R * R;
+  const int r0 = (blockIdx.x % rsplit) * per, rows = min(M - r0, per);
+  if (rows <= 0) return;
   const int64_t u = unit_index(g, l, b, h);
   float* lse_lds = q_lds + M * D;
-  float* red = lse_lds + M;  // [8] + [4][D]
-  for (int c = threadIdx.x; c < M * D; c += 256) {
-    int rho = c / D, dd = c % D;
-    int qq = rho / g.G, gq = rho % g.G;
-    q_lds[c] = qw[(int64_t)l * q_sl + (int64_t)(b * g.w + qq) * q_st + (int64_t)(h * g.G + gq) * q_sh + dd];
+  float* red = lse_lds + M;  // [2][R][NW], then [NW][D]
+  for (int c = threadIdx.x; c < rows * (D / 4); c += KB) {
+    const int rho = r0 + c / (D / 4), d4 = c % (D / 4);
+    const int qq = rho / g.G, gq = rho % g.G;
+    reinterpret_cast<float4*>(q_lds)[c] = reinterpret_cast<const float4*>(
+        qw + (int64_t)l * q_sl + (int64_t)(b * g.w + qq) * q_st + (int64_t)(h * g.G + gq) * q_sh)[d4];
   }
   if (P2)
-    for (int i = threadIdx.x; i < M; i += 256) lse_lds[i] = lse2[u * M + i];
-  __syncthreads();
-  const int key = kb * 256 + threadIdx.x;
+    for (int i = threadIdx.x; i < M; i += KB) lse_lds[i] = lse2[u * M + i];
+  const int key = kb * KB + threadIdx.x;
   const bool valid = key < n;
   const int keyc = valid ? key : n - 1;
   const float* krow = kc + (int64_t)l * k_sl + (tok0 + keyc) * k_st + (int64_t)h * k_sh;
   float kr[D];
 #pragma unroll
-  for (int t = 0; t < D; ++t) kr[t] = krow[t];
+  for (int t = 0; t < D; t += 4) {
+    const float4 x = *reinterpret_cast<const float4*>(krow + t);
+    kr[t] = x.x;
+    kr[t + 1] = x.y;
+    kr[t + 2] = x.z;
+    kr[t + 3] = x.w;
+  }
+  __syncthreads();
   const float c2 = g.scale * kLog2e;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   float s_acc = 0.f;
-  for (int rho = 0; rho < M; ++rho) {
-    const float* qr = q_lds + rho * D;
-    float dot = 0.f;
+  for (int i0 = 0; i0 < rows; i0 += R) {
+    float dot[R];
 #pragma unroll
-    for (int t = 0; t < D; ++t) dot = fmaf(qr[t], kr[t], dot);
-    const int qpos = n - g.w + rho / g.G;
-    const bool vis = valid && (!g.causal || key <= qpos);
-    const float x = dot * c2;
+    for (int i = 0; i < R; ++i) dot[i] = 0.f;
+#pragma unroll
+    for (int t = 0; t < D; t += 4) {
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        // rows past the end repeat the last one, unused
+        const float4 x = *reinterpret_cast<const float4*>(q_lds + min(i0 + i, rows - 1) * D + t);
+        dot[i] = fmaf(x.x, kr[t], dot[i]);
+        dot[i] = fmaf(x.y, kr[t + 1], dot[i]);
+        dot[i] = fmaf(x.z, kr[t + 2], dot[i]);
+        dot[i] = fmaf(x.w, kr[t + 3], dot[i]);
+      }
+    }
+    bool vis[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      const int qpos = n - g.w + (r0 + min(i0 + i, rows - 1)) / g.G;
+      vis[i] = valid && (!g.causal || key <= qpos);
+      dot[i] *= c2;
+    }
     if (!P2) {
-      float mx = wave_max(vis ? x : -INFINITY);
-      if (lane == 0) red[wave] = mx;
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        const float mx = wave_max(vis[i] ? dot[i] : -INFINITY);
+        if (lane == 0) red[i * NW + wave] = mx;
+      }
       __syncthreads();
-      float mt = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+      float mt[R];
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        mt[i] = red[i * NW];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) mt[i] = fmaxf(mt[i], red[i * NW + w]);
+        const float e =
+            (vis[i] && mt[i] != -INFINITY) ? __builtin_amdgcn_exp2f(dot[i] - mt[i]) : 0.f;
+        const float sw = wave_sum(e);
+        if (lane == 0) red[(R + i) * NW + wave] = sw;
+      }
+      // (the next rows' maxima are written before this barrier by no wave, and
+      // their sums only after the next one)
       __syncthreads();
-      float e = (vis && mt != -INFINITY) ? __builtin_amdgcn_exp2f(x - mt) : 0.f;
-      float sw = wave_sum(e);
-      if (lane == 0) red[wave] = sw;
-      __syncthreads();
-      if (threadIdx.x == 0)
-        part[(u * nkb_max + kb) * M + rho] = make_float2(mt, red[0] + red[1] + red[2] + red[3]);
-      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        if ((int)threadIdx.x != i || i0 + i >= rows) continue;
+        float sum = red[(R + i) * NW];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) sum += red[(R + i) * NW + w];
+        part[(u * nkb_max + kb) * M + r0 + i0 + i] = make_float2(mt[i], sum);
+      }
     } else {
-      if (vis) s_acc += __builtin_amdgcn_exp2f(x - lse_lds[rho]);
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        const float e = __builtin_amdgcn_exp2f(dot[i] - lse_lds[min(i0 + i, rows - 1)]);
+        if (vis[i] && i0 + i < rows) s_acc += e;
+      }
     }
   }
   if (P2) {
     if (valid) scores[lht_base(g, l, h, tok0) + key] = s_acc;
     if (kpart) {
       const float sp = (valid && s_acc > 0.f) ? s_acc : 0.f;
-      float* wred = red + 8;
+      float* wred = red + 2 * R * NW;
+      // The wave's D sums: in each step of the exchange a lane passes on half of
+      // the dimensions it holds (D - D / 64 exchanges, not 6 D), so that lane i
+      // ends with dimensions D / 64 i onwards.
 #pragma unroll
-      for (int t = 0; t < D; ++t) {
-        float x = wave_sum(sp * kr[t]);
-        if (lane == 0) wred[wave * D + t] = x;
+      for (int t = 0; t < D; ++t) kr[t] *= sp;
+#pragma unroll
+      for (int m = 32, half = D / 2; m >= 1; m >>= 1, half >>= 1) {
+        const bool up = (lane & m) != 0;
+#pragma unroll
+        for (int t = 0; t < half; ++t) {
+          const float own = up ? kr[t + half] : kr[t], send = up ? kr[t] : kr[t + half];
+          kr[t] = own + __shfl_xor(send, m, 64);
+        }
       }
+#pragma unroll
+      for (int t = 0; t < D / 64; ++t) wred[wave * D + lane * (D / 64) + t] = kr[t];
       __syncthreads();
-      for (int t = threadIdx.x; t < D; t += 256)
-        kpart[(u * nkb_max + kb) * D + t] = wred[t] + wred[D + t] + wred[2 * D + t] + wred[3 * D + t];
+      for (int t = threadIdx.x; t < D; t += KB) {
+        float x = wred[t];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) x += wred[w * D + t];
+        kpart[(u * nkb_max + kb) * D + t] = x;
+      }
     }
   }
 }
@@ -1007,7 +1079,7 @@ size_t score_smem_bytes(const Geo& g, int32_t dtype) {
     const size_t red = nw * (Mp * 2 > (size_t)g.D ? Mp * 2 : (size_t)g.D) * 4;
     return (q > red ? q : red) + Mp * 8;
   }
-  return (size_t)M * g.D * 4 + (size_t)M * 4 + 8 * 4 + (size_t)4 * g.D * 4;
+  return (size_t)M * g.D * 4 + (size_t)M * 4 + 2 * kF32Rows * 4 * 4 + (size_t)4 * g.D * 4;
 }
 
 template <int D, int NQT>
@@ -1095,8 +1167,11 @@ static certkv_status launch_mfma(const ScoreArgs& a, const SeqTab& st, hipStream
 template <int D>
 static certkv_status launch_f32(const ScoreArgs& a, const SeqTab& st, int max_len, hipStream_t s) {
   const Geo& g = a.g;
-  const int nkb = (max_len + 255) / 256;
-  dim3 grid(nkb, g.H * st.count, g.L);
+  const int nkb = (max_len + 255) / 256, M = g.w * g.G;
+  const int64_t wgs = (int64_t)nkb * g.H * st.count * g.L;
+  int rsplit = 1;  // up to four pass-1 workgroups per compute unit, of kF32Rows rows or more
+  while (rsplit * kF32Rows < M && 2 * rsplit * wgs <= 4 * 256) rsplit *= 2;
+  dim3 grid(nkb * rsplit, g.H * st.count, g.L);
   size_t smem = score_smem_bytes(g, CERTKV_F32);
   const float* q = static_cast<const float*>(a.q.ptr);
   const float* k = static_cast<const float*>(a.k.ptr);
@@ -1104,19 +1179,26 @@ static certkv_status launch_f32(const ScoreArgs& a, const SeqTab& st, int max_le
     CERTKV_LAUNCH("score_lse_import", lse_io_kernel<true>, dim3(g.H * st.count, g.L), dim3(256), 0,
                   s, g, st, a.lse_in, a.lse2, (float*)nullptr);
   } else {
-    CERTKV_LAUNCH("score_pass1_f32", (score_f32_kernel<D, false>), grid, dim3(256), smem, s, g, st,
-                  q, a.q.s_layer, a.q.s_token, a.q.s_head, k, a.k.s_layer, a.k.s_token, a.k.s_head,
-                  a.nkb_max, a.part, (const float*)nullptr, (float*)nullptr, (float*)nullptr);
+    CERTKV_LAUNCH("score_pass1_f32", (score_f32_kernel<D, false, 256>), grid, dim3(256), smem, s, g,
+                  st, q, a.q.s_layer, a.q.s_token, a.q.s_head, k, a.k.s_layer, a.k.s_token,
+                  a.k.s_head, a.nkb_max, rsplit, a.part, (const float*)nullptr, (float*)nullptr, (float*)nullptr);
     CERTKV_LAUNCH("score_lse_combine", lse_combine_kernel<false>, dim3(g.H * st.count, g.L),
                   dim3(256), 0, s, g, st, 256, a.nkb_max, (const float2*)a.part, a.lse2, a.flag, 0);
   }
-  CERTKV_LAUNCH("score_pass2_f32", (score_f32_kernel<D, true>), grid, dim3(256), smem, s, g, st, q,
-                a.q.s_layer, a.q.s_token, a.q.s_head, k, a.k.s_layer, a.k.s_token, a.k.s_head,
-                a.nkb_max, (float2*)nullptr, (const float*)a.lse2, a.scores,
-                a.ksum ? a.kpart : (float*)nullptr);
+  auto pass2 = [&](auto kernel, int keys) -> certkv_status {
+    CERTKV_LAUNCH("score_pass2_f32", kernel,
+                  dim3((max_len + keys - 1) / keys, g.H * st.count, g.L), dim3(keys), smem, s, g, st,
+                  q, a.q.s_layer, a.q.s_token, a.q.s_head, k, a.k.s_layer, a.k.s_token, a.k.s_head,
+                  a.nkb2_max, 1, (float2*)nullptr, (const float*)a.lse2, a.scores,
+                  a.ksum ? a.kpart : (float*)nullptr);
+    return CERTKV_OK;
+  };
+  const certkv_status rc = a.keys_per_block2 == 64 ? pass2(score_f32_kernel<D, true, 64>, 64)
+                                                   : pass2(score_f32_kernel<D, true, 256>, 256);
+  if (rc != CERTKV_OK) return rc;
   if (a.ksum)
     CERTKV_LAUNCH("score_ksum_reduce", ksum_reduce_kernel, dim3(g.H * st.count, g.L), dim3(128), 0,
-                  s, g, st, 256, a.nkb_max, (const float*)a.kpart, a.ksum);
+                  s, g, st, a.keys_per_block2, a.nkb2_max, (const float*)a.kpart, a.ksum);
   if (a.lse_out)
     CERTKV_LAUNCH("score_lse_export", lse_io_kernel<false>, dim3(g.H * st.count, g.L), dim3(256), 0,
                   s, g, st, (const float*)nullptr, a.lse2, a.lse_out);

@@ -267,3 +267,42 @@ def test_decode_chunks(rows, dim, group, tq):
         assert ((got - ref).norm(dim=1) <= 1e-4 * ref.norm(dim=1)).all(), u
         err = lse[0, u * tq:(u + 1) * tq].double().reshape(-1) - torch.logsumexp(z, 1)
         assert err.abs().max() <= 1e-4
+
+
+@pytest.mark.parametrize("dim,group,window,lens,heads", [
+    (64, 1, 1, [1, 63], 2),              # one row, blocks of less than a wave
+    (64, 1, 16, [64, 65, 1024, 257], 4),
+    (64, 3, 7, [255, 256, 513], 3),      # rows no multiple of the rows per step
+    (128, 4, 30, [300, 129], 8),
+    (64, 4, 64, [8000, 4097, 9999], 8),  # four-wave blocks, rows not shared out
+])
+@pytest.mark.parametrize("causal", [True, False])
+def test_score_f32_blocks(dim, group, window, lens, heads, causal):
+    # fp32 scores, key sums and row log-sum-exps against fp64.  A dot product of
+    # dim fp32 terms is off by at most dim 2^-24 times the sum of its terms'
+    # magnitudes (under 0.01 here), far above what the sums add.
+    spec = ck.ProblemSpec(2, heads, group, dim, window, lens, torch.float32, causal=causal)
+    gen = torch.Generator().manual_seed(sum(lens))
+    q = torch.randn((2, len(lens) * window, heads * group, dim), generator=gen)
+    k = torch.randn((2, sum(lens), heads, dim), generator=gen)
+    got, ksum, lse = ck.score(spec, q.to(DEV), k.to(DEV), with_ksum=True, with_lse=True)
+    got, ksum, lse = got.cpu().double(), ksum.cpu(), lse.cpu().double()
+    given = ck.score(spec, q.to(DEV), k.to(DEV), lse_in=lse.float().to(DEV)).cpu().double()
+    t0 = 0
+    for b, n in enumerate(lens):
+        row = torch.arange(window * group)[:, None] // group
+        hide = torch.arange(n)[None] > n - window + row if causal else torch.zeros(1, n).bool()
+        for l in range(2):
+            for h in range(heads):
+                qh = q[l, b * window:(b + 1) * window, h * group:(h + 1) * group].double()
+                kh = k[l, t0:t0 + n, h].double()
+                z = (qh.reshape(-1, dim) @ kh.t() / dim ** 0.5).masked_fill(hide, -np.inf)
+                ref = torch.logsumexp(z, 1)
+                x = lse[l, b * window:(b + 1) * window, h * group:(h + 1) * group].reshape(-1)
+                assert (x - ref).abs().max() <= 2e-5
+                s = (z - ref[:, None]).exp().sum(0)
+                assert ((got[l, h, t0:t0 + n] - s).abs() <= 2e-5 * s + 1e-30).all()
+                assert ((given[l, h, t0:t0 + n] - s).abs() <= 4e-5 * s + 1e-30).all()
+                u = (l * len(lens) + b) * heads + h
+                assert ((ksum[u] - s @ kh).abs() <= 4e-5 * (s @ kh.abs())).all()
+        t0 += n
