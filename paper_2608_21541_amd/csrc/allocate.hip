@@ -900,12 +900,13 @@ __global__ __launch_bounds__(kAllocThreads) void allocate_hull_kernel(
           atomicMax((unsigned long long*)&fail_s[q], (unsigned long long)dkey(v));
       }
       __syncthreads();
-      // what is left: above every failure, up to the best
+      // what is left: above every failure and below the best (whose equals, a
+      // plateau of running maxima, would only take up pivots)
       if (open && (tid & 511) < H) {
         const int h = tid & 511;
         int a = il[q][h], e = ir[q][h];
         if (fail_s[q] != 0ull) a = first_above(h, a, e, dval(fail_s[q]));
-        if (best_s[q] != ~0ull) e = first_above(h, a, e, dval(best_s[q]));
+        if (best_s[q] != ~0ull) e = first_not_below(h, a, e, dval(best_s[q]));
         il[q][h] = a;
         ir[q][h] = e;
       }
@@ -914,7 +915,7 @@ __global__ __launch_bounds__(kAllocThreads) void allocate_hull_kernel(
         bool more = false;
         if (stride > 1)
           for (int h = 0; h < H; ++h)
-            if (il[q][h] < ir[q][h] && dkey(pbm[h * nblk + il[q][h]]) < best_s[q]) more = true;
+            if (il[q][h] < ir[q][h]) more = true;
         open_s[q] = more ? 1 : 0;
       }
       __syncthreads();
@@ -1068,7 +1069,7 @@ __global__ __launch_bounds__(kAllocThreads) void allocate_hull_kernel(
         };
         int a = il[0][tid], e = ir[0][tid];
         if (fail_s[0] != 0ull) a = above(a, e, fail_s[0]);
-        if (best_s[0] != ~0ull) e = above(a, e, best_s[0]);
+        if (best_s[0] != ~0ull) e = above(a, e, best_s[0] - 1);  // not the best's equals
         il[0][tid] = a;
         ir[0][tid] = e;
       }
@@ -1077,7 +1078,7 @@ __global__ __launch_bounds__(kAllocThreads) void allocate_hull_kernel(
         bool more = false;
         if (stride > 1)
           for (int x = 0; x < ns; ++x)
-            if (il[0][x] < ir[0][x] && dkey(blk[x * kBlk + il[0][x]]) < best_s[0]) more = true;
+            if (il[0][x] < ir[0][x]) more = true;
         open_s[0] = more ? 1 : 0;
       }
       __syncthreads();
