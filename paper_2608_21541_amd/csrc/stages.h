@@ -134,8 +134,9 @@ struct TailArgs {
   uint64_t* bitmap;
   int32_t bm_stride;
   int32_t nsplit;            // gather workgroups per unit
+  int32_t nslice;            // mass workgroups per unit (standalone path)
   double* kpart;             // [U][nsplit][2][D] partial kept sums
-  double* mpart;             // [U][nsplit][3] partial masses (standalone path)
+  double* mpart;             // [U][nslice][3] partial masses (standalone path)
   const double* evicted_sum; // [U] from the selection pass, or NULL
   const double* total_sum;   // [U] from the selection pass, or NULL
   const double* ksum;

@@ -56,7 +56,9 @@ __global__ void bitmap_clear_kernel(uint64_t* __restrict__ bm, int64_t words) {
 
 // nsplit workgroups share a unit's kept entries: the atomics of one workgroup
 // per unit are a serial chain of round trips (two sequences of 65537 and 24001
-// keys, 8 heads: 247 us with one, 18 us with 33).
+// keys, 8 heads: 247 us with one).  The bits of one word that neighbouring
+// lanes set are joined first: up to 64 atomics to the same word wait for each
+// other (a head that keeps almost all of 65537: 30 us, joined 4).
 __global__ void bitmap_set_kernel(Geo g, SeqTab st, int32_t nsplit,
                                   const int64_t* __restrict__ kept_offsets,
                                   const int32_t* __restrict__ kept_idx, uint64_t* __restrict__ bm,
@@ -70,12 +72,25 @@ __global__ void bitmap_set_kernel(Geo g, SeqTab st, int32_t nsplit,
   const int n = st.len[bl];
   const int64_t u = unit_index(g, l, st.first + bl, h);
   const int64_t o0 = kept_offsets[u], o1 = kept_offsets[u + 1];
-  for (int64_t i = o0 + (int64_t)split * blockDim.x + threadIdx.x; i < o1;
-       i += (int64_t)nsplit * blockDim.x) {
-    const int j = kept_idx[i];
-    if (j >= 0 && j < n)
-      atomicOr(reinterpret_cast<unsigned long long*>(&bm[u * bm_stride + (j >> 6)]),
-               1ull << (j & 63));
+  const int lane = threadIdx.x & 63;
+  for (int64_t i0 = o0 + (int64_t)split * blockDim.x; i0 < o1; i0 += (int64_t)nsplit * blockDim.x) {
+    const int64_t i = i0 + threadIdx.x;
+    const int j = i < o1 ? kept_idx[i] : -1;
+    const bool ok = j >= 0 && j < n;
+    const int word = ok ? j >> 6 : -1;
+    unsigned long long bits = ok ? 1ull << (j & 63) : 0ull;
+    // each lane collects the bits of its word from the lanes that follow it
+    // without a break (in any order: joining a later run's bits as well sets
+    // no bit that is not to be set); the first lane of a run holds them all
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const unsigned long long y = __shfl_down(bits, o, 64);
+      const int w = __shfl_down(word, o, 64);
+      if (lane + o < 64 && w == word) bits |= y;
+    }
+    const int before = __shfl_up(word, 1, 64);
+    if (ok && (lane == 0 || before != word))
+      atomicOr(reinterpret_cast<unsigned long long*>(&bm[u * bm_stride + word]), bits);
   }
 }
 
@@ -131,7 +146,7 @@ struct TailMass {
   bool uniform;     // every score zero: uniform weights, masses are counts
   bool direct;      // the evicted rows are summed (else totals minus kept)
 };
-__device__ __forceinline__ TailMass tail_masses(int64_t u, int n, int nk, int nsplit, bool totals,
+__device__ __forceinline__ TailMass tail_masses(int64_t u, int n, int nk, int nslice, bool totals,
                                                 const double* evicted_sum, const double* total_sum,
                                                 const double* mpart) {
   TailMass t;
@@ -143,10 +158,10 @@ __device__ __forceinline__ TailMass tail_masses(int64_t u, int n, int nk, int ns
   } else {
     t.all = t.ev = nE = 0.0;
 #pragma unroll 8
-    for (int sp = 0; sp < nsplit; ++sp) {
-      t.all += mpart[(u * nsplit + sp) * 3 + 0];
-      t.ev += mpart[(u * nsplit + sp) * 3 + 1];
-      nE += mpart[(u * nsplit + sp) * 3 + 2];
+    for (int sp = 0; sp < nslice; ++sp) {
+      t.all += mpart[(u * nslice + sp) * 3 + 0];
+      t.ev += mpart[(u * nslice + sp) * 3 + 1];
+      nE += mpart[(u * nslice + sp) * 3 + 2];
     }
   }
   t.uniform = !(t.all > 0.0);
@@ -158,6 +173,21 @@ __device__ __forceinline__ TailMass tail_masses(int64_t u, int n, int nk, int ns
   return t;
 }
 
+// Kept rows of one split: the unit's rows in nsplit parts, none shorter than a
+// step of the gather, so that a unit of few rows takes few splits (and its
+// finalize reads few partials) while one that keeps almost every row of a
+// small launch uses them all.
+template <int D, typename T>
+struct GatherStep {
+  static constexpr int EPL = 16 / sizeof(T);      // elements per 16-byte lane chunk
+  static constexpr int LPR = D / EPL;             // lanes per row
+  static constexpr int RPS = kTailThreads / LPR;  // rows per load of the workgroup
+  static constexpr int UR = 4;                    // loads of a step
+  static __device__ __forceinline__ int rows(int nk, int nsplit) {
+    return max((nk + nsplit - 1) / nsplit, RPS * UR);
+  }
+};
+
 // Copy a slice of kept rows to the packed cache and/or accumulate the fp64
 // partial weighted key and value sums of the slice.  A direct unit's evicted
 // rows are read here, by every split, and not by the unit's one finalize
@@ -166,16 +196,15 @@ __device__ __forceinline__ TailMass tail_masses(int64_t u, int n, int nk, int ns
 // sums in the finalize kernel).
 template <int D, typename T, bool DO_TAIL, bool DO_COMPACT>
 __global__ __launch_bounds__(kTailThreads) void tail_gather_kernel(
-    Geo g, SeqTab st, int32_t nsplit, bool totals, const uint64_t* __restrict__ bm,
+    Geo g, SeqTab st, int32_t nsplit, int32_t nslice, bool totals, const uint64_t* __restrict__ bm,
     int32_t bm_stride, const double* __restrict__ mpart, const double* __restrict__ evicted_sum,
     const double* __restrict__ total_sum, const float* __restrict__ scores, const T* __restrict__ kc,
     int64_t k_sl, int64_t k_st, int64_t k_sh, const T* __restrict__ vc, int64_t v_sl,
     int64_t v_st, int64_t v_sh, const int64_t* __restrict__ kept_offsets,
     const int32_t* __restrict__ kept_idx, double* __restrict__ kpart_out,
     T* __restrict__ k_packed, T* __restrict__ v_packed, int32_t* __restrict__ pos_packed) {
-  constexpr int EPL = 16 / sizeof(T);      // elements per 16-byte lane chunk
-  constexpr int LPR = D / EPL;             // lanes per row
-  constexpr int RPS = kTailThreads / LPR;  // rows per workgroup step
+  using Step = GatherStep<D, T>;
+  constexpr int EPL = Step::EPL, LPR = Step::LPR, RPS = Step::RPS;
   __shared__ double redk[DO_TAIL ? RPS : 1][D];
   __shared__ double redv[DO_TAIL ? RPS : 1][D];
   __shared__ int32_t lpos[DO_TAIL ? kListTile : 1];   // a direct unit's evicted positions
@@ -197,7 +226,7 @@ __global__ __launch_bounds__(kTailThreads) void tail_gather_kernel(
   const int ri = tid / LPR, ci = tid % LPR;
   const int64_t off = kept_offsets[u];
   const int nk = (int)(kept_offsets[u + 1] - off);
-  const int per = (nk + nsplit - 1) / nsplit;
+  const int per = Step::rows(nk, nsplit);
   const int i0 = split * per, i1 = min(nk, i0 + per);
   const int64_t poff = off + g.slot * u;  // packed segment start
   const T* kb = kc + (int64_t)l * k_sl + tok0 * k_st + (int64_t)h * k_sh;
@@ -208,13 +237,14 @@ __global__ __launch_bounds__(kTailThreads) void tail_gather_kernel(
   for (int e = 0; e < EPL; ++e) ak[e] = av[e] = 0.0;
   // Four rows per lane group per step: their indices, then their rows and
   // scores, are loaded together so that each step waits for two round trips.
-  constexpr int UR = 4;
+  constexpr int UR = Step::UR;
   bool direct = false, uniform = false;
   if (DO_TAIL) {
-    const TailMass tm = tail_masses(u, n, nk, nsplit, totals, evicted_sum, total_sum, mpart);
+    const TailMass tm = tail_masses(u, n, nk, nslice, totals, evicted_sum, total_sum, mpart);
     direct = tm.direct;
     uniform = tm.uniform;
   }
+  if (!direct && i0 >= i1) return;  // (the whole workgroup; the finalize skips its partial)
   if (DO_TAIL && direct) {
     // The evicted positions of this split's slice that carry weight, listed in
     // position order a tile at a time (a ballot per round and wave, then the
@@ -338,7 +368,7 @@ __global__ __launch_bounds__(kTailThreads) void tail_gather_kernel(
 // Per unit: combine partials, form the slot, append it to the packed cache.
 template <int D, typename T, bool DO_TAIL, bool DO_COMPACT>
 __global__ __launch_bounds__(kTailThreads) void tail_finalize_kernel(
-    Geo g, SeqTab st, int32_t nsplit, const int64_t* __restrict__ kept_offsets,
+    Geo g, SeqTab st, int32_t nsplit, int32_t nslice, const int64_t* __restrict__ kept_offsets,
     const double* __restrict__ kpart, const double* __restrict__ mpart,
     const double* __restrict__ evicted_sum, const double* __restrict__ total_sum,
     const double* __restrict__ ksum, const double* __restrict__ vsum, float* __restrict__ k_star,
@@ -358,22 +388,25 @@ __global__ __launch_bounds__(kTailThreads) void tail_finalize_kernel(
   const int nk = (int)(kept_offsets[u + 1] - off);
 
   if (DO_TAIL) {
-    const TailMass tm = tail_masses(u, n, nk, nsplit, ksum && vsum, evicted_sum, total_sum, mpart);
-    for (int d = tid; d < D; d += kTailThreads) {
-      double sk = 0.0, sv = 0.0;
-      // partials added in split order; unrolled so that the loads of 16
-      // splits are in flight together
-#pragma unroll 16
-      for (int sp = 0; sp < nsplit; ++sp) {
-        sk += kpart[((u * nsplit + sp) * 2 + 0) * D + d];
-        sv += kpart[((u * nsplit + sp) * 2 + 1) * D + d];
+    const TailMass tm = tail_masses(u, n, nk, nslice, ksum && vsum, evicted_sum, total_sum, mpart);
+    const int per = GatherStep<D, T>::rows(nk, nsplit);
+    const int used = tm.direct ? nsplit : (nk + per - 1) / per;  // the partials that were written
+    for (int x = tid; x < 2 * D; x += kTailThreads) {
+      // x: a key dimension, or D + a value dimension
+      double sum = 0.0;
+      // partials added in split order, the loads of 32 splits in flight together
+      // (those past the last read it again and are not added)
+      for (int s0 = 0; s0 < used; s0 += 32) {
+        double y[32];
+#pragma unroll
+        for (int i = 0; i < 32; ++i)
+          y[i] = kpart[(u * nsplit + min(s0 + i, used - 1)) * 2 * D + x];
+#pragma unroll
+        for (int i = 0; i < 32; ++i) sum += s0 + i < used ? y[i] : 0.0;
       }
-      if (!tm.direct) {
-        sk = ksum[u * D + d] - sk;
-        sv = vsum[u * D + d] - sv;
-      }
-      slot_k[d] = tm.ev > 0.0 ? (float)(sk / tm.ev) : 0.f;
-      slot_v[d] = tm.ev > 0.0 ? (float)(sv / tm.ev) : 0.f;
+      const int d = x < D ? x : x - D;
+      if (!tm.direct) sum = (x < D ? ksum : vsum)[u * D + d] - sum;
+      (x < D ? slot_k : slot_v)[d] = tm.ev > 0.0 ? (float)(sum / tm.ev) : 0.f;
     }
     __syncthreads();
     for (int d = tid; d < D; d += kTailThreads) {
@@ -402,21 +435,22 @@ template <int D, typename T, bool DT, bool DC>
 static certkv_status launch_tail(const TailArgs& a, const SeqTab& st, hipStream_t s) {
   const Geo& g = a.g;
   const dim3 grid_split(g.H * st.count * a.nsplit, g.L);
+  const dim3 grid_slice(g.H * st.count * a.nslice, g.L);
   const dim3 grid_unit(g.H * st.count, g.L);
   const char* gname = DT ? (DC ? "tail_compact_gather" : "tail_gather") : "compact_gather";
   const char* fname = DT ? (DC ? "tail_compact_finalize" : "tail_finalize") : "compact_slot";
   if (DT && !(a.evicted_sum && a.total_sum))
-    CERTKV_LAUNCH("tail_mass", mass_kernel, grid_split, dim3(kTailThreads), 0, s, g, st, a.nsplit,
+    CERTKV_LAUNCH("tail_mass", mass_kernel, grid_slice, dim3(kTailThreads), 0, s, g, st, a.nslice,
                   a.scores, (const uint64_t*)a.bitmap, a.bm_stride, a.mpart);
   CERTKV_LAUNCH(gname, (tail_gather_kernel<D, T, DT, DC>), grid_split, dim3(kTailThreads), 0, s, g,
-                st, a.nsplit, a.ksum && a.vsum, (const uint64_t*)a.bitmap, a.bm_stride,
+                st, a.nsplit, a.nslice, a.ksum && a.vsum, (const uint64_t*)a.bitmap, a.bm_stride,
                 (const double*)a.mpart, a.evicted_sum, a.total_sum, a.scores,
                 static_cast<const T*>(a.k.ptr), a.k.s_layer, a.k.s_token, a.k.s_head,
                 static_cast<const T*>(a.v.ptr), a.v.s_layer, a.v.s_token, a.v.s_head,
                 a.kept_offsets, a.kept_idx, a.kpart, static_cast<T*>(a.k_packed),
                 static_cast<T*>(a.v_packed), a.pos_packed);
   CERTKV_LAUNCH(fname, (tail_finalize_kernel<D, T, DT, DC>), grid_unit, dim3(kTailThreads), 0, s, g,
-                st, a.nsplit, a.kept_offsets, (const double*)a.kpart, (const double*)a.mpart,
+                st, a.nsplit, a.nslice, a.kept_offsets, (const double*)a.kpart, (const double*)a.mpart,
                 a.evicted_sum, a.total_sum, a.ksum, a.vsum, a.k_star, a.v_star, a.tail_mass,
                 static_cast<T*>(a.k_packed), static_cast<T*>(a.v_packed), a.pos_packed);
   return CERTKV_OK;

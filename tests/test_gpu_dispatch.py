@@ -306,3 +306,76 @@ def test_score_f32_blocks(dim, group, window, lens, heads, causal):
                 u = (l * len(lens) + b) * heads + h
                 assert ((ksum[u] - s @ kh).abs() <= 4e-5 * (s @ kh.abs())).all()
         t0 += n
+
+
+@pytest.mark.parametrize("name,lens", [("C2", [255, 256, 4097, 20001]), ("C1", [63, 300, 9000])])
+def test_gather_splits(name, lens):
+    # Kept rows shared out over a unit's splits: none, one, part of a step, a
+    # step and a row, and all but one, with the totals given (evicted = totals
+    # - kept).  Packed rows are copies.
+    # The slot: fp64 sums of n terms in another order, rounded once to fp32;
+    # totals minus kept loses the kept share (at most a factor 64 by the rule
+    # that sums the evicted rows directly beyond it).
+    cfg = synth.config(name, seqlens=lens)
+    cache = synth.make_cache(cfg, "cpu")
+    spec, H = spec_of(cfg), cfg.kv_heads
+    s = _scores((1, H, sum(lens)), 12)
+    k, v = cache["k"], cache["v"]
+    bud, ksum, vsum, t0 = [], [], [], 0
+    for n in lens:
+        for h in range(H):
+            bud.append([0, 1, min(n, 33), min(n, 129), n // 3, n - 1, n // 50, n // 10][h % 8])
+            w = torch.from_numpy(s[0, h, t0:t0 + n]).double()
+            ksum.append(w @ k[0, t0:t0 + n, h].double())
+            vsum.append(w @ v[0, t0:t0 + n, h].double())
+        t0 += n
+    st, kd, vd = torch.from_numpy(s).to(DEV), k.to(DEV), v.to(DEV)
+    _, off, idx = ck.select(spec, st, torch.tensor(bud, dtype=torch.int32, device=DEV))
+    ks, vs, mass = ck.tail_summary(spec, st, kd, vd, off, idx, torch.stack(ksum).to(DEV),
+                                   torch.stack(vsum).to(DEV))
+    kp, vp, pos, po = ck.compact(spec, kd, vd, off, idx, ks, vs)
+    off, po, idx, pos, kp, vp = off.tolist(), po.tolist(), idx.cpu(), pos.cpu(), kp.cpu(), vp.cpu()
+    t0 = u = 0
+    for b, n in enumerate(lens):
+        for h in range(H):
+            rows = idx[off[u]:off[u + 1]].long()
+            p = po[u]
+            assert torch.equal(pos[p:p + len(rows)].long(), rows)
+            w = torch.from_numpy(s[0, h, t0:t0 + n]).double()
+            tot = w.sum()
+            w[rows] = 0.0
+            assert abs(mass[u].item() - (w.sum() / tot).item()) <= 1e-12
+            for got, packed, x in ((ks, kp, k), (vs, vp, v)):
+                x = x[0, t0:t0 + n, h]
+                assert torch.equal(packed[p:p + len(rows)], x[rows])
+                assert torch.equal(packed[p + len(rows)], got[u].cpu().to(x.dtype))
+                z = max(w.sum().item(), 1e-300)  # (nothing evicted: a zero slot)
+                ref, scale = w @ x.double() / z, w @ x.double().abs() / z
+                assert ((got[u].cpu().double() - ref).abs()
+                        <= 2.0 ** -24 * ref.abs() + 64 * n * 2.0 ** -52 * scale + 1e-300).all(), u
+            u += 1
+        t0 += n
+
+
+def test_kept_bitmap_of_unordered_positions():
+    # Kept positions of a caller's own, not ascending, repeated or out of range:
+    # the evicted mass is that of the positions in none of them.
+    n, H = 700, 4
+    spec = ck.ProblemSpec(1, H, 1, 64, 16, [n], torch.float32)
+    gen = torch.Generator().manual_seed(2)
+    idx = torch.stack([torch.randperm(n, generator=gen)[:300], torch.arange(300).flip(0),
+                       torch.arange(300) // 3 * 5 % n,
+                       torch.arange(300) % 2 * 64 + torch.arange(300) % 7]).int()
+    idx[3, 5] = -1
+    idx[3, 6] = n
+    s = torch.rand((1, H, n), generator=gen) + 0.5
+    k = torch.randn((1, n, H, 64), generator=gen)
+    off = torch.arange(H + 1, dtype=torch.int64) * 300
+    _, _, mass = ck.tail_summary(spec, s.to(DEV), k.to(DEV), k.to(DEV), off.to(DEV),
+                                 idx.reshape(-1).to(DEV))
+    for h in range(H):
+        w = s[0, h].double()
+        tot = w.sum()
+        ok = idx[h][(idx[h] >= 0) & (idx[h] < n)].long()
+        w[ok] = 0.0
+        assert abs(mass[h].item() - (w.sum() / tot).item()) <= 1e-12
