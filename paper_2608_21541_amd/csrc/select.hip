@@ -2,12 +2,12 @@
 //
 // The top-b keys of a unit (score descending, ties by position) are exactly
 // the keys whose (radix key, position) pair is lexicographically <= the pair
-// at rank b-1 of the sort.  One workgroup streams the unit's scores in
-// position order (4096 positions per step, 4 consecutive per thread), tests
-// each key against that threshold, and compacts the kept positions with wave
-// ballots and a prefix over the 16 waves, so kept indices come out ascending
-// without a scatter.  The same pass sums (s)_+ over the evicted
-// keys and over all keys in fp64 (the tail mass and its normalizer).
+// at rank b-1 of the sort.  A workgroup streams its part of the unit's scores in
+// position order (tiles of 8192 positions), tests each key against that
+// threshold, and compacts the kept positions with wave ballots and a prefix over
+// the 16 waves, so kept indices come out ascending without a scatter.  The same
+// pass sums (s)_+ over the evicted keys and over all keys in fp64 (the tail mass
+// and its normalizer).
 #include "stages.h"
 
 namespace certkv {
@@ -68,20 +68,35 @@ constexpr int kSelThreads = 1024;
 constexpr int kSelWaves = kSelThreads / 64;
 constexpr int kSelRounds = 8;                     // rounds of 1024 consecutive positions
 constexpr int kSelTile = kSelThreads * kSelRounds; // 8192 positions per iteration
+// Parts of a unit of n positions.
+__host__ __device__ inline int sel_parts(int n, int part_tiles) {
+  const int tiles = (int)(((int64_t)n + kSelTile - 1) / kSelTile);
+  return (tiles + part_tiles - 1) / part_tiles;
+}
 constexpr int kSelScanPer = kSelRounds * kSelWaves / 64;  // counts per lane of the scan
 
+// One workgroup per part of a unit: part_tiles tiles, or the whole unit.  Tile
+// after tile with two barriers each, a long unit is a serial chain (4 us a
+// tile); a part instead counts the kept keys before it by itself, from scores
+// that the L2 holds, which needs no barrier and no exchange between workgroups.
+// The last part meets every score that way, in the order and on the threads of
+// a workgroup that walks the whole unit, and forms the sums.  Whole units and parts: 8 of 32768 positions
+// 19 and 15 us, 64 of 8192 to 65536 34 and 26, 24 of 9999 to 30001 without sums
+// 18 and 14.
 __global__ __launch_bounds__(kSelThreads) void select_kernel(
-    Geo g, SeqTab st, const float* __restrict__ scores, const uint32_t* __restrict__ sorted_keys,
-    const int32_t* __restrict__ perm, const int32_t* __restrict__ budgets,
-    const int64_t* __restrict__ kept_offsets, int32_t* __restrict__ kept_idx, int64_t capacity,
+    Geo g, SeqTab st, int32_t part_tiles, const float* __restrict__ scores,
+    const uint32_t* __restrict__ sorted_keys, const int32_t* __restrict__ perm,
+    const int32_t* __restrict__ budgets, const int64_t* __restrict__ kept_offsets,
+    int32_t* __restrict__ kept_idx, int64_t capacity,
     double* __restrict__ evicted_sum, double* __restrict__ total_sum, uint64_t* __restrict__ bm,
     int32_t bm_stride, uint8_t* __restrict__ mask) {
   // kept counts of each (round, wave) of a tile, then their exclusive prefix
   // in position order (round-major); the tile's total at the end
   __shared__ uint32_t kcnt[kSelRounds * kSelWaves + 1];
   __shared__ double dsum[2][kSelWaves];
-  const int h = blockIdx.x % g.H;
-  const int bl = blockIdx.x / g.H;
+  int h, part;
+  const int bl = locate_part(g, st, blockIdx.x,
+                             [&](int x) { return sel_parts(st.len[x], part_tiles); }, h, part);
   const int l = blockIdx.y;
   if (bl >= st.count) return;
   const int b = st.first + bl;
@@ -112,9 +127,44 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
       sv[r] = __uint_as_float(
           buf_load_u32(srs, (uint32_t)(j0 + r * kSelThreads + (int)threadIdx.x) * 4u));
   };
+  // kept window keys hold ranks 0..w-1 in position order; the others are kept up
+  // to the threshold pair at rank bb-1
+  auto keeps = [&](int j, float x) -> bool {
+    const uint32_t key = desc_key(x);
+    return j < n && (j >= wkeep ? (j - wkeep < bb)
+                                : (bb > g.keep_w && (key < kthr || (key == kthr && j <= ithr))));
+  };
+  const int start = (int)min((int64_t)part * part_tiles * kSelTile, (int64_t)n);
+  const int end = (int)min((int64_t)(part + 1) * part_tiles * kSelTile, (int64_t)n);
+  const bool sums = end == n && evicted_sum;  // the unit's last part
   float cur[kSelRounds], nxt[kSelRounds];
-  load(0, cur);
-  for (int j0 = 0; j0 < n; j0 += kSelTile) {
+  load(start, cur);
+  if (start > 0) {
+    uint32_t before = 0;
+    float x[kSelRounds], y[kSelRounds];
+    load(0, x);
+    for (int j0 = 0; j0 < start; j0 += kSelTile) {
+      load(j0 + kSelTile, y);  // (of the part itself, unused, after the last tile)
+#pragma unroll
+      for (int r = 0; r < kSelRounds; ++r) {
+        const bool keep = keeps(j0 + r * kSelThreads + (int)threadIdx.x, x[r]);
+        before += keep ? 1u : 0u;
+        if (sums) {
+          const double sp = x[r] > 0.f ? (double)x[r] : 0.0;
+          sa += sp;
+          se += keep ? 0.0 : sp;
+        }
+      }
+#pragma unroll
+      for (int r = 0; r < kSelRounds; ++r) x[r] = y[r];
+    }
+    const uint32_t c = wave_sum(before);
+    if (lane == 0) kcnt[wave] = c;
+    __syncthreads();
+    for (int w = 0; w < kSelWaves; ++w) run += kcnt[w];
+    __syncthreads();
+  }
+  for (int j0 = start; j0 < end; j0 += kSelTile) {
     load(j0 + kSelTile, nxt);
     uint32_t kmask = 0;
     uint64_t bal[kSelRounds];  // wave-uniform: scalar registers
@@ -122,14 +172,12 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
     for (int r = 0; r < kSelRounds; ++r) {
       const int j = j0 + r * kSelThreads + (int)threadIdx.x;
       const bool valid = j < n;
-      const uint32_t key = desc_key(cur[r]);
-      // kept window keys hold ranks 0..w-1 in position order; the others
-      // are kept up to the threshold pair at rank bb-1
-      const bool keep = valid && (j >= wkeep ? (j - wkeep < bb)
-                                             : (bb > g.keep_w && (key < kthr || (key == kthr && j <= ithr))));
-      const double sp = (valid && cur[r] > 0.f) ? (double)cur[r] : 0.0;
-      sa += sp;
-      se += keep ? 0.0 : sp;
+      const bool keep = keeps(j, cur[r]);
+      if (sums) {
+        const double sp = (valid && cur[r] > 0.f) ? (double)cur[r] : 0.0;
+        sa += sp;
+        se += keep ? 0.0 : sp;
+      }
       bal[r] = __ballot(keep);
       if (mask && valid) mask[base + j] = keep ? 1 : 0;  // 64 consecutive bytes per wave
       kmask |= (uint32_t)keep << r;
@@ -177,6 +225,7 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
 #pragma unroll
     for (int r = 0; r < kSelRounds; ++r) cur[r] = nxt[r];
   }
+  if (!sums) return;
   se = wave_sum(se);
   sa = wave_sum(sa);
   if (lane == 0) {
@@ -190,8 +239,8 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
       e += dsum[0][w];
       t += dsum[1][w];
     }
-    if (evicted_sum) evicted_sum[u] = e;
-    if (total_sum) total_sum[u] = t;
+    evicted_sum[u] = e;
+    total_sum[u] = t;
   }
 }
 
@@ -448,7 +497,19 @@ certkv_status run_uniform_budgets(const Geo& g, const SeqTab& st, int32_t* budge
 }
 
 certkv_status run_select(const SelectArgs& a, const SeqTab& st, hipStream_t s) {
-  CERTKV_LAUNCH("select", select_kernel, dim3(a.g.H * st.count, a.g.L), dim3(kSelThreads), 0, s, a.g, st,
+  // The smallest parts that start together (two workgroups to a compute unit);
+  // with a unit per compute unit none is split.
+  int part_tiles = 1 << 18;  // n < 2^31
+  if ((int64_t)a.g.L * a.g.H * st.count < 256) {
+    part_tiles = 1;
+    auto wgs = [&](int t) {
+      return (int64_t)a.g.L * count_parts(a.g, st, [&](int bl) { return sel_parts(st.len[bl], t); });
+    };
+    while (wgs(part_tiles) > 512) part_tiles *= 2;
+  }
+  const dim3 grid(count_parts(a.g, st, [&](int bl) { return sel_parts(st.len[bl], part_tiles); }),
+                  a.g.L);
+  CERTKV_LAUNCH("select", select_kernel, grid, dim3(kSelThreads), 0, s, a.g, st, part_tiles,
                 a.scores, a.sorted_keys, a.perm, (const int32_t*)a.budgets,
                 (const int64_t*)a.kept_offsets, a.kept_idx, a.capacity, a.evicted_sum, a.total_sum,
                 a.bitmap, a.bm_stride, a.mask);

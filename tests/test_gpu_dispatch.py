@@ -379,3 +379,38 @@ def test_kept_bitmap_of_unordered_positions():
         ok = idx[h][(idx[h] >= 0) & (idx[h] < n)].long()
         w[ok] = 0.0
         assert abs(mass[h].item() - (w.sum() / tot).item()) <= 1e-12
+
+
+@pytest.mark.parametrize("lens,heads,layers", [
+    ([8192, 8191, 1], 4, 1), ([8193, 40960, 24577], 4, 1),  # parts of one tile, and their edges
+    ([65537, 9000], 8, 6),                                  # parts of several
+    ([16400], 8, 32),                                       # a unit per compute unit: not split
+])
+@pytest.mark.parametrize("keep_window", [False, True])
+def test_select_parts(lens, heads, layers, keep_window):
+    # Kept positions and masks of budgets from none to all against the order.
+    rng = np.random.default_rng(len(lens))
+    w = 1 if min(lens) < 16 else 16
+    spec = ck.ProblemSpec(layers, heads, 1, 64, w, lens, torch.float32, keep_window=keep_window)
+    s = np.round(_scores((layers, heads, sum(lens)), 9) * 64) / 64  # ties across parts
+    bud = np.array([[[rng.integers(0, n + 1) for _ in range(heads)] for n in lens]
+                    for _ in range(layers)], np.int32)
+    bud[0, :, 0], bud[0, :, 1] = 0, lens
+    got, off, idx, mask = ck.select(spec, torch.from_numpy(s).to(DEV),
+                                    torch.from_numpy(bud.reshape(-1)).to(DEV), with_mask=True)
+    off, idx, mask = off.tolist(), idx.cpu().numpy(), mask.cpu().numpy()
+    u, step = 0, 1 if layers < 10 else 7
+    for l in range(layers):
+        t0 = 0
+        for b, n in enumerate(lens):
+            for h in range(heads):
+                assert off[u + 1] - off[u] == bud[l, b, h]
+                if u % step == 0:
+                    perm = oracle.order(s[l, h, t0:t0 + n], keep_window=w if keep_window else 0)
+                    kept = np.sort(perm[:bud[l, b, h]])
+                    assert np.array_equal(idx[off[u]:off[u + 1]], kept), (l, b, h)
+                    ref = np.zeros(n, np.uint8)
+                    ref[kept] = 1
+                    assert np.array_equal(mask[l, h, t0:t0 + n], ref)
+                u += 1
+            t0 += n
