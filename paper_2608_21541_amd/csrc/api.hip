@@ -826,25 +826,24 @@ static int decode_rows_bound(const Plan& P, int32_t max_rows) {
   return (max_rows > 0 && max_rows < P.max_len) ? max_rows : P.max_len;
 }
 
-// Decode workspace: split partials (output rows, then (max, sum) pairs), the
-// work-item list and its length, each 256-byte aligned.
+// Decode workspace: split partials (output rows, then (max, sum) pairs), each
+// 256-byte aligned.
 struct DecodeWs {
   int keys_min;
   int64_t cover;
   int nsplit;
-  size_t ml_off, items_off, count_off, total;
+  size_t ml_off, total;
 };
 static DecodeWs decode_ws_layout(const Plan& P, int32_t tq, int32_t max_rows) {
   auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
   DecodeWs w;
   w.keys_min = decode_keys_min(P.U, P.max_len, tq, P.g.G);
   w.cover = decode_cover(decode_rows_bound(P, max_rows));
-  w.nsplit = (int)(w.cover / w.keys_min);
+  // (chunks are cut through the units: a unit's first and last may be partial)
+  w.nsplit = (int)(w.cover / w.keys_min) + 1;
   const size_t rows = decode_partial_rows(P.U, w.nsplit, tq, P.g.G);
   w.ml_off = up(rows * (size_t)P.g.D * sizeof(float));
-  w.items_off = up(w.ml_off + rows * sizeof(float2));
-  w.count_off = up(w.items_off + (size_t)P.U * w.nsplit * sizeof(int2));
-  w.total = w.count_off + 256;
+  w.total = up(w.ml_off + rows * sizeof(float2));
   return w;
 }
 
@@ -892,8 +891,6 @@ static certkv_status decode_impl(const certkv_problem* p, certkv_tensor q_new, i
   a.packed_offsets = packed_offsets;
   a.part_o = static_cast<float*>(ws);
   a.part_ml = reinterpret_cast<float2*>(static_cast<char*>(ws) + W.ml_off);
-  a.items = reinterpret_cast<int2*>(static_cast<char*>(ws) + W.items_off);
-  a.item_count = reinterpret_cast<int32_t*>(static_cast<char*>(ws) + W.count_off);
   a.cl = cl;
   a.out = out;
   a.lse = lse;

@@ -7,10 +7,10 @@
 // over the unit's packed segment:
 //   z_i = scale <q, k_i>,  out = sum_i softmax(z)_i v_i,  lse = log sum e^z.
 //
-// Split over keys: the work items are (unit, chunk) pairs, chunks of up to 4096
-// keys (dec_keys), taken in a fixed stride by a persistent grid of as many
-// workgroups as stay resident; a workgroup finds its item among the packed
-// offsets itself (up to kLocalUnits units) or in a list built on the device.  A workgroup holds the unit's query tiles of
+// Split over keys: the packed rows are cut into chunks of the same length
+// (dec_keys), taken in a fixed stride by a persistent grid of as many
+// workgroups as stay resident; a workgroup finds the units of its chunks in the
+// packed offsets.  A workgroup holds the unit's query tiles of
 // 32 rows, one wave each; with fewer than four tiles, two or four waves share
 // a tile and split its output dims.  Key and value tiles of 32 rows go from
 // memory straight into LDS (wave-wide 16-byte LDS-DMA loads into a ring of
@@ -32,7 +32,7 @@
 
 namespace certkv {
 
-constexpr int kDecKeys = 4096;    // keys per work item (one split) at most
+constexpr int kDecKeys = 4096;    // keys per chunk, as long as the workspace has slots
 constexpr int kDecKeysMin = 128;  // and at least
 constexpr int kDecTile = 32;    // keys per tile
 
@@ -103,9 +103,10 @@ __device__ __forceinline__ int dec_swz_v(int r, int c) {
 // as inline assembly so that the compiler does not treat the load as a
 // pending LDS write (which would make it wait for every load in flight at
 // each barrier); the caller waits for it with dec_wait_vm0 before the
-// barrier that publishes the stage.
+// barrier that publishes the stage.  Non-temporal: a row is read once per call
+// (32 layers, 3.36M rows, one query: 338 us without, 5.1 TB/s; 287 with).
 __device__ __forceinline__ void dec_dma16(const void* src, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt"
                :
                : "v"(src), "s"(__builtin_amdgcn_readfirstlane(lds))
                : "memory", "m0");
@@ -141,80 +142,59 @@ __device__ __forceinline__ uint32_t dec_lds_addr(const void* p) {
 typedef short dec_s16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) dec_s16x4 dec_lds_s16x4;
 
-// Keys per chunk: the same for every unit, a power of two in [keys_min, 4096],
-// from the packed rows alone.  Long chunks amortize the start of an item (its
-// queries, the first tiles' latency) and its partials; with few rows they leave
-// compute units idle, so chunks are halved while there would be fewer than 512
-// (the resident workgroups).  One layer of 8 heads at 32768 tokens, 26216 rows,
-// one query: 100 us in 4096-key chunks, 11 us in 128-key ones; all 32
-// layers at 131072 keep 4096.
-__device__ __forceinline__ int dec_keys(const int64_t* __restrict__ poff, int64_t U, int keys_min) {
-  const int64_t rows = poff[U] - poff[0];
-  int k = keys_min;
-  while (k < kDecKeys && (int64_t)k * 1024 <= rows) k *= 2;
-  return k;
+// Rows per chunk.  The packed rows of all units, one after another, are cut
+// into chunks of the same length, so that a workgroup's share does not depend
+// on how the rows are spread over the heads: a chunk that crosses from one unit
+// to the next is two pieces.  With chunks cut per unit the resident workgroups
+// got one or two of 4096 keys each, or less at a unit's end: 32 layers of 8
+// heads, 3.36M rows, one query 355 us, and 338 here (287 with the loads non-temporal);
+// 32 queries 449 and 377.
+// parts workgroups are resident at once and take the same number of chunks
+// each, of at most 4096 keys, or up to twice keys_min where the workspace has no
+// slots for shorter ones (long chunks amortize the queries' load, the first
+// tiles' latency and the partials, and bound how long the fp32 sums get).  Few
+// rows leave compute units idle in such chunks and take shorter ones, of
+// keys_min at least (one layer of 26216 rows: 100 us in 4096-key chunks, 11 us
+// in 128-key ones).
+__device__ __forceinline__ int dec_keys(int64_t rows, int keys_min, int parts) {
+  if (rows < (int64_t)parts * keys_min) return keys_min;
+  const int64_t rounds = min((rows + (int64_t)parts * kDecKeys - 1) / ((int64_t)parts * kDecKeys),
+                             rows / ((int64_t)parts * keys_min));  // both 1 or more
+  const int64_t k = (rows + parts * rounds - 1) / (parts * rounds);
+  return (int)((k + kDecTile - 1) / kDecTile) * kDecTile;
 }
 
-// The work items of a decode: every (unit, chunk) pair whose chunk starts
-// inside the unit's segment (at most cover rows of it), unit-major.  One
-// workgroup scans the per-unit chunk counts in rounds of kItemThreads units.
-constexpr int kItemThreads = 1024;
-__global__ __launch_bounds__(kItemThreads) void decode_items_kernel(
-    int64_t U, int64_t cover, int32_t keys_min, const int64_t* __restrict__ poff,
-    int2* __restrict__ items, int32_t* __restrict__ count) {
-  __shared__ int scan[kItemThreads];
-  const int t = threadIdx.x;
-  const int keys = dec_keys(poff, U, keys_min);
-  int base = 0;  // items of the earlier rounds
-  for (int64_t u0 = 0; u0 < U; u0 += kItemThreads) {
-    const int64_t u = u0 + t;
-    int n = 0;
-    if (u < U) n = (int)((min(cover, poff[u + 1] - poff[u]) + keys - 1) / keys);
-    scan[t] = n;
-    __syncthreads();
-    for (int d = 1; d < kItemThreads; d <<= 1) {  // inclusive scan
-      const int x = t >= d ? scan[t - d] : 0;
-      __syncthreads();
-      scan[t] += x;
-      __syncthreads();
-    }
-    const int start = base + scan[t] - n;
-    for (int k = 0; k < n; ++k) items[start + k] = make_int2((int)u, k);
-    base += scan[kItemThreads - 1];
-    __syncthreads();  // scan[] is rewritten by the next round
-  }
-  if (t == 0) {
-    count[0] = base;
-    count[1] = keys;
+// x of lane i (wave-uniform).
+__device__ __forceinline__ int64_t dec_readlane(int64_t x, int i) {
+  const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)x, i);
+  const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)((uint64_t)x >> 32), i);
+  return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+
+// Pieces of a unit whose len rows start at packed row p0.
+__device__ __forceinline__ int dec_pieces(int64_t p0, int64_t len, int keys) {
+  return len > 0 ? (int)((p0 + len - 1) / keys - p0 / keys) + 1 : 0;
+}
+
+// The unit that holds packed row r (counted from the first unit's), by a wave:
+// 64 units' ends per step.  U past the last row.
+__device__ __forceinline__ int dec_find_unit(const int64_t* __restrict__ poff, int U, int64_t r,
+                                             int lane) {
+  int lo = 0, n = U;  // the answer is one of [lo, lo + n]
+  while (true) {
+    const int step = (n + 63) / 64;
+    const int i = lo + lane * step + step - 1;
+    const bool past = i >= U || poff[i + 1] - poff[0] > r;  // unit i ends past r
+    lo += (int)__popcll(__ballot(!past)) * step;
+    if (step == 1) return min(lo, U);
+    n = step;
   }
 }
 
-// The same list without a launch of its own: item `item` of the list, found by
-// a wave from the offsets (a unit per lane); x = -1 past its end.  With more
-// units, or many items to a workgroup, the launch costs less than the searches
-// (256 units, three items each: 5 us in all, a launch 3 us).
-constexpr int kLocalUnits = 64;
-__device__ __forceinline__ int2 dec_find_item(const int64_t* __restrict__ poff, int U,
-                                              int64_t cover, int keys, int item, int lane) {
-  const int64_t len = poff[min(lane + 1, U)] - poff[min(lane, U)];
-  const int c = (int)((min(cover, len) + keys - 1) / keys);
-  int incl = c;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const int y = __shfl_up(incl, d, 64);
-    if (lane >= d) incl += y;
-  }
-  const uint64_t at = __ballot(item < incl && item >= incl - c);
-  if (at == 0) return make_int2(-1, 0);
-  const int u = (int)__builtin_ctzll(at);
-  return make_int2(u, item - __builtin_amdgcn_readlane(incl - c, u));
-}
-
-// LOCAL: the items are found from the offsets (else read from the list).
-template <int D, int NQT, bool LOCAL>
+template <int D, int NQT>
 __device__ __forceinline__ void decode_body(
-    const Geo& g, int64_t U, int64_t cover, int32_t keys_min, const int2* __restrict__ items,
-    const int32_t* __restrict__ item_count, int32_t tq, int32_t nsplit, int32_t mp,
+    const Geo& g, int64_t U, int64_t cover, int32_t keys_min, int32_t parts, int32_t tq,
+    int32_t nsplit, int32_t mp,
     const uint16_t* __restrict__ qn, int64_t q_sl, int64_t q_st, int64_t q_sh,
     const uint16_t* __restrict__ kp, const uint16_t* __restrict__ vp,
     const int64_t* __restrict__ poff, float* __restrict__ part_o, float2* __restrict__ part_ml) {
@@ -231,32 +211,47 @@ __device__ __forceinline__ void decode_body(
   static_assert((NINS % NW == 0 || NINS < NW) && TILE_CH % 64 == 0, "stage split");
   __shared__ __align__(16) uint16_t lds[NBUF][2][TILE];
 
-  // A persistent grid over the work items (unit, chunk), taken in a fixed
-  // stride: consecutive chunks of a long segment go to different workgroups.
-  const int keys = LOCAL ? dec_keys(poff, U, keys_min) : item_count[1];
-  const int nitems = LOCAL ? 0x7fffffff : item_count[0];
-  for (int item = blockIdx.x; item < nitems; item += gridDim.x) {
-  int2 it;
-  if constexpr (LOCAL) {
-    it = dec_find_item(poff, (int)U, cover, keys, item, threadIdx.x & 63);
-    if (it.x < 0) break;  // whole workgroup: past the last item
-  } else {
-    it = items[item];
+  // A persistent grid over the chunks, and in each over the units it meets.
+  // Up to 64 units: their segments in the lanes of every wave, so that a piece
+  // waits for one load before its queries and tiles, not for three in turn.
+  const bool few = U <= 64;
+  const int lane = threadIdx.x & 63;
+  int64_t ps = 0, pe = 0;
+  if (few) {
+    ps = poff[min(lane, (int)U)];
+    pe = poff[min(lane + 1, (int)U)];
   }
-  const int64_t u = it.x;
-  const int split = it.y;
+  auto seg_start = [&](int64_t u) { return few ? dec_readlane(ps, (int)u) : poff[u]; };
+  auto seg_end = [&](int64_t u) { return few ? dec_readlane(pe, (int)u) : poff[u + 1]; };
+  const int64_t base = seg_start(0), rows = seg_end(U - 1) - base;
+  const int keys = dec_keys(rows, keys_min, parts);
+  // Where the grid has workgroups left for the units' first pieces, those that
+  // start inside a chunk are theirs, and no workgroup takes two pieces in turn.
+  const int64_t nch = (rows + keys - 1) / keys;
+  const bool heads = nch + U - 1 <= gridDim.x;
+  for (int64_t x = blockIdx.x; x < (heads ? nch + U - 1 : nch); x += gridDim.x) {
+  const int64_t head = x - nch + 1;  // from 1: the unit whose first piece is taken
+  const int64_t r0 = x < nch ? x * keys : seg_start(head) - base;
+  const int64_t s = x < nch ? x : r0 / keys, r1 = min(rows, (s + 1) * keys);
+  if (x >= nch && r0 == s * keys) continue;  // a chunk's first piece
+  const uint64_t past = __ballot(pe - base > r0);
+  const int64_t u0 = x >= nch ? head
+                     : few    ? (past ? (int64_t)__builtin_ctzll(past) : U)
+                              : dec_find_unit(poff, (int)U, r0, lane);
+  for (int64_t u = u0; u < U; u = heads ? U : u + 1) {
+  const int64_t p0 = seg_start(u), at = p0 - base;  // the unit's first row, and from the first unit's
+  if (at >= r1) break;
+  const int len = (int)(seg_end(u) - p0);
+  const int c0 = (int)max(r0 - at, (int64_t)0);
+  const int c1 = (int)min(min(cover, (int64_t)len), r1 - at);
+  if (c0 >= c1) continue;  // whole workgroup: an empty unit, or rows past the caller's bound
+  const int split = (int)(s - at / keys);
   const int h = (int)(u % g.H);
   const int64_t lb = u / g.H;
   const int b = (int)(lb % g.B);
   const int l = (int)(lb / g.B);
-  const int64_t p0 = poff[u];
-  const int len = (int)(poff[u + 1] - p0);
-  const int c0 = split * keys;
-  if (c0 >= len) continue;  // whole workgroup: this unit has fewer chunks
-  const int c1 = min(len, c0 + keys);
   const int ntiles = (c1 - c0 + kDecTile - 1) / kDecTile;
   const int M = tq * g.G;
-  const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int qt = wave % NQT;        // query tile of this wave
   const int dsi = wave / NQT;       // its share of the output dims
@@ -433,27 +428,22 @@ __device__ __forceinline__ void decode_body(
 #pragma unroll
     for (int v = 0; v < 16; ++v)
       po[32 * (db0 + db) + 8 * (v >> 2) + 4 * hh + (v & 3)] = O[db][v];
-  __syncthreads();  // every wave is done with the stage buffers of this item
+  __syncthreads();  // every wave is done with the stage buffers of this piece
+  }
   }
 }
 
 // Two waves per SIMD: the register cap keeps the accumulators out of AGPRs.
-#define CERTKV_DECODE_KERNEL(NAME, LOCAL)                                                          \
-  template <int D, int NQT>                                                                        \
-  __global__ __launch_bounds__((64 * DecShape<D, NQT>::NW))                                        \
-  __attribute__((amdgpu_waves_per_eu(2))) void NAME(                                               \
-      Geo g, int64_t U, int64_t cover, int32_t keys_min, const int2* __restrict__ items,           \
-      const int32_t* __restrict__ item_count, int32_t tq, int32_t nsplit, int32_t mp,              \
-      const uint16_t* __restrict__ qn, int64_t q_sl, int64_t q_st, int64_t q_sh,                   \
-      const uint16_t* __restrict__ kp, const uint16_t* __restrict__ vp,                            \
-      const int64_t* __restrict__ poff, float* __restrict__ part_o,                                \
-      float2* __restrict__ part_ml) {                                                              \
-    decode_body<D, NQT, LOCAL>(g, U, cover, keys_min, items, item_count, tq, nsplit, mp, qn, q_sl, \
-                               q_st, q_sh, kp, vp, poff, part_o, part_ml);                         \
-  }
-CERTKV_DECODE_KERNEL(decode_kernel, false)
-CERTKV_DECODE_KERNEL(decode_local_kernel, true)
-#undef CERTKV_DECODE_KERNEL
+template <int D, int NQT>
+__global__ __launch_bounds__((64 * DecShape<D, NQT>::NW))
+__attribute__((amdgpu_waves_per_eu(2))) void decode_kernel(
+    Geo g, int64_t U, int64_t cover, int32_t keys_min, int32_t parts, int32_t tq, int32_t nsplit,
+    int32_t mp, const uint16_t* __restrict__ qn, int64_t q_sl, int64_t q_st, int64_t q_sh,
+    const uint16_t* __restrict__ kp, const uint16_t* __restrict__ vp,
+    const int64_t* __restrict__ poff, float* __restrict__ part_o, float2* __restrict__ part_ml) {
+  decode_body<D, NQT>(g, U, cover, keys_min, parts, tq, nsplit, mp, qn, q_sl, q_st, q_sh, kp, vp,
+                      poff, part_o, part_ml);
+}
 
 // Combine the chunk partials of each (unit, row): one workgroup per row, the
 // partial slots dealt round-robin to groups of D/4 threads (four output dims
@@ -476,8 +466,8 @@ constexpr int kCombThreads = 256;
 // bound is infinite).
 template <int D, bool CL>
 __global__ __launch_bounds__(kCombThreads) void decode_combine_kernel(
-    Geo g, int64_t U, int64_t cover, int32_t keys_min, int32_t tq, int32_t nsplit, int32_t mp,
-    const int64_t* __restrict__ poff, const float* __restrict__ part_o,
+    Geo g, int64_t U, int64_t cover, int32_t keys_min, int32_t parts, int32_t tq, int32_t nsplit,
+    int32_t mp, const int64_t* __restrict__ poff, const float* __restrict__ part_o,
     const float2* __restrict__ part_ml, float* __restrict__ out, float* __restrict__ lse,
     DecodeClusters cl, const uint16_t* __restrict__ qn, int64_t q_sl,
     int64_t q_st, int64_t q_sh) {
@@ -493,8 +483,8 @@ __global__ __launch_bounds__(kCombThreads) void decode_combine_kernel(
   const int sg = threadIdx.x / C4;
   const int c4 = threadIdx.x % C4;
   const int len = (int)(poff[u + 1] - poff[u]);
-  const int keys = dec_keys(poff, U, keys_min);
-  const int nv = (int)((min(cover, (int64_t)len) + keys - 1) / keys);
+  const int nv = dec_pieces(poff[u] - poff[0], min(cover, (int64_t)len),
+                            dec_keys(poff[U] - poff[0], keys_min, parts));
   if (len > cover && row == 0 && threadIdx.x == 0) report_range(g);
   const int64_t base = (int64_t)u * nsplit * mp + row;  // + slot * mp
   float m = -INFINITY, L = 0.f;
@@ -637,8 +627,8 @@ __global__ __launch_bounds__(kCombThreads) void decode_combine_kernel(
 // many slots of one are better dealt to the workgroup.
 template <int D>
 __global__ __launch_bounds__(kCombThreads) void decode_combine_rows_kernel(
-    Geo g, int64_t U, int64_t cover, int32_t keys_min, int32_t tq, int32_t nsplit, int32_t mp,
-    const int64_t* __restrict__ poff, const float* __restrict__ part_o,
+    Geo g, int64_t U, int64_t cover, int32_t keys_min, int32_t parts, int32_t tq, int32_t nsplit,
+    int32_t mp, const int64_t* __restrict__ poff, const float* __restrict__ part_o,
     const float2* __restrict__ part_ml, float* __restrict__ out, float* __restrict__ lse) {
   constexpr int C4 = D / 4;
   constexpr int RW = kCombThreads / C4;
@@ -646,8 +636,8 @@ __global__ __launch_bounds__(kCombThreads) void decode_combine_rows_kernel(
   const int row = blockIdx.y * RW + threadIdx.x / C4;
   const int c4 = threadIdx.x % C4;
   const int len = (int)(poff[u + 1] - poff[u]);
-  const int keys = dec_keys(poff, U, keys_min);
-  const int nv = (int)((min(cover, (int64_t)len) + keys - 1) / keys);
+  const int nv = dec_pieces(poff[u] - poff[0], min(cover, (int64_t)len),
+                            dec_keys(poff[U] - poff[0], keys_min, parts));
   if (len > cover && blockIdx.y == 0 && threadIdx.x == 0) report_range(g);
   if (row >= tq * g.G) return;
   const int64_t base = u * nsplit * mp + row;  // + slot * mp
@@ -719,24 +709,14 @@ static certkv_status launch_decode(const DecodeArgs& a, hipStream_t s) {
   const uint16_t* q = static_cast<const uint16_t*>(a.q.ptr);
   const uint16_t* kp = static_cast<const uint16_t*>(a.k_packed);
   const uint16_t* vp = static_cast<const uint16_t*>(a.v_packed);
-#define CERTKV_DECODE(KERNEL)                                                                      \
-  CERTKV_LAUNCH("decode", (KERNEL<D, NQT>), dim3(grid), dim3(NT), 0, s, g, a.U,      \
-                a.cover, a.keys_min, (const int2*)a.items, (const int32_t*)a.item_count, a.tq,     \
-                a.nsplit, mp, q, a.q.s_layer, a.q.s_token, a.q.s_head, kp, vp, a.packed_offsets,   \
-                a.part_o, a.part_ml)
-  if (a.U <= kLocalUnits) {
-    CERTKV_DECODE(decode_local_kernel);
-  } else {
-    CERTKV_LAUNCH("decode_items", decode_items_kernel, dim3(1), dim3(kItemThreads), 0, s, a.U,
-                  a.cover, a.keys_min, a.packed_offsets, a.items, a.item_count);
-    CERTKV_DECODE(decode_kernel);
-  }
-#undef CERTKV_DECODE
+  CERTKV_LAUNCH("decode", (decode_kernel<D, NQT>), dim3(grid), dim3(NT), 0, s, g, a.U, a.cover,
+                a.keys_min, (int32_t)want, a.tq, a.nsplit, mp, q, a.q.s_layer, a.q.s_token,
+                a.q.s_head, kp, vp, a.packed_offsets, a.part_o, a.part_ml);
   const int M = a.tq * g.G;
   constexpr int RW = 4 * kCombThreads / D;
 #define CERTKV_COMBINE(CL)                                                                         \
   CERTKV_LAUNCH("decode_combine", (decode_combine_kernel<D, CL>), dim3((unsigned)a.U, (unsigned)M), \
-                dim3(kCombThreads), 0, s, g, a.U, a.cover, a.keys_min, a.tq, a.nsplit, mp,         \
+                dim3(kCombThreads), 0, s, g, a.U, a.cover, a.keys_min, (int32_t)want, a.tq, a.nsplit, mp,       \
                 a.packed_offsets, (const float*)a.part_o, (const float2*)a.part_ml, a.out, a.lse,  \
                 a.cl, q, a.q.s_layer, a.q.s_token, a.q.s_head)
   if (a.cl.m > 0)
@@ -746,7 +726,7 @@ static certkv_status launch_decode(const DecodeArgs& a, hipStream_t s) {
   else
     CERTKV_LAUNCH("decode_combine", (decode_combine_rows_kernel<D>),
                   dim3((unsigned)a.U, (unsigned)((M + RW - 1) / RW)), dim3(kCombThreads), 0, s, g,
-                  a.U, a.cover, a.keys_min, a.tq, a.nsplit, mp, a.packed_offsets,
+                  a.U, a.cover, a.keys_min, (int32_t)want, a.tq, a.nsplit, mp, a.packed_offsets,
                   (const float*)a.part_o, (const float2*)a.part_ml, a.out, a.lse);
 #undef CERTKV_COMBINE
   return CERTKV_OK;

@@ -189,15 +189,13 @@ struct DecodeArgs {
   int32_t tq;                   // new queries per sequence
   int32_t keys_min;             // shortest chunk the workspace has slots for
   int64_t cover;                // rows of a segment that the chunks cover
-  int32_t nsplit;               // slots per unit: cover / keys_min
+  int32_t nsplit;               // slots per unit: cover / keys_min + 1
   certkv_tensor q;              // [L][B*tq][Hq][d] bf16
   const void* k_packed;         // [P][d] bf16
   const void* v_packed;
   const int64_t* packed_offsets;
   float* part_o;                // [U][nsplit][mp][d]
   float2* part_ml;              // [U][nsplit][mp]
-  int2* items;                  // [U * nsplit] work items (unit, chunk), built on device
-  int32_t* item_count;          // their number
   float* out;                   // [L][B*tq][Hq][d]
   float* lse;                   // optional [L][B*tq][Hq]
   DecodeClusters cl;

@@ -242,11 +242,13 @@ def test_hull_allocation_beside_the_full_search(layers):
 
 @pytest.mark.parametrize("dim,group,tq", [(128, 4, 1), (128, 4, 33), (64, 1, 1), (128, 8, 8)])
 @pytest.mark.parametrize("rows", [[1, 2, 31, 127, 128, 129, 4097, 700], [9000] * 4 + [3] * 5,
-                                  [37] * 300, [150000, 10, 4096, 0, 65536]])
+                                  [37] * 300, [150000, 10, 4096, 0, 65536],
+                                  [128, 128, 256, 0, 0, 1, 127, 0], [0, 5, 300, 0] * 20,
+                                  [9001] * 8 + [0] * 60 + [33000] * 60])
 def test_decode_chunks(rows, dim, group, tq):
-    # Chunk lengths from 128 to 4096 keys, segments of a row to many chunks and
-    # an empty one, units found by the workgroups and from the list, both
-    # combines.  Rows within 1e-4 of fp64 attention, as the decode tests.
+    # Chunk lengths from 128 to over 4096 keys, chunks that end with a unit and
+    # inside one, segments of a row to many chunks and empty ones, up to 64 units
+    # and more, both combines.  Rows within 1e-4 of fp64 attention, as the decode tests.
     if len(rows) == 300 and dim == 64:
         rows = rows * 30                       # many rows: the row combine
     n = max(max(rows), 16)
@@ -256,7 +258,7 @@ def test_decode_chunks(rows, dim, group, tq):
     kp, vp = (torch.randn((sum(rows), dim), generator=gen, device=DEV).bfloat16() for _ in range(2))
     q = torch.randn((1, len(rows) * tq, group, dim), generator=gen, device=DEV).bfloat16()
     out, lse = ck.decode(spec, q, kp, vp, off, tq, with_lse=True, max_rows=max(rows))
-    for u in range(0, len(rows), 1 if len(rows) < 50 else 97):
+    for u in range(0, len(rows), 1 if len(rows) < 200 else 97):
         a, b = int(off[u]), int(off[u + 1])
         if a == b:
             continue
