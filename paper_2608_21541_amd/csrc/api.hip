@@ -551,8 +551,9 @@ static certkv_status do_select(const Plan& P, const float* scores, const uint32_
     else if (!fused)  // the pass's own budgets lie in [b_min, n - 1] already
       TRY(run_clamp(P.g, t, budgets, s));
   }
-  TRY(run_offsets(P.U, P.g.slot, budgets, kept_offsets, packed_offsets, s));
   SelectArgs a;
+  a.own_offsets = P.U <= kSelOwnOffsets;
+  if (!a.own_offsets) TRY(run_offsets(P.U, P.g.slot, budgets, kept_offsets, packed_offsets, s));
   a.g = P.g;
   a.scores = scores;
   a.sorted_keys = sorted_keys;

@@ -86,14 +86,15 @@ constexpr int kSelScanPer = kSelRounds * kSelWaves / 64;  // counts per lane of 
 __global__ __launch_bounds__(kSelThreads) void select_kernel(
     Geo g, SeqTab st, int32_t part_tiles, const float* __restrict__ scores,
     const uint32_t* __restrict__ sorted_keys, const int32_t* __restrict__ perm,
-    const int32_t* __restrict__ budgets, const int64_t* __restrict__ kept_offsets,
-    int32_t* __restrict__ kept_idx, int64_t capacity,
+    const int32_t* __restrict__ budgets, bool own_offsets, int64_t* __restrict__ kept_offsets,
+    int64_t* __restrict__ packed_offsets, int32_t* __restrict__ kept_idx, int64_t capacity,
     double* __restrict__ evicted_sum, double* __restrict__ total_sum, uint64_t* __restrict__ bm,
     int32_t bm_stride, uint8_t* __restrict__ mask) {
   // kept counts of each (round, wave) of a tile, then their exclusive prefix
   // in position order (round-major); the tile's total at the end
   __shared__ uint32_t kcnt[kSelRounds * kSelWaves + 1];
   __shared__ double dsum[2][kSelWaves];
+  __shared__ int64_t osum[kSelWaves];
   int h, part;
   const int bl = locate_part(g, st, blockIdx.x,
                              [&](int x) { return sel_parts(st.len[x], part_tiles); }, h, part);
@@ -112,7 +113,26 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
     kthr = sorted_keys[base + bb - 1];
     ithr = perm[base + bb - 1];
   }
-  const int64_t off = kept_offsets[u];
+  int64_t off = 0;
+  if (own_offsets) {
+    // the budgets before this unit's, summed by every workgroup (kSelOwnOffsets
+    // at most: one load a thread); a unit's first part writes its offsets
+    const int64_t v = wave_sum((int64_t)((int64_t)threadIdx.x < u ? budgets[threadIdx.x] : 0));
+    if (lane == 0) osum[wave] = v;
+    __syncthreads();
+    for (int w = 0; w < kSelWaves; ++w) off += osum[w];
+    if (part == 0 && threadIdx.x == 0) {
+      kept_offsets[u] = off;
+      if (packed_offsets) packed_offsets[u] = off + g.slot * u;
+      const int64_t U = (int64_t)g.L * g.B * g.H;
+      if (u == U - 1) {
+        kept_offsets[U] = off + bb;
+        if (packed_offsets) packed_offsets[U] = off + bb + g.slot * U;
+      }
+    }
+  } else {
+    off = kept_offsets[u];
+  }
   int64_t run = 0;
   double se = 0.0, sa = 0.0;
   // Round r of a tile: positions j0 + 1024 r + thread, so every load covers
@@ -511,8 +531,8 @@ certkv_status run_select(const SelectArgs& a, const SeqTab& st, hipStream_t s) {
                   a.g.L);
   CERTKV_LAUNCH("select", select_kernel, grid, dim3(kSelThreads), 0, s, a.g, st, part_tiles,
                 a.scores, a.sorted_keys, a.perm, (const int32_t*)a.budgets,
-                (const int64_t*)a.kept_offsets, a.kept_idx, a.capacity, a.evicted_sum, a.total_sum,
-                a.bitmap, a.bm_stride, a.mask);
+                a.own_offsets, a.kept_offsets, a.packed_offsets, a.kept_idx, a.capacity,
+                a.evicted_sum, a.total_sum, a.bitmap, a.bm_stride, a.mask);
   return CERTKV_OK;
 }
 

@@ -416,3 +416,23 @@ def test_select_parts(lens, heads, layers, keep_window):
                     assert np.array_equal(mask[l, h, t0:t0 + n], ref)
                 u += 1
             t0 += n
+
+
+@pytest.mark.parametrize("layers,heads,batch", [(1, 1, 1), (16, 8, 8), (5, 41, 5), (2, 8, 70)])
+def test_offsets_of_many_units(layers, heads, batch):
+    # Offsets summed by the selection (up to 1024 units, several launches of 48
+    # sequences) and by a launch of their own; no key kept at the ends.
+    lens = [17 + 3 * (b % 5) for b in range(batch)]
+    spec = ck.ProblemSpec(layers, heads, 1, 64, 16, lens, torch.float32)
+    rng = np.random.default_rng(layers)
+    bud = np.concatenate([rng.integers(0, 17, heads) for _ in range(layers * batch)]).astype(np.int32)
+    bud[0] = bud[-1] = 0
+    s = torch.from_numpy(_scores((layers, heads, sum(lens)), 4)).to(DEV)
+    _, off, idx = ck.select(spec, s, torch.from_numpy(bud).to(DEV))
+    assert np.array_equal(off.cpu().numpy(), np.concatenate([[0], np.cumsum(bud)]))
+    off, idx, s = off.tolist(), idx.cpu().numpy(), s.cpu().numpy()
+    starts = np.concatenate([[0], np.cumsum(lens)])
+    for u in range(len(bud)):
+        l, b, h = u // (batch * heads), u // heads % batch, u % heads
+        sh = s[l, h, starts[b]:starts[b + 1]]
+        assert np.array_equal(idx[off[u]:off[u + 1]], np.sort(oracle.order(sh)[:bud[u]]))
