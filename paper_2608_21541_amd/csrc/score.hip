@@ -916,21 +916,33 @@ __global__ __launch_bounds__(128) void ksum_reduce_kernel(Geo g, SeqTab st, int3
 // fp32 inputs: one key per thread, window queries in LDS, VALU dot products.
 //
 // A row's dot product is a chain of D dependent FMAs and its block sum two
-// reductions, so rows go kF32Rows at a time: independent chains side by side,
+// reductions, so rows go f32_rows at a time: independent chains side by side,
 // and two barriers for all of them.  Pass 1's rows are shared out over rsplit
 // workgroups per key block and pass 2's blocks hold KB = 64 keys instead of
 // 256 where whole blocks would leave the chip idle; neither changes the order
 // in which a row sum or a score is added up.  Bound by latency at small sizes:
 // 1024 keys, 16 rows, 4 heads of 64: 22 + 25 us one row at a time in 16
-// workgroups, 9 + 13 us.
-constexpr int kF32Rows = 4;
+// workgroups, 10 + 12 us.
+// Bound by FMAs at large ones, where the rows' LDS reads must not all be in
+// flight: left to itself the compiler issues a whole step's reads first and
+// holds R D of them in registers, one wave per SIMD and at 128 dims scratch.
+// The accumulators pinned every 16 dims bound that to 16 R, four waves per SIMD
+// at 64 dims and three at 128 (pass 1 + pass 2, eight sequences of 16384, 8
+// heads: 64 rows of 64 dims 448 + 222 us one row at a time, 935 + 423 unpinned,
+// 312 + 162 pinned; of 128 dims 1527 + 569, 5441 + 4742, 554 + 343).  At 128 dims
+// one row at a time is the faster pinned form (with four 723 + 460).  Pass 2's
+// one-wave blocks of 64 dims, launched only where a compute unit has fewer than
+// two, are left unpinned: nothing else hides their latency (4096 keys, 64 rows, 8
+// heads 31 us, 36 pinned).
+constexpr int f32_rows(int D) { return D == 64 ? 4 : 1; }
 template <int D, bool P2, int KB>
 __global__ __launch_bounds__(KB) void score_f32_kernel(
     Geo g, SeqTab st, const float* __restrict__ qw, int64_t q_sl, int64_t q_st, int64_t q_sh,
     const float* __restrict__ kc, int64_t k_sl, int64_t k_st, int64_t k_sh, int32_t nkb_max,
     int32_t rsplit, float2* __restrict__ part, const float* __restrict__ lse2,
     float* __restrict__ scores, float* __restrict__ kpart) {
-  constexpr int NW = KB / 64, R = kF32Rows;
+  constexpr int NW = KB / 64, R = f32_rows(D);
+  constexpr bool kPinned = !(P2 && KB == 64 && D == 64);
   extern __shared__ __align__(16) unsigned char smem_raw[];
   float* q_lds = reinterpret_cast<float*>(smem_raw);
   const int kb = blockIdx.x / rsplit;
@@ -989,6 +1001,10 @@ __global__ __launch_bounds__(KB) void score_f32_kernel(
         dot[i] = fmaf(x.y, kr[t + 1], dot[i]);
         dot[i] = fmaf(x.z, kr[t + 2], dot[i]);
         dot[i] = fmaf(x.w, kr[t + 3], dot[i]);
+      }
+      if (kPinned && t % 16 == 12) {  // these FMAs before the next reads
+#pragma unroll
+        for (int i = 0; i < R; ++i) __asm__ volatile("" : "+v"(dot[i]) : : "memory");
       }
     }
     bool vis[R];
@@ -1079,7 +1095,7 @@ size_t score_smem_bytes(const Geo& g, int32_t dtype) {
     const size_t red = nw * (Mp * 2 > (size_t)g.D ? Mp * 2 : (size_t)g.D) * 4;
     return (q > red ? q : red) + Mp * 8;
   }
-  return (size_t)M * g.D * 4 + (size_t)M * 4 + 2 * kF32Rows * 4 * 4 + (size_t)4 * g.D * 4;
+  return (size_t)M * g.D * 4 + (size_t)M * 4 + 2 * f32_rows(g.D) * 4 * 4 + (size_t)4 * g.D * 4;
 }
 
 template <int D, int NQT>
@@ -1169,8 +1185,8 @@ static certkv_status launch_f32(const ScoreArgs& a, const SeqTab& st, int max_le
   const Geo& g = a.g;
   const int nkb = (max_len + 255) / 256, M = g.w * g.G;
   const int64_t wgs = (int64_t)nkb * g.H * st.count * g.L;
-  int rsplit = 1;  // up to four pass-1 workgroups per compute unit, of kF32Rows rows or more
-  while (rsplit * kF32Rows < M && 2 * rsplit * wgs <= 4 * 256) rsplit *= 2;
+  int rsplit = 1;  // up to four pass-1 workgroups per compute unit, of a step's rows or more
+  while (rsplit * f32_rows(D) < M && 2 * rsplit * wgs <= 4 * 256) rsplit *= 2;
   dim3 grid(nkb * rsplit, g.H * st.count, g.L);
   size_t smem = score_smem_bytes(g, CERTKV_F32);
   const float* q = static_cast<const float*>(a.q.ptr);

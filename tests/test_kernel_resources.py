@@ -20,6 +20,12 @@ KERNELS = [
     ("score.hip", "_ZN6certkv17score_mfma_kernelILi128ELi8ELi0E", 128),       # pass 1
     ("score.hip", "_ZN6certkv22score_pass2_w16_kernelILi128ELi8ELb1E", 128),  # pass 2, key sums
     ("score.hip", "_ZN6certkv22score_pass2_w16_kernelILi128ELi8ELb0E", 128),  # pass 2
+    ("score.hip", "_ZN6certkv16score_f32_kernelILi64ELb0ELi256E", 128),       # fp32 passes: four
+    ("score.hip", "_ZN6certkv16score_f32_kernelILi64ELb1ELi256E", 128),       # waves per SIMD,
+    ("score.hip", "_ZN6certkv16score_f32_kernelILi64ELb1ELi64E", 256),        # one-wave blocks: one,
+    ("score.hip", "_ZN6certkv16score_f32_kernelILi128ELb0ELi256E", 168),      # rows of 128: three
+    ("score.hip", "_ZN6certkv16score_f32_kernelILi128ELb1ELi256E", 168),
+    ("score.hip", "_ZN6certkv16score_f32_kernelILi128ELb1ELi64E", 168),
     ("sort.hip", "_ZN6certkv15seg_sort_kernel", 128),
     ("curves.hip", "_ZN6certkv13curves_kernelILi128ELb1ELi0E", 128),         # centered
     ("curves.hip", "_ZN6certkv13curves_kernelILi128ELb1ELi1E", 128),         # uncentered
