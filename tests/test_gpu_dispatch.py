@@ -140,17 +140,37 @@ def test_curve_segments(name, lens, heads, layers):
             t0 += n
 
 
+def _samples(n):
+    # Positions that the sort's splitters are chosen from (sort_sample).
+    ns = -(-2 * n // 4096) * 32
+    i = np.arange(ns, dtype=np.int64)
+    lo, hi = i * n // ns, (i + 1) * n // ns
+    x = (i * 0x9E3779B1) & 0xFFFFFFFF
+    x = ((x ^ x >> 15) * 0x2C1B3C6D) & 0xFFFFFFFF
+    x ^= x >> 13
+    return lo + (x * (hi - lo) >> 32)
+
+
+def _largest_bucket(s, perm):
+    # Elements between every 32nd sample of a unit in its order `perm`.
+    rank = np.empty(len(s), np.int64)
+    rank[perm] = np.arange(len(s))
+    cut = np.sort(rank[_samples(len(s))])[32::32]
+    return np.diff(np.concatenate([[0], cut, [len(s)]])).max()
+
+
 @pytest.mark.parametrize("lens", [[16], [4095], [4096, 33], [4097, 4096], [8193], [32768, 100, 5000],
                                   [32769], [70001, 33000], [262144], [262145]])
 @pytest.mark.parametrize("keep_window", [False, True])
 def test_sort_sizes(lens, keep_window):
     # One LDS sort, buckets by value beside units of one, and the edges between
     # them: random scores, ties (flat, quantized, signed zeros), order that
-    # follows the position, and keys that the evenly spaced samples miss (every
-    # sixteenth position and its neighbours loud), so that a bucket outgrows
-    # LDS and is sorted through memory.
+    # follows the position, and every score that is not a sample above all the
+    # samples, ties among them, so that the first bucket holds nearly the whole
+    # unit, outgrows LDS and is sorted through memory.
     cfg = synth.config("C1", seqlens=lens, layers=2)
     n_all, w = sum(lens), cfg.window
+    starts = np.concatenate([[0], np.cumsum(lens)])
     s = _scores((2, 4, n_all), n_all)
     s[0, 1] = 0.5
     s[0, 2] = np.round(s[0, 2] * 2) / 2 - 1.0
@@ -158,9 +178,10 @@ def test_sort_sizes(lens, keep_window):
     s[0, 3] = np.arange(n_all) / n_all
     s[1, 0] = np.arange(n_all)[::-1] / n_all
     s[1, 1, : n_all // 3] += 1e4
-    s[1, 2] = 1.0
-    s[1, 2, ::85] += 1.0 + _scores(len(s[1, 2, ::85]), 5)
-    s[1, 2, 1::85] += np.float32(1e-3) * _scores(len(s[1, 2, 1::85]), 6)
+    s[1, 2, ::3] = np.round(s[1, 2, ::3] * 4) / 4
+    s[1, 2] += 1e3
+    for t0, n in zip(starts, lens):
+        s[1, 2, t0 + _samples(n)] -= np.float32(1e3)
     s[1, 3, : n_all // 2] = 0.25                 # one long tie across runs, then spread scores
     spec = spec_of(cfg)
     spec.keep_window = keep_window
@@ -172,11 +193,36 @@ def test_sort_sizes(lens, keep_window):
                        with_perm=True)["perm"].cpu().numpy()
     for l in range(2):
         for h in range(4):
-            t0 = 0
-            for n in lens:
-                ref = oracle.order(s[l, h, t0:t0 + n], keep_window=w if keep_window else 0)
+            for t0, n in zip(starts, lens):
+                sh = s[l, h, t0:t0 + n]
+                ref = oracle.order(sh, keep_window=w if keep_window else 0)
                 assert np.array_equal(perm[l, h, t0:t0 + n], ref), (l, h, n)
-                t0 += n
+                if (l, h) == (1, 2) and n >= 5000:
+                    assert _largest_bucket(sh, ref) > 4096
+
+
+@pytest.mark.parametrize("period", [2, 16, 64, 128])
+def test_sort_of_periodic_scores(period):
+    # Scores with a period keep the buckets even: within three times the time
+    # of scores without one (a bucket of most of a unit takes ten times and more).
+    n, units = 65536, 64
+    spec = ck.ProblemSpec(units // 8, 8, 1, 64, 16, [n])
+    bud = torch.full((units,), n // 10, dtype=torch.int32, device=DEV)
+    s = torch.from_numpy(_scores((units // 8, 8, n), 21)).to(DEV)
+    p = s + 10.0 * (torch.arange(n, device=DEV) % period != 0)
+    us = []
+    for x in (s, p):
+        best = np.inf
+        for _ in range(4):
+            ck.profile_reset()
+            ck.profile_enable(True)
+            ck.select(spec, x, bud)
+            torch.cuda.synchronize()
+            ck.profile_enable(False)
+            best = min(best, sum(ms for k, (_, ms) in ck.profile_read().items()
+                                 if k.startswith("sort")))
+        us.append(1e3 * best)
+    assert us[1] <= 3 * us[0], us
 
 
 def _curves(kind, H, n, rng):
