@@ -476,7 +476,8 @@ __device__ __forceinline__ CellMap cells_around_mean(OrderLds& s, const uint32_t
 // which bind the vector unit (buckets of 64 units of 65536 keys, 1365 each: 113
 // us with them, 67 us with cells; 40 us with 2048 each and two workgroups to a
 // compute unit).  They are left for a cell of more than kCellMax elements:
-// many equal or close keys beside far ones.
+// many equal or close keys beside far ones.  (Not unrolled: four copies spill at
+// the 64 VGPRs of two workgroups to a compute unit.)
 __device__ __forceinline__ void lds_order(OrderLds& s, const uint32_t (&key)[kRunRounds],
                                           const int32_t (&val)[kRunRounds], const CellMap& cm,
                                           int R, int cnt, int lane, int wave) {
@@ -546,6 +547,7 @@ __device__ __forceinline__ void lds_order(OrderLds& s, const uint32_t (&key)[kRu
     v[r] = val[r];
   }
   for (int p = 0; p < 4; ++p) {
+#pragma unroll 1
     rank_clear(s.rk, lane, wave);
     __syncthreads();
     uint32_t dg[kRunRounds], lp[kRunRounds];

@@ -27,6 +27,11 @@ KERNELS = [
     ("score.hip", "_ZN6certkv16score_f32_kernelILi128ELb1ELi256E", 168),
     ("score.hip", "_ZN6certkv16score_f32_kernelILi128ELb1ELi64E", 168),
     ("sort.hip", "_ZN6certkv15seg_sort_kernel", 128),
+    ("sort.hip", "_ZN6certkv17sort_small_kernel", 64),                        # two workgroups of
+    ("sort.hip", "_ZN6certkv19sort_buckets_kernel", 64),                      # 1024 per compute unit
+    ("sort.hip", "_ZN6certkv21sort_splitters_kernel", 128),
+    ("sort.hip", "_ZN6certkv17sort_count_kernel", 64),
+    ("sort.hip", "_ZN6certkv19sort_scatter_kernel", 64),
     ("curves.hip", "_ZN6certkv13curves_kernelILi128ELb1ELi0E", 128),         # centered
     ("curves.hip", "_ZN6certkv13curves_kernelILi128ELb1ELi1E", 128),         # uncentered
     ("curves.hip", "_ZN6certkv13curves_kernelILi128ELb1ELi2E", 128),         # tail mass
