@@ -108,14 +108,21 @@ static void curve_split(Plan& P) {
 }
 
 // Buckets of the longest sequence for the sort (see sort.hip); 0: one
-// workgroup per unit.  The bucket sort is the faster one wherever its samples
-// fit one LDS sort (up to 262144 keys): with one workgroup per unit and with
-// buckets, launch by launch, 8 units of 32768 keys 130 and 37 us, 64 of 65536
-// 254 and 91, 256 of 32768 150 and 136, 256 of 131072 716 and 500 (716 and 667
-// on scores with planted keys).  (256 of 8192: 45 and 58 with each launch timed
-// apart, which costs 4 us per launch.)
+// workgroup per unit.  A workgroup sorts a unit of up to 8192 keys, one tile, in
+// four short passes, 256 units at a time; buckets take four launches but fill the
+// chip whatever the units' number.  So such units take a workgroup each where its
+// last round of 256 is at least half full and the rounds are few (one workgroup
+// per unit and buckets, the whole selection, units of 8192 and of 5000 keys: 64 units
+// 51 and 46 us, 46 and 40; 192 56 and 64, 48 and 52; 256 58 and 69, 50 and 60; 320 95
+// and 89, 83 and 75; 512 100 and 105, 86 and 89; 1024 178 and 174, 154 and 149; 2048
+// 352 and 323, 293 and 271).  Longer units are in buckets as long as their samples
+// fit one LDS sort (up to 262144 keys): 8 units of 32768 keys 150 and 49 us, 256 of
+// 16384 104 and 105, of 32768 177 and 155, of 131072 788 and 564.
 static int sort_buckets(const Plan& P) {
   const int nb = sort_nb(P.max_len);
+  if (nb > 1 && P.max_len <= 8192 && P.U <= 3 * kCUs &&
+      (P.U + kCUs - 1) / kCUs * kCUs - P.U < kCUs / 2)
+    return 0;
   return nb <= kSortNb ? nb : 0;
 }
 

@@ -22,9 +22,10 @@
 // equal scores keep ascending position.  The next tile's elements are loaded
 // while the current one is ranked.
 //
-// With few units that leaves most of the chip idle behind a serial chain of
-// tiles.  Then a unit is cut by value into buckets of about half of kSortRun
-// elements, each sorted by a workgroup of its own, entirely in LDS:
+// That is a serial chain of tiles, which leaves most of the chip idle with few
+// units.  So most units of more than kSortRun elements are cut by value into
+// buckets of about half of it, each sorted by a workgroup of its own, entirely in
+// LDS (units of up to kSortRun by one workgroup, without buckets):
 //   splitters  one workgroup per unit sorts kSortOver samples per bucket,
 //              one from each of as many equal stretches of positions, and
 //              picks every kSortOver-th;
@@ -546,8 +547,8 @@ __device__ __forceinline__ void lds_order(OrderLds& s, const uint32_t (&key)[kRu
     k[r] = key[r];
     v[r] = val[r];
   }
-  for (int p = 0; p < 4; ++p) {
 #pragma unroll 1
+  for (int p = 0; p < 4; ++p) {
     rank_clear(s.rk, lane, wave);
     __syncthreads();
     uint32_t dg[kRunRounds], lp[kRunRounds];

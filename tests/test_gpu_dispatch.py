@@ -201,6 +201,23 @@ def test_sort_sizes(lens, keep_window):
                     assert _largest_bucket(sh, ref) > 4096
 
 
+@pytest.mark.parametrize("layers,heads", [(1, 128), (43, 3), (4, 64), (257, 1), (385, 1), (96, 8),
+                                          (769, 1)])
+@pytest.mark.parametrize("lens", [[8192], [4097], [8193]])
+def test_sort_of_many_units(layers, heads, lens):
+    # Units of up to 8192 keys sorted by a workgroup each or in buckets, by
+    # their number.
+    layers, heads = (layers, heads) if heads <= 64 else (layers * heads // 64, 64)
+    spec = ck.ProblemSpec(layers, heads, 1, 64, 16, lens, torch.float32)
+    s = np.round(_scores((layers, heads, lens[0]), 31) * 256) / 256
+    st = torch.from_numpy(s).to(DEV)
+    v = torch.zeros((layers, lens[0], heads, 64), device=DEV)
+    perm = ck.allocate(spec, st, v, [lens[0] // 10], with_perm=True)["perm"].cpu().numpy()
+    for u in {0, 1, layers * heads // 2, layers * heads - 1}:
+        l, h = u // heads, u % heads
+        assert np.array_equal(perm[l, h], oracle.order(s[l, h])), u
+
+
 @pytest.mark.parametrize("period", [2, 16, 64, 128])
 def test_sort_of_periodic_scores(period):
     # Scores with a period keep the buckets even: within three times the time
