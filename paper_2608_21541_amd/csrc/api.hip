@@ -57,7 +57,6 @@ struct Plan {
   int kpb;           // keys per scoring block, pass 1
   int nkb_max;       // pass-1 scoring blocks per unit (max over sequences)
   int kpb2;          // keys per scoring block, pass 2
-  int nkb2_max;      // pass-2 scoring blocks per unit
   int nblk_max;      // 256-rank allocation blocks per unit
   int chunk_blocks;  // allocation blocks per chunk of the hull filter
   int bm_words;      // 64-bit bitmap words per unit
@@ -201,7 +200,6 @@ static certkv_status make_plan(const certkv_problem* p, Plan* pl) {
   P.kpb = kpb;
   P.nkb_max = (max_len + kpb - 1) / kpb;
   P.kpb2 = kpb2;
-  P.nkb2_max = (max_len + kpb2 - 1) / kpb2;
   P.nblk_max = (max_len + 255) / 256;
   // Chunks of 8 blocks share the filter's fixed work; with less than eight waves
   // of them per SIMD (1024 SIMDs) chunks of 2 are done sooner (8 units of 32768
@@ -349,14 +347,33 @@ enum : uint32_t {
   NEED_OFFSETS = 256u,
 };
 
+// Parts of the launch that has the most, in every layer (see part_base); one
+// launch of a stage after the other uses the same array.
+template <typename F>
+static size_t launch_parts(const Plan& P, F parts) {
+  size_t most = 0;
+  for (int b0 = 0; b0 < P.g.B; b0 += kMaxSeq) {
+    size_t c = 0;
+    for (int b = b0; b < P.g.B && b < b0 + kMaxSeq; ++b)
+      c += (size_t)parts((int)(P.cu[b + 1] - P.cu[b]));
+    most = c > most ? c : most;
+  }
+  return most * P.g.H * P.g.L;
+}
+
 static size_t layout(const Plan& P, uint32_t need, void* ws, Bufs* b) {
   WS w;
   w.base = static_cast<char*>(ws);
   const size_t LHT = (size_t)P.g.L * P.g.H * (size_t)P.g.T;
   if (need & NEED_SCORE) {
-    b->part = w.take<float2>((size_t)P.U * P.nkb_max * P.M);
+    // pass 2's key-sum partials take the place of pass 1's row partials, which
+    // the row sums have read by then
+    const size_t rows = (size_t)P.U * P.nkb_max * P.M * 2;
+    const size_t sums =
+        launch_parts(P, [&](int n) { return (n + P.kpb2 - 1) / P.kpb2; }) * P.g.D;
+    b->kpart = w.take<float>(rows > sums ? rows : sums);
+    b->part = reinterpret_cast<float2*>(b->kpart);
     b->lse2 = w.take<float>((size_t)P.U * P.M);
-    b->kpart = w.take<float>((size_t)P.U * P.nkb2_max * P.g.D);
     b->flag = w.take<int32_t>((size_t)P.U);
   }
   if (need & NEED_KSUM) {
@@ -465,7 +482,6 @@ static certkv_status do_score(const Plan& P, certkv_tensor q, certkv_tensor k,
   a.keys_per_block = P.dtype == CERTKV_BF16 ? P.kpb : 256;
   a.nkb_max = P.dtype == CERTKV_BF16 ? P.nkb_max : (P.max_len + 255) / 256;
   a.keys_per_block2 = P.kpb2;
-  a.nkb2_max = P.nkb2_max;
   for (const SeqTab& t : make_tabs(P, nullptr, 0.f)) {
     int ml = 0;
     for (int i = 0; i < t.count; ++i) ml = t.len[i] > ml ? t.len[i] : ml;

@@ -99,6 +99,19 @@ inline unsigned count_parts(const Geo& g, const SeqTab& st, F parts) {
   return (unsigned)(c * g.H);
 }
 
+// First entry of a unit in an array that holds one entry per part that exists:
+// the units of a launch by sequence and head, each with its parts in every
+// layer.  (Arrays with the longest sequence's parts for every unit outgrow the cache of
+// a ragged batch.)
+template <typename F>
+__device__ __forceinline__ int64_t part_base(const Geo& g, const SeqTab& st, int l, int bl, int h,
+                                             F parts) {
+  int64_t c = 0;
+  for (int i = 0; i < bl; ++i) c += parts(i);
+  const int p = parts(bl);
+  return (c * g.H + (int64_t)h * p) * g.L + (int64_t)l * p;
+}
+
 // Raw buffer resource over [base, base + bytes): loads through it take a
 // uniform 64-bit base and a 32-bit per-lane byte offset, and return zero for
 // offsets at or beyond `bytes` (hardware range check).

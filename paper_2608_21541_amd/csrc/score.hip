@@ -53,10 +53,19 @@ enum { kPass1Sum = 0, kPass1Max = 1 };
 // the heads of a block next to each other, each XCD reading one head of the
 // same tokens, uniform lengths were slower (64 units of 32768 keys, 128 rows:
 // pass 1 130 us against 121, 32 rows 115 against 102).
+__device__ __forceinline__ int score_blocks(const SeqTab& st, int bl, int32_t keys_per_block) {
+  return (st.len[bl] + keys_per_block - 1) / keys_per_block;
+}
 __device__ __forceinline__ int score_block(const Geo& g, const SeqTab& st, int32_t keys_per_block,
                                            int x, int& kb, int& h) {
   return locate_part(
-      g, st, x, [&](int bl) { return (st.len[bl] + keys_per_block - 1) / keys_per_block; }, h, kb);
+      g, st, x, [&](int bl) { return score_blocks(st, bl, keys_per_block); }, h, kb);
+}
+
+// A block's row of the key-sum partials, one for each block that exists.
+__device__ __forceinline__ int64_t kpart_row(const Geo& g, const SeqTab& st, int32_t keys_per_block,
+                                             int l, int bl, int h, int kb) {
+  return part_base(g, st, l, bl, h, [&](int i) { return score_blocks(st, i, keys_per_block); }) + kb;
 }
 
 // One round of a transpose-reduce over lane bit M: lanes with that bit set
@@ -330,7 +339,7 @@ template <int D, int NQT, bool KSUM>
 __global__ __launch_bounds__(kScoreThreads) __attribute__((amdgpu_waves_per_eu((KSUM || NQT > 8) ? 2 : 4, 8))) void score_pass2_kernel(
     Geo g, SeqTab st, const uint16_t* __restrict__ qw, int64_t q_sl, int64_t q_st,
     int64_t q_sh, const uint16_t* __restrict__ kc, int64_t k_sl, int64_t k_st,
-    int64_t k_sh, int32_t keys_per_block, int32_t nkb_max, const float* __restrict__ lse2,
+    int64_t k_sh, int32_t keys_per_block, const float* __restrict__ lse2,
     float* __restrict__ scores, float* __restrict__ kpart) {
   constexpr int KS = D / 16;   // MFMA k-steps
   constexpr int HD = D / 2;    // dims per lane half
@@ -530,10 +539,11 @@ __global__ __launch_bounds__(kScoreThreads) __attribute__((amdgpu_waves_per_eu((
 #pragma unroll
     for (int e = 0; e < PER; ++e) red_lds[wave * D + hh * HD + c32 * PER + e] = v[e];
     __syncthreads();
+    const int64_t row = kpart_row(g, st, keys_per_block, l, bl, h, kb);
     for (int dd = threadIdx.x; dd < D; dd += kScoreThreads) {
       float s = 0.f;
       for (int wv = 0; wv < NW; ++wv) s += red_lds[wv * D + dd];
-      kpart[(u * nkb_max + kb) * D + dd] = s;
+      kpart[row * D + dd] = s;
     }
   }
 }
@@ -582,7 +592,7 @@ template <int D, int NQT, bool KSUM>
 __global__ __launch_bounds__(kP2Threads) __attribute__((amdgpu_waves_per_eu(4, 8))) void score_pass2_w16_kernel(
     Geo g, SeqTab st, const uint16_t* __restrict__ qw, int64_t q_sl, int64_t q_st,
     int64_t q_sh, const uint16_t* __restrict__ kc, int64_t k_sl, int64_t k_st,
-    int64_t k_sh, int32_t keys_per_block, int32_t nkb_max, const float* __restrict__ lse2,
+    int64_t k_sh, int32_t keys_per_block, const float* __restrict__ lse2,
     float* __restrict__ scores, float* __restrict__ kpart) {
   using SM = P2Smem<D, NQT>;
   constexpr int KS = D / 16;   // MFMA k-steps
@@ -803,10 +813,11 @@ __global__ __launch_bounds__(kP2Threads) __attribute__((amdgpu_waves_per_eu(4, 8
     for (int sg = 0; sg < NSTG; ++sg)
       red_lds[wave * D + 64 * sg + lane] = kacc[sg][0] + kacc[sg][1] + kacc[sg][2];
     __syncthreads();
+    const int64_t row = kpart_row(g, st, keys_per_block, l, bl, h, kb);
     for (int dd = threadIdx.x; dd < D; dd += kP2Threads) {
       float s = 0.f;
       for (int wv = 0; wv < kP2Waves; ++wv) s += red_lds[wv * D + dd];
-      kpart[(u * nkb_max + kb) * D + dd] = s;
+      kpart[row * D + dd] = s;
     }
   }
 }
@@ -893,7 +904,6 @@ __global__ __launch_bounds__(256) void lse_io_kernel(Geo g, SeqTab st, const flo
 
 // Sum the per-block weighted key sums in fp64 (fixed block order).
 __global__ __launch_bounds__(128) void ksum_reduce_kernel(Geo g, SeqTab st, int32_t keys_per_block,
-                                                           int32_t nkb_max,
                                                            const float* __restrict__ kpart,
                                                            double* __restrict__ ksum) {
   const int h = blockIdx.x % g.H;
@@ -902,12 +912,13 @@ __global__ __launch_bounds__(128) void ksum_reduce_kernel(Geo g, SeqTab st, int3
   if (bl >= st.count) return;
   const int b = st.first + bl;
   const int n = st.len[bl];
-  const int nkb = (n + keys_per_block - 1) / keys_per_block;
+  const int nkb = score_blocks(st, bl, keys_per_block);
   const int64_t u = unit_index(g, l, b, h);
+  const int64_t row = kpart_row(g, st, keys_per_block, l, bl, h, 0);
   for (int dd = threadIdx.x; dd < g.D; dd += blockDim.x) {
     double s = 0.0;
 #pragma unroll 16
-    for (int kb = 0; kb < nkb; ++kb) s += (double)kpart[(u * nkb_max + kb) * g.D + dd];
+    for (int kb = 0; kb < nkb; ++kb) s += (double)kpart[(row + kb) * g.D + dd];
     ksum[u * g.D + dd] = s;
   }
 }
@@ -1073,11 +1084,12 @@ __global__ __launch_bounds__(KB) void score_f32_kernel(
 #pragma unroll
       for (int t = 0; t < D / 64; ++t) wred[wave * D + lane * (D / 64) + t] = kr[t];
       __syncthreads();
+      const int64_t row = kpart_row(g, st, KB, l, bl, h, kb);
       for (int t = threadIdx.x; t < D; t += KB) {
         float x = wred[t];
 #pragma unroll
         for (int w = 1; w < NW; ++w) x += wred[w * D + t];
-        kpart[(u * nkb_max + kb) * D + t] = x;
+        kpart[row * D + t] = x;
       }
     }
   }
@@ -1152,28 +1164,28 @@ static certkv_status launch_mfma(const ScoreArgs& a, const SeqTab& st, hipStream
     if (a.ksum)
       CERTKV_LAUNCH("score_pass2_mfma", (score_pass2_w16_kernel<D, NQT, true>), grid2,
                     dim3(kP2Threads), smem2, s, g, st, q, a.q.s_layer, a.q.s_token, a.q.s_head, k,
-                    a.k.s_layer, a.k.s_token, a.k.s_head, a.keys_per_block2, a.nkb2_max,
+                    a.k.s_layer, a.k.s_token, a.k.s_head, a.keys_per_block2,
                     (const float*)a.lse2, a.scores, a.kpart);
     else
       CERTKV_LAUNCH("score_pass2_mfma", (score_pass2_w16_kernel<D, NQT, false>), grid2,
                     dim3(kP2Threads), smem2, s, g, st, q, a.q.s_layer, a.q.s_token, a.q.s_head, k,
-                    a.k.s_layer, a.k.s_token, a.k.s_head, a.keys_per_block2, a.nkb2_max,
+                    a.k.s_layer, a.k.s_token, a.k.s_head, a.keys_per_block2,
                     (const float*)a.lse2, a.scores, (float*)nullptr);
   } else {
     if (a.ksum)
       CERTKV_LAUNCH("score_pass2_mfma", (score_pass2_kernel<D, NQT, true>), grid2,
                     dim3(kScoreThreads), smem, s, g, st, q, a.q.s_layer, a.q.s_token, a.q.s_head, k,
-                    a.k.s_layer, a.k.s_token, a.k.s_head, a.keys_per_block2, a.nkb2_max,
+                    a.k.s_layer, a.k.s_token, a.k.s_head, a.keys_per_block2,
                     (const float*)a.lse2, a.scores, a.kpart);
     else
       CERTKV_LAUNCH("score_pass2_mfma", (score_pass2_kernel<D, NQT, false>), grid2,
                     dim3(kScoreThreads), smem, s, g, st, q, a.q.s_layer, a.q.s_token, a.q.s_head, k,
-                    a.k.s_layer, a.k.s_token, a.k.s_head, a.keys_per_block2, a.nkb2_max,
+                    a.k.s_layer, a.k.s_token, a.k.s_head, a.keys_per_block2,
                     (const float*)a.lse2, a.scores, (float*)nullptr);
   }
   if (a.ksum)
     CERTKV_LAUNCH("score_ksum_reduce", ksum_reduce_kernel, dim3(g.H * st.count, g.L), dim3(128), 0,
-                  s, g, st, a.keys_per_block2, a.nkb2_max, (const float*)a.kpart, a.ksum);
+                  s, g, st, a.keys_per_block2, (const float*)a.kpart, a.ksum);
   if (a.lse_out)
     CERTKV_LAUNCH("score_lse_export", lse_io_kernel<false>, dim3(g.H * st.count, g.L), dim3(256), 0,
                   s, g, st, (const float*)nullptr, a.lse2, a.lse_out);
@@ -1205,7 +1217,7 @@ static certkv_status launch_f32(const ScoreArgs& a, const SeqTab& st, int max_le
     CERTKV_LAUNCH("score_pass2_f32", kernel,
                   dim3((max_len + keys - 1) / keys, g.H * st.count, g.L), dim3(keys), smem, s, g, st,
                   q, a.q.s_layer, a.q.s_token, a.q.s_head, k, a.k.s_layer, a.k.s_token, a.k.s_head,
-                  a.nkb2_max, 1, (float2*)nullptr, (const float*)a.lse2, a.scores,
+                  0, 1, (float2*)nullptr, (const float*)a.lse2, a.scores,
                   a.ksum ? a.kpart : (float*)nullptr);
     return CERTKV_OK;
   };
@@ -1214,7 +1226,7 @@ static certkv_status launch_f32(const ScoreArgs& a, const SeqTab& st, int max_le
   if (rc != CERTKV_OK) return rc;
   if (a.ksum)
     CERTKV_LAUNCH("score_ksum_reduce", ksum_reduce_kernel, dim3(g.H * st.count, g.L), dim3(128), 0,
-                  s, g, st, a.keys_per_block2, a.nkb2_max, (const float*)a.kpart, a.ksum);
+                  s, g, st, a.keys_per_block2, (const float*)a.kpart, a.ksum);
   if (a.lse_out)
     CERTKV_LAUNCH("score_lse_export", lse_io_kernel<false>, dim3(g.H * st.count, g.L), dim3(256), 0,
                   s, g, st, (const float*)nullptr, a.lse2, a.lse_out);

@@ -93,6 +93,24 @@ def test_dry_run_score_validation():
                           None) == _lib.CERTKV_EINVAL  # scores are required
 
 
+@pytest.mark.parametrize("L,H,G,w,seqlens,mib", [
+    (1, 4, 8, 64, (159000,) + (1000,) * 99, 17.0),   # a long sequence beside many short ones
+    (1, 8, 4, 64, (131072,) + (1024,) * 47, 7.2),
+    (1, 1, 4, 64, (1 << 20,) + (512,) * 249, 10.1),
+    (1, 4, 1, 16, (1024,), 0.1),
+    (32, 8, 4, 64, (131072,), 4.8),
+])
+def test_score_workspace_of_ragged_batches(L, H, G, w, seqlens, mib):
+    # The scoring workspace follows the blocks that exist, not the longest
+    # sequence's for every one, and fits the fixed array of score_noalloc.
+    lib = _lib.lib()
+    p = problem(L=L, seqlens=seqlens, H=H, G=G, w=w)
+    assert lib.certkv_workspace_size(ctypes.byref(p), _lib.STAGE_SCORE) <= mib * 2 ** 20
+    t = tensor(sl=sum(seqlens) * 64 * 128, st=H * 128)
+    assert lib.certkv_score_noalloc(ctypes.byref(p), t, t, None, FAKE, None, None,
+                                    None) == _lib.CERTKV_OK
+
+
 def test_dry_run_allocate_budget_checks():
     L = _lib.lib()
     p = problem()

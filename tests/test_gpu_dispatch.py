@@ -373,6 +373,30 @@ def test_score_f32_blocks(dim, group, window, lens, heads, causal):
         t0 += n
 
 
+@pytest.mark.parametrize("dtype,dim,window", [(torch.bfloat16, 128, 16), (torch.bfloat16, 64, 120),
+                                              (torch.float32, 64, 16)])
+@pytest.mark.parametrize("lens", [[5000] + [333] * 49 + [1500], [131] * 20 + [9000, 640]])
+def test_ragged_key_sums(dtype, dim, window, lens):
+    # A long sequence beside short ones, in one launch of up to 48 and in two:
+    # the key sums of the scores given out, in fp64.  A block's fp32 sums of at
+    # most n terms are off by n 2^-24 of the terms' magnitudes.
+    H, G, L = 3, 4 if window > 100 else 2, 2
+    spec = ck.ProblemSpec(L, H, G, dim, window, lens, dtype)
+    gen = torch.Generator(device=DEV).manual_seed(len(lens))
+    q = torch.randn((L, len(lens) * window, H * G, dim), generator=gen, device=DEV).to(dtype)
+    k = torch.randn((L, sum(lens), H, dim), generator=gen, device=DEV).to(dtype)
+    s, ksum = ck.score(spec, q, k, with_ksum=True)[:2]
+    u = torch.arange(L * len(lens) * H).reshape(L, len(lens), H)
+    t0 = 0
+    for b, n in enumerate(lens):
+        sb, kb = s[..., t0:t0 + n].double(), k[:, t0:t0 + n].double()
+        for l in range(L):
+            for h in range(H):
+                ref, mag = sb[l, h] @ kb[l, :, h], sb[l, h] @ kb[l, :, h].abs()
+                assert ((ksum[u[l, b, h]] - ref).abs() <= n * 2.0 ** -24 * mag).all(), (l, b, h)
+        t0 += n
+
+
 @pytest.mark.parametrize("name,lens", [("C2", [255, 256, 4097, 20001]), ("C1", [63, 300, 9000])])
 def test_gather_splits(name, lens):
     # Kept rows shared out over a unit's splits: none, one, part of a step, a
