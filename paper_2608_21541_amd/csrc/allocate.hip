@@ -78,7 +78,6 @@ constexpr size_t kSyncWords = kSyncArg + (size_t)kSyncGroups * 2 * kTreeMax * 64
 
 size_t alloc_sync_words() { return kSyncWords; }
 size_t alloc_chunk_points() { return kChunkCap; }
-size_t alloc_unit_points() { return kUnitCap; }
 
 // Lanes below this one among those set in `mask`.
 __device__ __forceinline__ uint32_t count_below64(uint64_t mask) {
@@ -339,6 +338,16 @@ __device__ __forceinline__ int hull_filter(uint2* pts, int m, int rounds, int la
   return m;
 }
 
+// Chunks of nb blocks of a unit of n ranks, and the first one of a unit's in the
+// chunks' arrays (one entry per chunk of the launch).
+__device__ __forceinline__ int hull_chunks(int n, int nb) {
+  return ((n + kBlk - 1) / kBlk + nb - 1) / nb;
+}
+__device__ __forceinline__ int64_t hull_base(const Geo& g, const SeqTab& st, int l, int bl, int h,
+                                             int nb) {
+  return part_base(g, st, l, bl, h, [&](int i) { return hull_chunks(st.len[i], nb); });
+}
+
 template <bool HULL, int NB>
 __global__ __launch_bounds__(256) void curve_blockstats_kernel(Geo g, SeqTab st, int32_t nblk_max,
                                                                const float* __restrict__ curves,
@@ -347,7 +356,6 @@ __global__ __launch_bounds__(256) void curve_blockstats_kernel(Geo g, SeqTab st,
                                                                int32_t* __restrict__ cpos,
                                                                double* __restrict__ dmax,
                                                                int32_t* __restrict__ sync, int32_t nsync,
-                                                               int32_t nchunk_max,
                                                                uint2* __restrict__ hull_pts,
                                                                int32_t* __restrict__ hull_cnt) {
   __shared__ __align__(16) uint2 hlist[HULL ? 4 : 1][HULL ? kChunkList : 1];
@@ -429,7 +437,7 @@ __global__ __launch_bounds__(256) void curve_blockstats_kernel(Geo g, SeqTab st,
     const int bmin = st.b_min[bl];
     const int c_lo = max(k0 * kBlk, bmin), c_hi = min((k0 + NB) * kBlk, n) - 1;
     const bool over0 = __ballot(bad) != 0ull;
-    const int64_t ch_i = u * nchunk_max + (k0 / NB);
+    const int64_t ch_i = hull_base(g, st, l, bl, h, NB) + k0 / NB;
     if (c_lo > c_hi || over0) {
       if (lane == 0) hull_cnt[ch_i] = over0 ? -1 : 0;
       return;
@@ -518,13 +526,14 @@ __global__ __launch_bounds__(256) void curve_blockstats_kernel(Geo g, SeqTab st,
   }
 }
 
-// A unit's chunk lists joined and filtered again, and its largest curve value.
+// A unit's chunk lists joined, filtered again and written over the first of them,
+// and its largest curve value.
 // Count -1: a chunk or the unit has too many points.
 constexpr int kMergeThreads = 256;
 __global__ __launch_bounds__(kMergeThreads) void hull_merge_kernel(
-    Geo g, SeqTab st, int32_t nblk_max, int32_t nb, int32_t nchunk_max,
-    const float* __restrict__ cmaxb, const uint2* __restrict__ hull_pts, const int32_t* __restrict__ hull_cnt,
-    uint2* __restrict__ unit_pts, int32_t* __restrict__ unit_cnt, float* __restrict__ unit_max) {
+    Geo g, SeqTab st, int32_t nblk_max, int32_t nb, const float* __restrict__ cmaxb,
+    uint2* __restrict__ hull_pts, const int32_t* __restrict__ hull_cnt,
+    int32_t* __restrict__ unit_cnt, float* __restrict__ unit_max) {
   __shared__ __align__(16) uint2 list[kMergeCap];
   __shared__ int32_t off[kLdsItems / 2 + 1];  // where each chunk's points go
   __shared__ float mx_s[kMergeThreads / 64];
@@ -536,7 +545,8 @@ __global__ __launch_bounds__(kMergeThreads) void hull_merge_kernel(
   const int64_t u = unit_index(g, l, st.first + bl, h);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int nblk = (n + kBlk - 1) / kBlk;
-  const int nchunk = (nblk + nb - 1) / nb;  // <= kLdsItems / 2
+  const int nchunk = hull_chunks(n, nb);  // <= kLdsItems / 2
+  const int64_t ch0 = hull_base(g, st, l, bl, h, nb);
   float mx = -INFINITY;
 #pragma unroll 4
   for (int k = tid; k < nblk; k += kMergeThreads) mx = fmaxf(mx, cmaxb[u * nblk_max + k]);
@@ -545,7 +555,7 @@ __global__ __launch_bounds__(kMergeThreads) void hull_merge_kernel(
   if (wave == 0) {
     int run = 0;
     for (int q0 = 0; q0 < nchunk; q0 += 64) {
-      int c = q0 + lane < nchunk ? hull_cnt[u * nchunk_max + q0 + lane] : 0;
+      int c = q0 + lane < nchunk ? hull_cnt[ch0 + q0 + lane] : 0;
       if (__ballot(c < 0) != 0ull) c = kMergeCap + 1;  // a chunk overflowed: so does the unit
       int incl = c;
 #pragma unroll
@@ -569,7 +579,7 @@ __global__ __launch_bounds__(kMergeThreads) void hull_merge_kernel(
 #pragma unroll
       for (int j = 0; j < Q; ++j) {
         const int q = min(q0 + j * W, nchunk - 1);
-        x[j] = hull_pts[(u * nchunk_max + q) * kChunkCap + lane];
+        x[j] = hull_pts[(ch0 + q) * kChunkCap + lane];
       }
 #pragma unroll
       for (int j = 0; j < Q; ++j) {
@@ -580,7 +590,7 @@ __global__ __launch_bounds__(kMergeThreads) void hull_merge_kernel(
         const int q = q0 + j * W;
         if (q < nchunk)
           for (int i = 64 + lane; i < off[q + 1] - off[q]; i += 64)
-            list[off[q] + i] = hull_pts[(u * nchunk_max + q) * kChunkCap + i];
+            list[off[q] + i] = hull_pts[(ch0 + q) * kChunkCap + i];
       }
     }
   }
@@ -589,7 +599,7 @@ __global__ __launch_bounds__(kMergeThreads) void hull_merge_kernel(
   if (fits) m = hull_filter(list, m, 6, lane);
   const bool over = !fits || m > kUnitCap;
   if (!over)
-    for (int i = lane; i < m; i += 64) unit_pts[u * kUnitCap + i] = list[i];
+    for (int i = lane; i < m; i += 64) hull_pts[ch0 * kChunkCap + i] = list[i];
   if (lane == 0) {
     unit_cnt[u] = over ? -1 : m;
     for (int w = 0; w < kMergeThreads / 64; ++w) mx = fmaxf(mx, mx_s[w]);
@@ -602,7 +612,7 @@ __global__ __launch_bounds__(kMergeThreads) void hull_merge_kernel(
 // barrier.
 __global__ __launch_bounds__(kAllocThreads) void allocate_hull_kernel(
     Geo g, SeqTab st, const float* __restrict__ curves, const double* __restrict__ dmax,
-    int32_t nblk_max, int32_t steps, const uint2* __restrict__ unit_pts,
+    int32_t nblk_max, int32_t nb, int32_t steps, const uint2* __restrict__ hull_pts,
     const int32_t* __restrict__ unit_cnt, const float* __restrict__ unit_max,
     int32_t* __restrict__ budgets, int64_t* __restrict__ stats, int32_t* __restrict__ done) {
   // hull points; then block running maxima, and blocks of running maxima
@@ -649,10 +659,12 @@ __global__ __launch_bounds__(kAllocThreads) void allocate_hull_kernel(
   }
   uint2* pts = reinterpret_cast<uint2*>(pool);
   __syncthreads();
+  const int64_t ch0 = hull_base(g, st, l, bl, 0, nb), per_head = (int64_t)hull_chunks(n, nb) * g.L;
   for (int h = wave; h < H; h += kAllocWaves) {
     const int m = cnt_s[h];
+    const uint2* p = hull_pts + (ch0 + h * per_head) * kChunkCap;
 #pragma unroll 4
-    for (int i = lane; i < m; i += 64) pts[off_s[h] + i] = unit_pts[(u0 + h) * kUnitCap + i];
+    for (int i = lane; i < m; i += 64) pts[off_s[h] + i] = p[i];
   }
   __syncthreads();
 
@@ -1973,19 +1985,18 @@ certkv_status run_allocate(const AllocArgs& a, const SeqTab& st, hipStream_t s) 
 #define CERTKV_BLOCKSTATS(HULL, NB)                                                                \
   CERTKV_LAUNCH("curve_blockstats", (curve_blockstats_kernel<HULL, NB>), bgrid, dim3(256), 0, s,   \
                 a.g, st, a.nblk_max, a.curves, a.cmin, a.cmaxb, a.cpos, a.dmax, sync,              \
-                (int32_t)kSyncArg, nchunk, a.hull_pts, a.hull_cnt)
+                (int32_t)kSyncArg, a.hull_pts, a.hull_cnt)
   if (hull) {
     if (nb == 8)
       CERTKV_BLOCKSTATS(true, 8);
     else
       CERTKV_BLOCKSTATS(true, 2);
     CERTKV_LAUNCH("hull_merge", hull_merge_kernel, dim3(a.g.H * st.count, a.g.L),
-                  dim3(kMergeThreads), 0, s, a.g, st, a.nblk_max, nb, nchunk,
-                  (const float*)a.cmaxb, (const uint2*)a.hull_pts, (const int32_t*)a.hull_cnt,
-                  a.unit_pts, a.unit_cnt, a.unit_max);
+                  dim3(kMergeThreads), 0, s, a.g, st, a.nblk_max, nb, (const float*)a.cmaxb,
+                  a.hull_pts, (const int32_t*)a.hull_cnt, a.unit_cnt, a.unit_max);
     CERTKV_LAUNCH("allocate_hull", allocate_hull_kernel, dim3(st.count, a.g.L), dim3(kAllocThreads),
-                  0, s, a.g, st, a.curves, (const double*)a.dmax, a.nblk_max, a.steps,
-                  (const uint2*)a.unit_pts, (const int32_t*)a.unit_cnt, (const float*)a.unit_max,
+                  0, s, a.g, st, a.curves, (const double*)a.dmax, a.nblk_max, nb, a.steps,
+                  (const uint2*)a.hull_pts, (const int32_t*)a.unit_cnt, (const float*)a.unit_max,
                   a.budgets, a.repairs, a.done);
   } else {
     CERTKV_BLOCKSTATS(false, 8);

@@ -65,7 +65,6 @@ struct Plan {
   int seg_chunks;    // curves: chunks per segment
   int nseg_max;      // curves: segments of the longest sequence (1: unsplit)
   int sort_nb;       // sort: buckets of the longest sequence (0: not split)
-  int sort_ntile;    // sort: tiles of the longest sequence
   int alloc;         // allocator: 0 Lagrangian + repair, 1 uniform, 2 greedy marginal
   const int64_t* cu;
 };
@@ -223,7 +222,6 @@ static certkv_status make_plan(const certkv_problem* p, Plan* pl) {
   }
   curve_split(P);
   P.sort_nb = sort_buckets(P);
-  P.sort_ntile = (int)(((int64_t)max_len + kSortRun - 1) / kSortRun);
   return CERTKV_OK;
 }
 
@@ -323,7 +321,7 @@ struct Bufs {
   double* segtot = nullptr;
   int64_t* repairs = nullptr;
   int32_t* alloc_sync = nullptr;
-  uint2 *hull_pts = nullptr, *unit_pts = nullptr;
+  uint2* hull_pts = nullptr;
   int32_t *hull_cnt = nullptr, *unit_cnt = nullptr, *alloc_done = nullptr;
   float* unit_max = nullptr;
   // select / tail
@@ -387,11 +385,13 @@ static size_t layout(const Plan& P, uint32_t need, void* ws, Bufs* b) {
     b->valsB = w.take<int32_t>(LHT);
     b->ssum = w.take<double>((size_t)P.U);
     if (P.sort_nb > 1) {
-      b->splitters = w.take<uint64_t>((size_t)P.U * P.sort_nb);
-      b->windows = w.take<uint2>((size_t)P.U * P.sort_nb);
-      b->sort_counts = w.take<uint32_t>((size_t)P.U * P.sort_ntile * P.sort_nb);
-      b->bucket_start = w.take<uint32_t>((size_t)P.U * (P.sort_nb + 1));
-      b->tile_sum = w.take<double>((size_t)P.U * P.sort_ntile);
+      const size_t nbs = launch_parts(P, [](int n) { return sort_nb(n); });
+      const size_t tiles = launch_parts(P, [](int n) { return sort_tiles(n); });
+      b->splitters = w.take<uint64_t>(nbs);
+      b->windows = w.take<uint2>(nbs);
+      b->sort_counts = w.take<uint32_t>(tiles * P.sort_nb);
+      b->bucket_start = w.take<uint32_t>(nbs);
+      b->tile_sum = w.take<double>(tiles);
     }
   }
   if (need & NEED_PERM) b->perm = w.take<int32_t>(LHT);
@@ -405,10 +405,11 @@ static size_t layout(const Plan& P, uint32_t need, void* ws, Bufs* b) {
     b->dmax = w.take<double>((size_t)P.U * P.nblk_max);
     b->repairs = w.take<int64_t>((size_t)P.g.L * P.g.B * 3);
     b->alloc_sync = w.take<int32_t>(alloc_sync_words());
-    const size_t chunks = (size_t)P.U * ((P.nblk_max + P.chunk_blocks - 1) / P.chunk_blocks);
+    const size_t chunks = launch_parts(P, [&](int n) {
+      return ((n + 255) / 256 + P.chunk_blocks - 1) / P.chunk_blocks;
+    });
     b->hull_pts = w.take<uint2>(chunks * alloc_chunk_points());
     b->hull_cnt = w.take<int32_t>(chunks);
-    b->unit_pts = w.take<uint2>((size_t)P.U * alloc_unit_points());
     b->unit_cnt = w.take<int32_t>((size_t)P.U);
     b->unit_max = w.take<float>((size_t)P.U);
     b->alloc_done = w.take<int32_t>((size_t)P.g.L * P.g.B);
@@ -503,7 +504,6 @@ static certkv_status do_sort(const Plan& P, const float* scores, int32_t* perm, 
   a.perm_out = perm;
   a.ssum = w.ssum;
   a.nb_max = P.sort_nb;
-  a.ntile_max = P.sort_ntile;
   a.splitters = w.splitters;
   a.windows = w.windows;
   a.counts = w.sort_counts;
@@ -549,7 +549,6 @@ static certkv_status do_allocate(const Plan& P, const float* curves, const int32
   a.chunk_blocks = P.chunk_blocks;
   a.hull_pts = w.hull_pts;
   a.hull_cnt = w.hull_cnt;
-  a.unit_pts = w.unit_pts;
   a.unit_cnt = w.unit_cnt;
   a.unit_max = w.unit_max;
   a.done = w.alloc_done;

@@ -111,6 +111,11 @@ __device__ __forceinline__ int64_t part_base(const Geo& g, const SeqTab& st, int
   const int p = parts(bl);
   return (c * g.H + (int64_t)h * p) * g.L + (int64_t)l * p;
 }
+// The same for the unit of item x of a launch that locate_part numbers by those
+// parts: its part of the unit's p.
+__device__ __forceinline__ int64_t part_base_of(const Geo& g, int l, int x, int part, int p) {
+  return (int64_t)(x - part) * g.L + (int64_t)l * p;
+}
 
 // Raw buffer resource over [base, base + bytes): loads through it take a
 // uniform 64-bit base and a 32-bit per-lane byte offset, and return zero for

@@ -44,11 +44,6 @@
 
 namespace certkv {
 
-// Tiles of a unit of n elements.
-__host__ __device__ inline int sort_tiles(int n) {
-  return (int)(((int64_t)n + kSortRun - 1) / kSortRun);
-}
-
 constexpr int kSortThreads = 1024;
 constexpr int kSortWaves = kSortThreads / 64;
 constexpr int kSortRounds = 8;
@@ -633,16 +628,17 @@ __global__ __launch_bounds__(kSortThreads) void sort_small_kernel(
 // and leave the rest in a few buckets that outgrow LDS (256 units of 131072, every
 // 64th score low: a selection 24980 us, 677 so; 720 with one workgroup per unit).
 __device__ __forceinline__ int sort_sample(int i, int n, int ns) {
-  const int lo = (int)((int64_t)i * n / ns), hi = (int)((int64_t)(i + 1) * n / ns);
+  // (below 2^31: at most 4096 samples of 262144 positions)
+  const uint32_t lo = (uint32_t)i * n / ns, hi = (uint32_t)(i + 1) * n / ns;
   uint32_t x = (uint32_t)i * 0x9e3779b1u;
   x = (x ^ x >> 15) * 0x2c1b3c6du;
   x ^= x >> 13;
-  return lo + (int)__umulhi(x, (uint32_t)(hi - lo));
+  return (int)(lo + __umulhi(x, hi - lo));
 }
 
 __global__ __launch_bounds__(kSortThreads) void sort_splitters_kernel(
-    Geo g, SeqTab st, int32_t nb_max, const float* __restrict__ scores,
-    uint64_t* __restrict__ splitters, uint2* __restrict__ windows) {
+    Geo g, SeqTab st, const float* __restrict__ scores, uint64_t* __restrict__ splitters,
+    uint2* __restrict__ windows) {
   __shared__ OrderLds so;
   const int h = blockIdx.x % g.H;
   const int bl = blockIdx.x / g.H;
@@ -652,7 +648,6 @@ __global__ __launch_bounds__(kSortThreads) void sort_splitters_kernel(
   const int nb = sort_nb(n);
   if (nb <= 1) return;
   const int64_t base = lht_base(g, l, h, st.start[bl]);
-  const int64_t u = unit_index(g, l, st.first + bl, h);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wkeep = n - g.keep_w;
   const int ns = nb * kSortOver;  // <= kSortRun, < n
@@ -671,11 +666,12 @@ __global__ __launch_bounds__(kSortThreads) void sort_splitters_kernel(
   const CellMap cm = cells_around_mean(so, key, desc_key(scores[base]), R, ns, lane, wave);
   lds_order(so, key, val, cm, R, ns, lane, wave);
   if (threadIdx.x < nb) {
+    const int64_t b0 = part_base(g, st, l, bl, h, [&](int i) { return sort_nb(st.len[i]); });
     const int i = threadIdx.x * kSortOver;
-    if (threadIdx.x > 0) splitters[u * nb_max + threadIdx.x - 1] = so.word[i];
+    if (threadIdx.x > 0) splitters[b0 + threadIdx.x - 1] = so.word[i];
     // the second and the second to last sample of the bucket: its cells reach
     // as far again on either side (one stray sample doesn't widen them)
-    windows[u * nb_max + threadIdx.x] = make_uint2((uint32_t)(so.word[i + 1] >> 32),
+    windows[b0 + threadIdx.x] = make_uint2((uint32_t)(so.word[i + 1] >> 32),
                                                    (uint32_t)(so.word[i + kSortOver - 2] >> 32));
   }
 }
@@ -683,7 +679,7 @@ __global__ __launch_bounds__(kSortThreads) void sort_splitters_kernel(
 // Buckets of a tile's elements (8 bits each, to ids) and their counts, and the
 // tile's sum of (s)_+.
 __global__ __launch_bounds__(kSortThreads) void sort_count_kernel(
-    Geo g, SeqTab st, int32_t ntile_max, int32_t nb_max, const float* __restrict__ scores,
+    Geo g, SeqTab st, int32_t nb_max, const float* __restrict__ scores,
     const uint64_t* __restrict__ splitters, uint8_t* __restrict__ ids,
     uint32_t* __restrict__ counts, double* __restrict__ tile_sum) {
   __shared__ uint64_t sp[256];
@@ -698,7 +694,8 @@ __global__ __launch_bounds__(kSortThreads) void sort_count_kernel(
   const int e0 = tile * kSortRun;
   const int nb = sort_nb(n);
   const int64_t base = lht_base(g, l, h, st.start[bl]);
-  const int64_t u = unit_index(g, l, st.first + bl, h);
+  const int64_t b0 = part_base(g, st, l, bl, h, [&](int i) { return sort_nb(st.len[i]); });
+  const int64_t t0 = part_base_of(g, l, blockIdx.x, tile, sort_tiles(n));
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wkeep = n - g.keep_w;
   const BufRsrc srs = make_rsrc(scores + base, (uint32_t)n * 4u);
@@ -707,7 +704,7 @@ __global__ __launch_bounds__(kSortThreads) void sort_count_kernel(
   for (int r = 0; r < kRunRounds; ++r)
     raw[r] = buf_load_u32(srs, (uint32_t)(e0 + r * kSortThreads + tid) * 4u);
   if (tid < nb) {
-    sp[tid] = tid < nb - 1 ? splitters[u * nb_max + tid] : ~0ull;
+    sp[tid] = tid < nb - 1 ? splitters[b0 + tid] : ~0ull;
     cnt_s[tid] = 0u;
   }
   __syncthreads();
@@ -730,14 +727,14 @@ __global__ __launch_bounds__(kSortThreads) void sort_count_kernel(
     }
   }
   const double t = block_sum(psum, red, lane, wave);  // past a barrier: the counts are whole
-  if (tid == 0) tile_sum[u * ntile_max + tile] = t;
-  if (tid < nb) counts[(u * ntile_max + tile) * nb_max + tid] = cnt_s[tid];
+  if (tid == 0) tile_sum[t0 + tile] = t;
+  if (tid < nb) counts[(t0 + tile) * nb_max + tid] = cnt_s[tid];
 }
 
 // Elements of a tile to their buckets, in position order: ranks by bucket as
 // in a radix pass, staged bucket-major so that runs are written together.
 __global__ __launch_bounds__(kSortThreads) void sort_scatter_kernel(
-    Geo g, SeqTab st, int32_t ntile_max, int32_t nb_max, const float* __restrict__ scores,
+    Geo g, SeqTab st, int32_t nb_max, const float* __restrict__ scores,
     const uint8_t* __restrict__ ids, const uint32_t* __restrict__ counts,
     const double* __restrict__ tile_sum, uint32_t* __restrict__ keys, int32_t* __restrict__ vals,
     uint32_t* __restrict__ bucket_start, double* __restrict__ ssum_out) {
@@ -754,10 +751,11 @@ __global__ __launch_bounds__(kSortThreads) void sort_scatter_kernel(
   const int n = st.len[bl];
   const int e0 = tile * kSortRun;
   const int nb = sort_nb(n);
-  const int ntile = (n + kSortRun - 1) / kSortRun;
+  const int ntile = sort_tiles(n);
   const int cnt = min(kSortRun, n - e0);
   const int64_t base = lht_base(g, l, h, st.start[bl]);
   const int64_t u = unit_index(g, l, st.first + bl, h);
+  const int64_t t0 = part_base_of(g, l, blockIdx.x, tile, ntile);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wkeep = n - g.keep_w;
   uint32_t raw[kRunRounds], dg[kRunRounds], lp[kRunRounds];
@@ -772,7 +770,7 @@ __global__ __launch_bounds__(kSortThreads) void sort_scatter_kernel(
   if (tid < 256) {
     uint32_t all = 0u, bef = 0u;
     if (tid < nb) {
-      const uint32_t* c = counts + u * ntile_max * (int64_t)nb_max + tid;
+      const uint32_t* c = counts + t0 * nb_max + tid;
 #pragma unroll 8
       for (int t = 0; t < ntile; ++t) {
         const uint32_t x = c[(int64_t)t * nb_max];
@@ -808,11 +806,11 @@ __global__ __launch_bounds__(kSortThreads) void sort_scatter_kernel(
     }
   }
   if (tile == 0) {
-    if (tid < nb) bucket_start[u * (nb_max + 1) + tid] = bstart[tid];
-    if (tid == 0) bucket_start[u * (nb_max + 1) + nb] = (uint32_t)n;
+    const int64_t b0 = part_base(g, st, l, bl, h, [&](int i) { return sort_nb(st.len[i]); });
+    if (tid < nb) bucket_start[b0 + tid] = bstart[tid];
     if (wave == 1) {
       double x = 0.0;
-      for (int t = lane; t < ntile; t += 64) x += tile_sum[u * ntile_max + t];
+      for (int t = lane; t < ntile; t += 64) x += tile_sum[t0 + t];
       x = wave_sum(x);
       if (lane == 0) ssum_out[u] = x;
     }
@@ -822,7 +820,7 @@ __global__ __launch_bounds__(kSortThreads) void sort_scatter_kernel(
 // (eight waves per SIMD: two workgroups to a compute unit)
 __global__ __launch_bounds__(kSortThreads)
 __attribute__((amdgpu_waves_per_eu(8, 8))) void sort_buckets_kernel(
-    Geo g, SeqTab st, int32_t nb_max, const float* __restrict__ scores,
+    Geo g, SeqTab st, const float* __restrict__ scores,
     uint32_t* __restrict__ keys_in, int32_t* __restrict__ vals_in,
     const uint32_t* __restrict__ bucket_start, const uint2* __restrict__ windows,
     uint32_t* __restrict__ keys_out, int32_t* __restrict__ perm_out) {
@@ -837,9 +835,9 @@ __attribute__((amdgpu_waves_per_eu(8, 8))) void sort_buckets_kernel(
   const int n = st.len[bl];
   const int nb = sort_nb(n);
   const int64_t base = lht_base(g, l, h, st.start[bl]);
-  const int64_t u = unit_index(g, l, st.first + bl, h);
-  const int lo = (int)bucket_start[u * (nb_max + 1) + bk];
-  const int m = (int)bucket_start[u * (nb_max + 1) + bk + 1] - lo;
+  const int64_t b0 = part_base_of(g, l, blockIdx.x, bk, nb);
+  const int lo = (int)bucket_start[b0 + bk];
+  const int m = (bk + 1 < nb ? (int)bucket_start[b0 + bk + 1] : n) - lo;
   if (m <= 0) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wkeep = n - g.keep_w;
@@ -864,7 +862,7 @@ __attribute__((amdgpu_waves_per_eu(8, 8))) void sort_buckets_kernel(
     }
     CellMap cm;
     if (nb > 1) {
-      const uint2 w = windows[u * nb_max + bk];
+      const uint2 w = windows[b0 + bk];
       const float span = (float)(w.y - w.x);
       cm = CellMap{w.x, -span, (float)kCells / (3.f * span + 1.f)};
     } else {
@@ -937,16 +935,16 @@ certkv_status run_sort(const SortArgs& a, const SeqTab& st, hipStream_t s) {
   uint8_t* ids = reinterpret_cast<uint8_t*>(a.valsA);  // dead before the buckets are written
   const dim3 tiles(count_parts(g, st, [&](int i) { return sort_tiles(st.len[i]); }), g.L);
   CERTKV_LAUNCH("sort_splitters", sort_splitters_kernel, units, dim3(kSortThreads), 0, s, g, st,
-                a.nb_max, a.scores, a.splitters, a.windows);
+                a.scores, a.splitters, a.windows);
   CERTKV_LAUNCH("sort_count", sort_count_kernel, tiles, dim3(kSortThreads), 0, s, g, st,
-                a.ntile_max, a.nb_max, a.scores, (const uint64_t*)a.splitters, ids, a.counts,
+                a.nb_max, a.scores, (const uint64_t*)a.splitters, ids, a.counts,
                 a.tile_sum);
   CERTKV_LAUNCH("sort_scatter", sort_scatter_kernel, tiles, dim3(kSortThreads), 0, s, g, st,
-                a.ntile_max, a.nb_max, a.scores, (const uint8_t*)ids, (const uint32_t*)a.counts,
+                a.nb_max, a.scores, (const uint8_t*)ids, (const uint32_t*)a.counts,
                 (const double*)a.tile_sum, a.keysB, a.valsB, a.bucket_start, a.ssum);
   CERTKV_LAUNCH("sort_buckets", sort_buckets_kernel,
                 dim3(count_parts(g, st, [&](int i) { return sort_nb(st.len[i]); }), g.L),
-                dim3(kSortThreads), 0, s, g, st, a.nb_max, a.scores, a.keysB, a.valsB,
+                dim3(kSortThreads), 0, s, g, st, a.scores, a.keysB, a.valsB,
                 (const uint32_t*)a.bucket_start, (const uint2*)a.windows, a.keys_out, a.perm_out);
   return CERTKV_OK;
 }

@@ -40,6 +40,10 @@ constexpr int kSortNb = kSortRun / kSortOver;  // buckets of a unit at most
 __host__ __device__ inline int sort_nb(int n) {
   return n <= kSortRun ? 1 : (int)((2 * (int64_t)n + kSortRun - 1) / kSortRun);
 }
+// Tiles of a unit of n elements.
+__host__ __device__ inline int sort_tiles(int n) {
+  return (int)(((int64_t)n + kSortRun - 1) / kSortRun);
+}
 struct SortArgs {
   Geo g;
   const float* scores;
@@ -49,12 +53,12 @@ struct SortArgs {
   // split by value into buckets (nb_max = buckets of the longest sequence; 1:
   // every unit fits one LDS sort; 0: one workgroup sorts a unit through memory)
   int32_t nb_max;
-  int32_t ntile_max;         // tiles of kSortRun elements of the longest sequence
-  uint64_t* splitters;       // [U][nb_max]
-  uint2* windows;            // [U][nb_max] keys that most of a bucket lies between
-  uint32_t* counts;          // [U][ntile_max][nb_max]
-  uint32_t* bucket_start;    // [U][nb_max + 1]
-  double* tile_sum;          // [U][ntile_max]
+  // one entry per bucket, or per tile of kSortRun elements, of the launch (part_base)
+  uint64_t* splitters;       // per bucket
+  uint2* windows;            // per bucket: keys that most of it lies between
+  uint32_t* counts;          // per tile, [nb_max]
+  uint32_t* bucket_start;    // per bucket
+  double* tile_sum;          // per tile
 };
 certkv_status run_sort(const SortArgs& a, const SeqTab& st, hipStream_t s);
 
@@ -87,16 +91,14 @@ struct AllocArgs {
   int64_t* repairs;
   int32_t* sync;    // alloc_sync_words() words: cross-workgroup bisection (optional)
   int32_t chunk_blocks;  // blocks per chunk of the hull filter: 2 or 8
-  uint2* hull_pts;   // [U][chunks][alloc_chunk_points()] hull points of the chunks
-  int32_t* hull_cnt; // [U][chunks]
-  uint2* unit_pts;   // [U][alloc_unit_points()] hull points of the units
+  uint2* hull_pts;   // per chunk, [alloc_chunk_points()]: its hull points, then its unit's
+  int32_t* hull_cnt; // per chunk (of the launch: part_base)
   int32_t* unit_cnt; // [U]
   float* unit_max;   // [U]
   int32_t* done;     // [L*B] set where the hull kernel allocated
 };
 size_t alloc_sync_words();
 size_t alloc_chunk_points();
-size_t alloc_unit_points();
 certkv_status run_allocate(const AllocArgs& a, const SeqTab& st, hipStream_t s);
 
 // Units up to which the selection sums the offsets by itself: a launch of one

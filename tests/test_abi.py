@@ -111,6 +111,24 @@ def test_score_workspace_of_ragged_batches(L, H, G, w, seqlens, mib):
                                     None) == _lib.CERTKV_OK
 
 
+@pytest.mark.parametrize("L,seqlens,allocate,select,compress", [
+    (1, (159000,) + (1000,) * 99, 31, 20, 118),
+    (32, (131072,) + (512,) * 255, 2340, 1285, 12130),  # (bitmaps and curve statistics of the longest)
+    (32, (512,) * 256, 786, 641, 1260),
+    (32, (4096,) * 8, 210, 161, 230),
+    (1, (32768,), 8, 5.1, 11),
+])
+def test_workspaces_of_ragged_batches(L, seqlens, allocate, select, compress):
+    # MiB of the stages: the sort's and the allocation's arrays follow the buckets,
+    # tiles and chunks that exist, not the longest sequence's for every unit.
+    lib = _lib.lib()
+    H = 4 if len(seqlens) == 100 else 8
+    p = problem(L=L, seqlens=seqlens, H=H, G=8 if H == 4 else 4, w=64)
+    for stage, mib in ((_lib.STAGE_ALLOCATE, allocate), (_lib.STAGE_SELECT, select),
+                       (_lib.STAGE_COMPRESS, compress)):
+        assert lib.certkv_workspace_size(ctypes.byref(p), stage) <= mib * 2 ** 20, stage
+
+
 def test_dry_run_allocate_budget_checks():
     L = _lib.lib()
     p = problem()
