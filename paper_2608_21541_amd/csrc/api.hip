@@ -95,14 +95,22 @@ static void curve_split(Plan& P) {
   P.seg_chunks = (int)max_nch;
   P.nseg_max = 1;
   if (P.U > kCUs) return;
-  for (int64_t sc = (total * LH + kCUs - 1) / kCUs; 16 * sc + 10 < 9 * max_nch; ++sc) {
+  // (longer segments are never more workgroups: the shortest that fit are found by
+  // halving, since a call makes its plan anew)
+  int64_t lo = (total * LH + kCUs - 1) / kCUs, end = (9 * max_nch - 10 + 15) / 16;
+  const int64_t worth = end;  // from here on a split costs what it saves: 16 sc + 10 >= 9 max_nch
+  while (lo < end) {
+    const int64_t sc = (lo + end) / 2;
     int64_t wgs = 0;
     for (int b = 0; b < P.g.B; ++b) wgs += (chunks(b) + sc - 1) / sc;
-    if (wgs * LH > kCUs) continue;
-    P.seg_chunks = (int)sc;
-    P.nseg_max = (int)((max_nch + sc - 1) / sc);
-    return;
+    if (wgs * LH > kCUs)
+      lo = sc + 1;
+    else
+      end = sc;
   }
+  if (lo >= worth) return;
+  P.seg_chunks = (int)lo;
+  P.nseg_max = (int)((max_nch + lo - 1) / lo);
 }
 
 // Buckets of the longest sequence for the sort (see sort.hip); 0: one

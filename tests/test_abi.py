@@ -4,6 +4,7 @@ launched, so these run without a GPU)."""
 import ctypes
 import os
 import re
+import time
 
 import pytest
 
@@ -127,6 +128,19 @@ def test_workspaces_of_ragged_batches(L, seqlens, allocate, select, compress):
     for stage, mib in ((_lib.STAGE_ALLOCATE, allocate), (_lib.STAGE_SELECT, select),
                        (_lib.STAGE_COMPRESS, compress)):
         assert lib.certkv_workspace_size(ctypes.byref(p), stage) <= mib * 2 ** 20, stage
+
+
+def test_plan_of_a_ragged_batch_is_quick():
+    # A call makes its plan on the host: a long sequence beside many short ones took
+    # 160 us of one-by-one search for the curves' segments.
+    lib = _lib.lib()
+    p = problem(L=1, seqlens=(1 << 20,) + (512,) * 249, H=1, G=4, w=64)
+    best = 1.0
+    for _ in range(30):
+        t = time.perf_counter()
+        lib.certkv_workspace_size(ctypes.byref(p), _lib.STAGE_COMPRESS)
+        best = min(best, time.perf_counter() - t)
+    assert best < 60e-6, best
 
 
 def test_dry_run_allocate_budget_checks():
