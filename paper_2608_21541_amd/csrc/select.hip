@@ -8,6 +8,8 @@
 // the 16 waves, so kept indices come out ascending without a scatter.  The same
 // pass sums (s)_+ over the evicted keys and over all keys in fp64 (the tail mass
 // and its normalizer).
+#include <type_traits>
+
 #include "stages.h"
 
 namespace certkv {
@@ -83,6 +85,10 @@ constexpr int kSelScanPer = kSelRounds * kSelWaves / 64;  // counts per lane of 
 // a workgroup that walks the whole unit, and forms the sums.  Whole units and parts: 8 of 32768 positions
 // 19 and 15 us, 64 of 8192 to 65536 34 and 26, 24 of 9999 to 30001 without sums
 // 18 and 14.
+// Whole units, sums and the mask are compile-time forms: the tests for them in
+// the tile's rounds keep these from being scheduled together (256 units of 131072
+// positions 72 us with the tests and 64 without; with the sums, in a pass, 81 and 71).
+template <bool WHOLE, bool SUMS, bool MASK>
 __global__ __launch_bounds__(kSelThreads) void select_kernel(
     Geo g, SeqTab st, int32_t part_tiles, const float* __restrict__ scores,
     const uint32_t* __restrict__ sorted_keys, const int32_t* __restrict__ perm,
@@ -95,9 +101,10 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
   __shared__ uint32_t kcnt[kSelRounds * kSelWaves + 1];
   __shared__ double dsum[2][kSelWaves];
   __shared__ int64_t osum[kSelWaves];
-  int h, part;
-  const int bl = locate_part(g, st, blockIdx.x,
-                             [&](int x) { return sel_parts(st.len[x], part_tiles); }, h, part);
+  int h = blockIdx.x % g.H, part = 0, bl = blockIdx.x / g.H;
+  if constexpr (!WHOLE)
+    bl = locate_part(g, st, blockIdx.x, [&](int x) { return sel_parts(st.len[x], part_tiles); }, h,
+                     part);
   const int l = blockIdx.y;
   if (bl >= st.count) return;
   const int b = st.first + bl;
@@ -113,6 +120,23 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
     kthr = sorted_keys[base + bb - 1];
     ithr = perm[base + bb - 1];
   }
+  // Round r of a tile: positions j0 + 1024 r + thread, so every load covers
+  // 256 consecutive bytes per wave.  Loads through a range-checked buffer:
+  // positions past the end read as zero, so no branch sits around them and
+  // the next tile's loads stay in flight while this one is tested; they are
+  // masked where used.
+  const BufRsrc srs = make_rsrc(scores + base, (uint32_t)n * 4u);
+  auto load = [&](int j0, float (&sv)[kSelRounds]) {
+#pragma unroll
+    for (int r = 0; r < kSelRounds; ++r)
+      sv[r] = __uint_as_float(
+          buf_load_u32(srs, (uint32_t)(j0 + r * kSelThreads + (int)threadIdx.x) * 4u));
+  };
+  const int start = WHOLE ? 0 : (int)min((int64_t)part * part_tiles * kSelTile, (int64_t)n);
+  const int end = WHOLE ? n : (int)min((int64_t)(part + 1) * part_tiles * kSelTile, (int64_t)n);
+  const bool sums = SUMS && (WHOLE || end == n);  // the unit's last part
+  float cur[kSelRounds], nxt[kSelRounds];
+  load(start, cur);
   int64_t off = 0;
   if (own_offsets) {
     // the budgets before this unit's, summed by every workgroup (kSelOwnOffsets
@@ -135,18 +159,6 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
   }
   int64_t run = 0;
   double se = 0.0, sa = 0.0;
-  // Round r of a tile: positions j0 + 1024 r + thread, so every load covers
-  // 256 consecutive bytes per wave.  Loads through a range-checked buffer:
-  // positions past the end read as zero, so no branch sits around them and
-  // the next tile's loads stay in flight while this one is tested; they are
-  // masked where used.
-  const BufRsrc srs = make_rsrc(scores + base, (uint32_t)n * 4u);
-  auto load = [&](int j0, float (&sv)[kSelRounds]) {
-#pragma unroll
-    for (int r = 0; r < kSelRounds; ++r)
-      sv[r] = __uint_as_float(
-          buf_load_u32(srs, (uint32_t)(j0 + r * kSelThreads + (int)threadIdx.x) * 4u));
-  };
   // kept window keys hold ranks 0..w-1 in position order; the others are kept up
   // to the threshold pair at rank bb-1
   auto keeps = [&](int j, float x) -> bool {
@@ -154,12 +166,7 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
     return j < n && (j >= wkeep ? (j - wkeep < bb)
                                 : (bb > g.keep_w && (key < kthr || (key == kthr && j <= ithr))));
   };
-  const int start = (int)min((int64_t)part * part_tiles * kSelTile, (int64_t)n);
-  const int end = (int)min((int64_t)(part + 1) * part_tiles * kSelTile, (int64_t)n);
-  const bool sums = end == n && evicted_sum;  // the unit's last part
-  float cur[kSelRounds], nxt[kSelRounds];
-  load(start, cur);
-  if (start > 0) {
+  if (!WHOLE && start > 0) {
     uint32_t before = 0;
     float x[kSelRounds], y[kSelRounds];
     load(0, x);
@@ -199,7 +206,7 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
         se += keep ? 0.0 : sp;
       }
       bal[r] = __ballot(keep);
-      if (mask && valid) mask[base + j] = keep ? 1 : 0;  // 64 consecutive bytes per wave
+      if (MASK && valid) mask[base + j] = keep ? 1 : 0;  // 64 consecutive bytes per wave
       kmask |= (uint32_t)keep << r;
       if (lane == 0) {
         kcnt[r * kSelWaves + wave] = (uint32_t)__popcll(bal[r]);
@@ -529,11 +536,20 @@ certkv_status run_select(const SelectArgs& a, const SeqTab& st, hipStream_t s) {
   }
   const dim3 grid(count_parts(a.g, st, [&](int bl) { return sel_parts(st.len[bl], part_tiles); }),
                   a.g.L);
-  CERTKV_LAUNCH("select", select_kernel, grid, dim3(kSelThreads), 0, s, a.g, st, part_tiles,
-                a.scores, a.sorted_keys, a.perm, (const int32_t*)a.budgets,
-                a.own_offsets, a.kept_offsets, a.packed_offsets, a.kept_idx, a.capacity,
-                a.evicted_sum, a.total_sum, a.bitmap, a.bm_stride, a.mask);
-  return CERTKV_OK;
+  const auto launch = [&](auto kernel) -> certkv_status {
+    CERTKV_LAUNCH("select", kernel, grid, dim3(kSelThreads), 0, s, a.g, st, part_tiles, a.scores,
+                  a.sorted_keys, a.perm, (const int32_t*)a.budgets, a.own_offsets, a.kept_offsets,
+                  a.packed_offsets, a.kept_idx, a.capacity, a.evicted_sum, a.total_sum, a.bitmap,
+                  a.bm_stride, a.mask);
+    return CERTKV_OK;
+  };
+  const auto forms = [&](auto whole) -> certkv_status {
+    constexpr bool W = decltype(whole)::value;
+    if (a.evicted_sum)
+      return a.mask ? launch(select_kernel<W, true, true>) : launch(select_kernel<W, true, false>);
+    return a.mask ? launch(select_kernel<W, false, true>) : launch(select_kernel<W, false, false>);
+  };
+  return grid.x == (unsigned)(a.g.H * st.count) ? forms(std::true_type()) : forms(std::false_type());
 }
 
 }  // namespace certkv
