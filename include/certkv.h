@@ -353,11 +353,15 @@ certkv_status certkv_compress(const certkv_problem* p, certkv_tensor q_win,
  *   max_rows       bound on the rows of any head's segment (b_h + 1), or 0 for
  *                  n_b of the longest sequence; it sizes the workspace. A
  *                  longer segment stores CERTKV_ERANGE in *dev_status and its
- *                  rows past the next multiple of 4096 are left out
+ *                  rows past the next multiple of 4096 are left out. The
+ *                  output's bits do not depend on it
  *   k_packed, v_packed, packed_offsets  the packed cache of certkv_compact or
  *                  certkv_compress (device)
  *   out            [L][B*tq][Hq][d] fp32 out (contiguous)
  *   lse            optional [L][B*tq][Hq] fp32 out (natural log)
+ * The rows are cut into chunks by their number in the whole call, so a unit's
+ * sums are grouped differently beside other units: its output differs by the
+ * rounding of the sums (a few 1e-6 of a row's norm), in no other way.
  * Every packed row is visible to every new query (they follow the whole
  * cache).  bf16 caches only (CERTKV_EUNSUPPORTED for fp32); tq * G <= 512.
  * The workspace is certkv_decode_workspace_size(p, tq, max_rows) bytes,

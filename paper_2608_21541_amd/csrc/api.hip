@@ -857,24 +857,25 @@ static int decode_rows_bound(const Plan& P, int32_t max_rows) {
   return (max_rows > 0 && max_rows < P.max_len) ? max_rows : P.max_len;
 }
 
-// Decode workspace: split partials (output rows, then (max, sum) pairs), each
-// 256-byte aligned.
+// Decode workspace: partials (output rows, then (max, sum) pairs), each 256-byte
+// aligned.
 struct DecodeWs {
-  int keys_min;
-  int64_t cover;
-  int nsplit;
+  DecodeChunks ck;
   size_t ml_off, total;
 };
 static DecodeWs decode_ws_layout(const Plan& P, int32_t tq, int32_t max_rows) {
   auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
+  const int64_t bound = decode_rows_bound(P, max_rows);
+  int64_t rows = 0;  // of all segments: b_h <= n_b kept rows and the slot row
+  for (int b = 0; b < P.g.B; ++b) {
+    const int64_t n = P.cu[b + 1] - P.cu[b] + P.g.slot;
+    rows += n < bound ? n : bound;
+  }
   DecodeWs w;
-  w.keys_min = decode_keys_min(P.U, P.max_len, tq, P.g.G);
-  w.cover = decode_cover(decode_rows_bound(P, max_rows));
-  // (chunks are cut through the units: a unit's first and last may be partial)
-  w.nsplit = (int)(w.cover / w.keys_min) + 1;
-  const size_t rows = decode_partial_rows(P.U, w.nsplit, tq, P.g.G);
-  w.ml_off = up(rows * (size_t)P.g.D * sizeof(float));
-  w.total = up(w.ml_off + rows * sizeof(float2));
+  w.ck = decode_chunks(P.g.D, tq, P.g.G, bound, rows * P.g.L * P.g.H);
+  const size_t part = (size_t)decode_partials(w.ck, P.U) * decode_nqt(tq * P.g.G) * 32;
+  w.ml_off = up(part * (size_t)P.g.D * sizeof(float));
+  w.total = up(w.ml_off + part * sizeof(float2));
   return w;
 }
 
@@ -907,15 +908,13 @@ static certkv_status decode_impl(const certkv_problem* p, certkv_tensor q_new, i
   if (((uintptr_t)ws & 255u) != 0) return CERTKV_EINVAL;
   if (ws_bytes < need) return CERTKV_EWORKSPACE;
   const DecodeWs W = decode_ws_layout(P, tq, max_rows);
-  if ((int64_t)P.U * W.nsplit > INT32_MAX) return CERTKV_EUNSUPPORTED;
+  if (decode_partials(W.ck, P.U) > INT32_MAX) return CERTKV_EUNSUPPORTED;
   if (p->flags & CERTKV_DRY_RUN) return CERTKV_OK;
   DecodeArgs a;
   a.g = P.g;
   a.U = P.U;
   a.tq = tq;
-  a.keys_min = W.keys_min;
-  a.cover = W.cover;
-  a.nsplit = W.nsplit;
+  a.ck = W.ck;
   a.q = q_new;
   a.k_packed = k_packed;
   a.v_packed = v_packed;

@@ -8,9 +8,8 @@
 //   z_i = scale <q, k_i>,  out = sum_i softmax(z)_i v_i,  lse = log sum e^z.
 //
 // Split over keys: the packed rows are cut into chunks of the same length
-// (dec_keys), taken in a fixed stride by a persistent grid of as many
-// workgroups as stay resident; a workgroup finds the units of its chunks in the
-// packed offsets.  A workgroup holds the unit's query tiles of
+// (dec_cut), one or so for each of the workgroups that stay resident; a
+// workgroup finds the units of its chunk in the packed offsets.  A workgroup holds the unit's query tiles of
 // 32 rows, one wave each; with fewer than four tiles, two or four waves share
 // a tile and split its output dims.  Key and value tiles of 32 rows go from
 // memory straight into LDS (wave-wide 16-byte LDS-DMA loads into a ring of
@@ -26,15 +25,15 @@
 //     remainder (two MFMAs, about 16 bits of the fp32 weight), and V^T (A
 //     operand) comes from transposing LDS reads of the key-major value tile
 //     along the same key order.
-// The chunk partials (reference max, sum, unnormalized output) are combined
-// in split order by a second kernel (deterministic).
+// The partials (reference max, sum, unnormalized output) are combined in row
+// order by a second kernel (deterministic).
 #include "stages.h"
 
 namespace certkv {
 
-constexpr int kDecKeys = 4096;    // keys per chunk, as long as the workspace has slots
-constexpr int kDecKeysMin = 128;  // and at least
-constexpr int kDecTile = 32;    // keys per tile
+constexpr int kDecTileShift = 5;
+constexpr int kDecTile = 1 << kDecTileShift;  // keys per tile
+constexpr int kDecSumShift = 12;  // 4096 keys per fp32 accumulator
 
 typedef __bf16 dec_bf16x8 __attribute__((__vector_size__(8 * sizeof(__bf16))));
 typedef float dec_f32x16 __attribute__((__vector_size__(16 * sizeof(float))));
@@ -142,26 +141,77 @@ __device__ __forceinline__ uint32_t dec_lds_addr(const void* p) {
 typedef short dec_s16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) dec_s16x4 dec_lds_s16x4;
 
-// Rows per chunk.  The packed rows of all units, one after another, are cut
-// into chunks of the same length, so that a workgroup's share does not depend
-// on how the rows are spread over the heads: a chunk that crosses from one unit
-// to the next is two pieces.  With chunks cut per unit the resident workgroups
-// got one or two of 4096 keys each, or less at a unit's end: 32 layers of 8
-// heads, 3.36M rows, one query 355 us, and 338 here (287 with the loads non-temporal);
-// 32 queries 449 and 377.
-// parts workgroups are resident at once and take the same number of chunks
-// each, of at most 4096 keys, or up to twice keys_min where the workspace has no
-// slots for shorter ones (long chunks amortize the queries' load, the first
-// tiles' latency and the partials, and bound how long the fp32 sums get).  Few
-// rows leave compute units idle in such chunks and take shorter ones, of
-// keys_min at least (one layer of 26216 rows: 100 us in 4096-key chunks, 11 us
-// in 128-key ones).
-__device__ __forceinline__ int dec_keys(int64_t rows, int keys_min, int parts) {
-  if (rows < (int64_t)parts * keys_min) return keys_min;
-  const int64_t rounds = min((rows + (int64_t)parts * kDecKeys - 1) / ((int64_t)parts * kDecKeys),
-                             rows / ((int64_t)parts * keys_min));  // both 1 or more
-  const int64_t k = (rows + parts * rounds - 1) / (parts * rounds);
-  return (int)((k + kDecTile - 1) / kDecTile) * kDecTile;
+// The packed rows of all units, one after another, are cut into as many chunks
+// of the same length as workgroups are resident at once, so that every one gets the
+// same share however the rows are spread over the units: a chunk that crosses from
+// one unit to the next is two pieces.  Microseconds with chunks of 4096 keys cut
+// per unit, and so: 32 layers of 8 heads, 3.36M rows, one query 363 and 278; 12
+// layers of three sequences, 144 units, 618k rows 109 and 70; 7 layers of eight,
+// 896 units of 64 dims, 722k rows, 32 query rows 151 and 81; one layer of 26216 rows, in
+// 128-key chunks, the shortest, 105 and 15.
+// Chunks depend on the rows of the whole call, so a row's sums are grouped, and
+// rounded, differently beside other units.
+// A piece longer than 4096 rows writes a partial for every 4096 of them, the
+// bound on how long an fp32 sum gets (3.36M rows, sums of up to 6592: errors against
+// 64 bits 0.2 to 0.4 % larger), while its loads run on: in two chunks one after the
+// other, with the loads drained between them, the same rows take 5 % longer.
+// (Rows are counted in 32 bits, which divide in a few instructions: 2^31 rows of 64
+// dims are 512 GB.)
+struct DecCut {
+  uint32_t keys;  // rows per chunk
+  int sum_shift;  // log2 of the rows per partial
+  // partials of that many rows of one piece
+  __device__ __forceinline__ uint32_t partials(uint32_t rows) const {
+    return (rows + (1u << sum_shift) - 1u) >> sum_shift;
+  }
+};
+__device__ __forceinline__ DecCut dec_cut(const DecodeChunks& c, uint32_t rows, int64_t U) {
+  // With few rows the fixed cost of a piece (its queries, first tile and partials)
+  // outweighs them.  Then the chunks are fewer by the units' starts, so that every
+  // piece is a workgroup's only one: two of them per compute unit up to 1024 keys
+  // each, one up to 512 where the units are few (128 units of 64 dims, 131k rows, 64
+  // query rows: chunks of 128, 160, 352 keys 40, 41, 33 us; 32 units of 128 dims,
+  // 105k rows 41 us in chunks of 224, 34 of 480; of 1676 keys, 144 units: 70 us in
+  // 512 chunks, 76 in 369).
+  // (From the rows and not from the caller's bound on them: the chunks, and so the
+  // bits, are the same under any bound.)
+  constexpr uint32_t kOne = 256, kTwo = 512;
+  const uint32_t two = min((uint32_t)c.parts, kTwo);
+  uint32_t n = (uint32_t)c.parts;
+  if (n > kOne && 4 * U <= kOne && rows <= (kOne - (uint32_t)U + 1u) * 512u)
+    n = kOne - (uint32_t)U + 1u;
+  else if (2 * U <= two && rows <= (two - (uint32_t)U + 1u) * 1024u)
+    n = two - (uint32_t)U + 1u;
+  uint32_t k = rows <= n * (uint32_t)c.keys_min ? (uint32_t)c.keys_min : (rows + n - 1u) / n;
+  // (more rows than the bound allows for: longer chunks and sums, so that the
+  // partials stay within the workspace)
+  if (rows > (uint64_t)c.most * k) k = (rows + (uint32_t)c.most - 1u) / (uint32_t)c.most;
+  DecCut cut{(k + kDecTile - 1u) & ~(uint32_t)(kDecTile - 1), kDecSumShift};
+  while ((rows >> cut.sum_shift) > (uint32_t)c.sums) ++cut.sum_shift;
+  return cut;
+}
+
+// Partials: those of a unit lie one after the other, its first at this place,
+// where s0 is the chunk of its first row, `at` rows after the first unit's.  A unit
+// of len rows has a piece for each of its chunks and at most len >> sum_shift
+// partials beyond one for each, so that it ends before the next one's place.
+__device__ __forceinline__ uint32_t dec_place(const DecCut& cut, uint32_t at, uint32_t s0,
+                                              uint32_t u) {
+  return (at >> cut.sum_shift) + s0 + u;
+}
+// Rows of the first piece of a unit of len rows.
+__device__ __forceinline__ uint32_t dec_first(const DecCut& cut, uint32_t at, uint32_t s0,
+                                              uint32_t len) {
+  return min(len, (s0 + 1u) * cut.keys - at);
+}
+// Partials of a unit whose first len rows are attended.
+__device__ __forceinline__ uint32_t dec_partials(const DecCut& cut, uint32_t at, uint32_t s0,
+                                                 uint32_t len) {
+  const uint32_t first = dec_first(cut, at, s0, len), rest = len - first;
+  if (rest == 0) return cut.partials(first);
+  const uint32_t whole = rest / cut.keys;
+  return cut.partials(first) + whole * cut.partials(cut.keys) +
+         cut.partials(rest - whole * cut.keys);
 }
 
 // x of lane i (wave-uniform).
@@ -169,11 +219,6 @@ __device__ __forceinline__ int64_t dec_readlane(int64_t x, int i) {
   const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)x, i);
   const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)((uint64_t)x >> 32), i);
   return (int64_t)(((uint64_t)hi << 32) | lo);
-}
-
-// Pieces of a unit whose len rows start at packed row p0.
-__device__ __forceinline__ int dec_pieces(int64_t p0, int64_t len, int keys) {
-  return len > 0 ? (int)((p0 + len - 1) / keys - p0 / keys) + 1 : 0;
 }
 
 // The unit that holds packed row r (counted from the first unit's), by a wave:
@@ -193,8 +238,7 @@ __device__ __forceinline__ int dec_find_unit(const int64_t* __restrict__ poff, i
 
 template <int D, int NQT>
 __device__ __forceinline__ void decode_body(
-    const Geo& g, int64_t U, int64_t cover, int32_t keys_min, int32_t parts, int32_t tq,
-    int32_t nsplit, int32_t mp,
+    const Geo& g, int64_t U, const DecodeChunks& ck, int32_t tq, int32_t mp,
     const uint16_t* __restrict__ qn, int64_t q_sl, int64_t q_st, int64_t q_sh,
     const uint16_t* __restrict__ kp, const uint16_t* __restrict__ vp,
     const int64_t* __restrict__ poff, float* __restrict__ part_o, float2* __restrict__ part_ml) {
@@ -214,7 +258,8 @@ __device__ __forceinline__ void decode_body(
   // A persistent grid over the chunks, and in each over the units it meets.
   // Up to 64 units: their segments in the lanes of every wave, so that a piece
   // waits for one load before its queries and tiles, not for three in turn.
-  const bool few = U <= 64;
+  // (Not with eight query tiles and more, whose registers are all taken.)
+  const bool few = NQT < 8 && U <= 64;
   const int lane = threadIdx.x & 63;
   int64_t ps = 0, pe = 0;
   if (few) {
@@ -224,15 +269,16 @@ __device__ __forceinline__ void decode_body(
   auto seg_start = [&](int64_t u) { return few ? dec_readlane(ps, (int)u) : poff[u]; };
   auto seg_end = [&](int64_t u) { return few ? dec_readlane(pe, (int)u) : poff[u + 1]; };
   const int64_t base = seg_start(0), rows = seg_end(U - 1) - base;
-  const int keys = dec_keys(rows, keys_min, parts);
+  const DecCut cut = dec_cut(ck, (uint32_t)rows, U);
+  const int keys = (int)cut.keys;
   // Where the grid has workgroups left for the units' first pieces, those that
   // start inside a chunk are theirs, and no workgroup takes two pieces in turn.
-  const int64_t nch = (rows + keys - 1) / keys;
+  const int64_t nch = ((uint32_t)rows + cut.keys - 1u) / cut.keys;
   const bool heads = nch + U - 1 <= gridDim.x;
   for (int64_t x = blockIdx.x; x < (heads ? nch + U - 1 : nch); x += gridDim.x) {
   const int64_t head = x - nch + 1;  // from 1: the unit whose first piece is taken
   const int64_t r0 = x < nch ? x * keys : seg_start(head) - base;
-  const int64_t s = x < nch ? x : r0 / keys, r1 = min(rows, (s + 1) * keys);
+  const int64_t s = x < nch ? x : (uint32_t)r0 / cut.keys, r1 = min(rows, (s + 1) * keys);
   if (x >= nch && r0 == s * keys) continue;  // a chunk's first piece
   const uint64_t past = __ballot(pe - base > r0);
   const int64_t u0 = x >= nch ? head
@@ -243,9 +289,8 @@ __device__ __forceinline__ void decode_body(
   if (at >= r1) break;
   const int len = (int)(seg_end(u) - p0);
   const int c0 = (int)max(r0 - at, (int64_t)0);
-  const int c1 = (int)min(min(cover, (int64_t)len), r1 - at);
+  const int c1 = (int)min(min(ck.cover, (int64_t)len), r1 - at);
   if (c0 >= c1) continue;  // whole workgroup: an empty unit, or rows past the caller's bound
-  const int split = (int)(s - at / keys);
   const int h = (int)(u % g.H);
   const int64_t lb = u / g.H;
   const int b = (int)(lb % g.B);
@@ -284,12 +329,8 @@ __device__ __forceinline__ void decode_body(
   };
 
   DecFrag qf[KS];
-  float m_run = -INFINITY, l_run = 0.f;
+  float m_run, l_run;
   dec_f32x16 O[NDBW];  // O^T of the wave's 32-dim blocks db0 ..
-#pragma unroll
-  for (int db = 0; db < NDBW; ++db)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) O[db][v] = 0.f;
 
   // S^T = K Q^T of the key tile in stage buffer sb: lane (hh, c32) holds
   // query row c32 and keys 8*(v/4) + 4*hh + v%4 of the tile.
@@ -408,41 +449,59 @@ __device__ __forceinline__ void decode_body(
     for (int s = 0; s < KS; ++s) qf[s].u = make_uint4(0u, 0u, 0u, 0u);
   }
 
+  // the place of the piece's first partial
+  const uint32_t s0 = (uint32_t)at / cut.keys;
+  uint32_t place = dec_place(cut, (uint32_t)at, s0, (uint32_t)u);
+  if (s > s0)
+    place += cut.partials(dec_first(cut, (uint32_t)at, s0, (uint32_t)len)) +
+             ((uint32_t)s - s0 - 1u) * cut.partials(cut.keys);
+
   dec_wait_vm0();
   for (int st = 1; st < NBUF - 1 && st < ntiles; ++st) issue_stage(st);
-  for (int st = 0; st < ntiles; ++st) {
-    dec_wait_stages<PERW, NBUF - 2>(min(NBUF - 2, ntiles - 1 - st));
-    __syncthreads();
-    if (st + NBUF - 1 < ntiles) issue_stage(st + NBUF - 1);
-    finish_tile(st % NBUF, c0 + st * kDecTile, score_tile(st % NBUF));
+  for (int st = 0; st < ntiles;) {
+    // the rows of one partial
+    const int st0 = st, st_end = min(ntiles, st + (1 << (cut.sum_shift - kDecTileShift)));
+    m_run = -INFINITY;
+    l_run = 0.f;
+#pragma unroll
+    for (int db = 0; db < NDBW; ++db)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) O[db][v] = 0.f;
+    for (; st < st_end; ++st) {
+      dec_wait_stages<PERW, NBUF - 2>(min(NBUF - 2, ntiles - 1 - st));
+      __syncthreads();
+      if (st + NBUF - 1 < ntiles) issue_stage(st + NBUF - 1);
+      finish_tile(st % NBUF, c0 + st * kDecTile, score_tile(st % NBUF));
+    }
+    // the row's (max, sum), from the first wave of the query tile (every wave of
+    // it holds the same), and the unnormalized output of each wave's dims
+    const float l_row = l_run + __shfl_xor(l_run, 32, 64);
+    const int64_t pr =
+        (int64_t)(place + ((uint32_t)st0 >> (cut.sum_shift - kDecTileShift))) * mp + row;
+    if (row < M) {  // (the tile's padding rows are not written)
+      if (dsi == 0 && hh == 0) part_ml[pr] = make_float2(m_run, l_row);
+      float* po = part_o + pr * D;
+#pragma unroll
+      for (int db = 0; db < NDBW; ++db)
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+          po[32 * (db0 + db) + 8 * (v >> 2) + 4 * hh + (v & 3)] = O[db][v];
+    }
   }
-  // partials of this chunk: the row's (max, sum), from the first wave of the
-  // query tile (every wave of it holds the same), and the unnormalized output
-  // of each wave's dims
-  const float l_row = l_run + __shfl_xor(l_run, 32, 64);
-  const int64_t pr = ((int64_t)u * nsplit + split) * mp + row;
-  if (dsi == 0 && hh == 0) part_ml[pr] = make_float2(m_run, l_row);
-  float* po = part_o + pr * D;
-#pragma unroll
-  for (int db = 0; db < NDBW; ++db)
-#pragma unroll
-    for (int v = 0; v < 16; ++v)
-      po[32 * (db0 + db) + 8 * (v >> 2) + 4 * hh + (v & 3)] = O[db][v];
   __syncthreads();  // every wave is done with the stage buffers of this piece
   }
   }
 }
 
-// Two waves per SIMD: the register cap keeps the accumulators out of AGPRs.
+// Two waves per SIMD at least: the register cap keeps the accumulators out of
+// AGPRs; three where three workgroups fit a compute unit (decode_parts).
 template <int D, int NQT>
 __global__ __launch_bounds__((64 * DecShape<D, NQT>::NW))
-__attribute__((amdgpu_waves_per_eu(2))) void decode_kernel(
-    Geo g, int64_t U, int64_t cover, int32_t keys_min, int32_t parts, int32_t tq, int32_t nsplit,
-    int32_t mp, const uint16_t* __restrict__ qn, int64_t q_sl, int64_t q_st, int64_t q_sh,
+__attribute__((amdgpu_waves_per_eu(D == 64 && NQT == 4 ? 3 : 2))) void decode_kernel(
+    Geo g, int64_t U, DecodeChunks ck, int32_t tq, int32_t mp, const uint16_t* __restrict__ qn, int64_t q_sl, int64_t q_st, int64_t q_sh,
     const uint16_t* __restrict__ kp, const uint16_t* __restrict__ vp,
     const int64_t* __restrict__ poff, float* __restrict__ part_o, float2* __restrict__ part_ml) {
-  decode_body<D, NQT>(g, U, cover, keys_min, parts, tq, nsplit, mp, qn, q_sl, q_st, q_sh, kp, vp,
-                      poff, part_o, part_ml);
+  decode_body<D, NQT>(g, U, ck, tq, mp, qn, q_sl, q_st, q_sh, kp, vp, poff, part_o, part_ml);
 }
 
 // Combine the chunk partials of each (unit, row): one workgroup per row, the
@@ -466,8 +525,8 @@ constexpr int kCombThreads = 256;
 // bound is infinite).
 template <int D, bool CL>
 __global__ __launch_bounds__(kCombThreads) void decode_combine_kernel(
-    Geo g, int64_t U, int64_t cover, int32_t keys_min, int32_t parts, int32_t tq, int32_t nsplit,
-    int32_t mp, const int64_t* __restrict__ poff, const float* __restrict__ part_o,
+    Geo g, int64_t U, DecodeChunks ck, int32_t tq, int32_t mp, const int64_t* __restrict__ poff,
+    const float* __restrict__ part_o,
     const float2* __restrict__ part_ml, float* __restrict__ out, float* __restrict__ lse,
     DecodeClusters cl, const uint16_t* __restrict__ qn, int64_t q_sl,
     int64_t q_st, int64_t q_sh) {
@@ -483,10 +542,11 @@ __global__ __launch_bounds__(kCombThreads) void decode_combine_kernel(
   const int sg = threadIdx.x / C4;
   const int c4 = threadIdx.x % C4;
   const int len = (int)(poff[u + 1] - poff[u]);
-  const int nv = dec_pieces(poff[u] - poff[0], min(cover, (int64_t)len),
-                            dec_keys(poff[U] - poff[0], keys_min, parts));
-  if (len > cover && row == 0 && threadIdx.x == 0) report_range(g);
-  const int64_t base = (int64_t)u * nsplit * mp + row;  // + slot * mp
+  const DecCut cut = dec_cut(ck, (uint32_t)(poff[U] - poff[0]), U);
+  const uint32_t at_row = (uint32_t)(poff[u] - poff[0]), s0 = at_row / cut.keys;
+  const int nv = (int)dec_partials(cut, at_row, s0, (uint32_t)min(ck.cover, (int64_t)len));
+  const int64_t base = (int64_t)dec_place(cut, at_row, s0, (uint32_t)u) * mp + row;  // + slot * mp
+  if (len > ck.cover && row == 0 && threadIdx.x == 0) report_range(g);
   float m = -INFINITY, L = 0.f;
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
   auto fold = [&](float2 ml, float4 o) {
@@ -592,7 +652,8 @@ __global__ __launch_bounds__(kCombThreads) void decode_combine_kernel(
     if (dd < D) {
 #pragma unroll 8
       for (int gi = 0; gi < cl.m; ++gi)
-        at = fmaf(wc_s[gi], wc_s[gi] > 0.f ? bf16_to_f32(cl.vbar[(u * cl.m + gi) * D + dd]) : 0.f, at);
+        at = fmaf(wc_s[gi], wc_s[gi] > 0.f ? bf16_to_f32(cl.vbar[(u * cl.m + gi) * D + dd]) : 0.f,
+                    at);
     }
     if (dd < 64 && cl.bound) {
       // the certificate: a cluster per lane of the first wave
@@ -627,8 +688,8 @@ __global__ __launch_bounds__(kCombThreads) void decode_combine_kernel(
 // many slots of one are better dealt to the workgroup.
 template <int D>
 __global__ __launch_bounds__(kCombThreads) void decode_combine_rows_kernel(
-    Geo g, int64_t U, int64_t cover, int32_t keys_min, int32_t parts, int32_t tq, int32_t nsplit,
-    int32_t mp, const int64_t* __restrict__ poff, const float* __restrict__ part_o,
+    Geo g, int64_t U, DecodeChunks ck, int32_t tq, int32_t mp, const int64_t* __restrict__ poff,
+    const float* __restrict__ part_o,
     const float2* __restrict__ part_ml, float* __restrict__ out, float* __restrict__ lse) {
   constexpr int C4 = D / 4;
   constexpr int RW = kCombThreads / C4;
@@ -636,26 +697,27 @@ __global__ __launch_bounds__(kCombThreads) void decode_combine_rows_kernel(
   const int row = blockIdx.y * RW + threadIdx.x / C4;
   const int c4 = threadIdx.x % C4;
   const int len = (int)(poff[u + 1] - poff[u]);
-  const int nv = dec_pieces(poff[u] - poff[0], min(cover, (int64_t)len),
-                            dec_keys(poff[U] - poff[0], keys_min, parts));
-  if (len > cover && blockIdx.y == 0 && threadIdx.x == 0) report_range(g);
+  const DecCut cut = dec_cut(ck, (uint32_t)(poff[U] - poff[0]), U);
+  const uint32_t at_row = (uint32_t)(poff[u] - poff[0]), s0 = at_row / cut.keys;
+  const int nv = (int)dec_partials(cut, at_row, s0, (uint32_t)min(ck.cover, (int64_t)len));
+  const int64_t base = (int64_t)dec_place(cut, at_row, s0, (uint32_t)u) * mp + row;  // + slot * mp
+  if (len > ck.cover && blockIdx.y == 0 && threadIdx.x == 0) report_range(g);
   if (row >= tq * g.G) return;
-  const int64_t base = u * nsplit * mp + row;  // + slot * mp
   float m = -INFINITY, L = 0.f;
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
   constexpr int Q = 4;  // slots in flight; those past the last are read again and not folded
-  for (int s0 = 0; s0 < nv; s0 += Q) {
+  for (int i0 = 0; i0 < nv; i0 += Q) {
     float2 ml[Q];
     float4 o[Q];
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
-      const int64_t pr = base + (int64_t)min(s0 + i, nv - 1) * mp;
+      const int64_t pr = base + (int64_t)min(i0 + i, nv - 1) * mp;
       ml[i] = part_ml[pr];
       o[i] = reinterpret_cast<const float4*>(part_o + pr * D)[c4];
     }
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
-      if (s0 + i >= nv || ml[i].x == -INFINITY) continue;
+      if (i0 + i >= nv || ml[i].x == -INFINITY) continue;
       const float mn = fmaxf(m, ml[i].x);
       const float a = __builtin_amdgcn_exp2f(m - mn);  // 0 while m is -inf
       const float w = __builtin_amdgcn_exp2f(ml[i].x - mn);
@@ -703,20 +765,19 @@ static certkv_status launch_decode(const DecodeArgs& a, hipStream_t s) {
   }
   const int cus = device_cus(dev);
   if (cus <= 0) return CERTKV_EHIP;
-  const int64_t max_items = a.U * a.nsplit;
+  const int64_t max_items = a.ck.most + a.U - 1;
   const int64_t want = (int64_t)cus * nb;
   const unsigned grid = (unsigned)(max_items < want ? max_items : want);
   const uint16_t* q = static_cast<const uint16_t*>(a.q.ptr);
   const uint16_t* kp = static_cast<const uint16_t*>(a.k_packed);
   const uint16_t* vp = static_cast<const uint16_t*>(a.v_packed);
-  CERTKV_LAUNCH("decode", (decode_kernel<D, NQT>), dim3(grid), dim3(NT), 0, s, g, a.U, a.cover,
-                a.keys_min, (int32_t)want, a.tq, a.nsplit, mp, q, a.q.s_layer, a.q.s_token,
-                a.q.s_head, kp, vp, a.packed_offsets, a.part_o, a.part_ml);
+  CERTKV_LAUNCH("decode", (decode_kernel<D, NQT>), dim3(grid), dim3(NT), 0, s, g, a.U, a.ck, a.tq,
+                mp, q, a.q.s_layer, a.q.s_token, a.q.s_head, kp, vp, a.packed_offsets, a.part_o, a.part_ml);
   const int M = a.tq * g.G;
   constexpr int RW = 4 * kCombThreads / D;
 #define CERTKV_COMBINE(CL)                                                                         \
   CERTKV_LAUNCH("decode_combine", (decode_combine_kernel<D, CL>), dim3((unsigned)a.U, (unsigned)M), \
-                dim3(kCombThreads), 0, s, g, a.U, a.cover, a.keys_min, (int32_t)want, a.tq, a.nsplit, mp,       \
+                dim3(kCombThreads), 0, s, g, a.U, a.ck, a.tq, mp,                                   \
                 a.packed_offsets, (const float*)a.part_o, (const float2*)a.part_ml, a.out, a.lse,  \
                 a.cl, q, a.q.s_layer, a.q.s_token, a.q.s_head)
   if (a.cl.m > 0)
@@ -726,7 +787,7 @@ static certkv_status launch_decode(const DecodeArgs& a, hipStream_t s) {
   else
     CERTKV_LAUNCH("decode_combine", (decode_combine_rows_kernel<D>),
                   dim3((unsigned)a.U, (unsigned)((M + RW - 1) / RW)), dim3(kCombThreads), 0, s, g,
-                  a.U, a.cover, a.keys_min, (int32_t)want, a.tq, a.nsplit, mp, a.packed_offsets,
+                  a.U, a.ck, a.tq, mp, a.packed_offsets,
                   (const float*)a.part_o, (const float2*)a.part_ml, a.out, a.lse);
 #undef CERTKV_COMBINE
   return CERTKV_OK;
@@ -747,24 +808,25 @@ certkv_status run_decode(const DecodeArgs& a, hipStream_t s) {
   return a.g.D == 128 ? launch_decode_d<128>(a, s) : launch_decode_d<64>(a, s);
 }
 
-// Rows of partials: [U][nsplit][32 NQT].
-size_t decode_partial_rows(int64_t U, int nsplit, int tq, int G) {
-  return (size_t)U * nsplit * decode_nqt(tq * G) * 32;
+// Workgroups resident at once on the device the chunks are cut for: by LDS two
+// per compute unit at 128 dims and four at 64, by registers three with four query
+// tiles of 64 dims and one with eight and more.
+static int decode_parts(int D, int nqt) {
+  return 256 * (nqt >= 8 ? 1 : D == 128 ? 2 : nqt == 4 ? 3 : 4);
 }
 
-// The shortest chunk whose partials take up to 2^17 rows for units of max_len
-// (64 MB of outputs at 128 dims), else 4096 keys.  (Not from a caller's tighter
-// row bound: the chunks, and so the bits, are the same under any bound.)
-int decode_keys_min(int64_t U, int max_len, int tq, int G) {
-  const int64_t rows = ((int64_t)max_len + kDecKeys - 1) / kDecKeys * kDecKeys;
-  int k = kDecKeysMin;
-  while (k < kDecKeys && U * (rows / k) * decode_nqt(tq * G) * 32 > (1 << 17)) k *= 2;
-  return k;
+DecodeChunks decode_chunks(int D, int tq, int G, int64_t cover_rows, int64_t rows) {
+  const int nqt = decode_nqt(tq * G);
+  DecodeChunks c;
+  c.cover = (cover_rows + 4095) / 4096 * 4096;
+  c.keys_min = 128;
+  c.parts = decode_parts(D, nqt);
+  const int64_t shortest = (rows + c.keys_min - 1) / c.keys_min;
+  c.most = c.parts < shortest ? c.parts : (int32_t)shortest;
+  c.sums = (rows + (1 << kDecSumShift) - 1) >> kDecSumShift;
+  return c;
 }
 
-// Rows of a unit that the chunks cover: the bound, up to whole 4096s.
-int64_t decode_cover(int max_rows) {
-  return ((int64_t)max_rows + kDecKeys - 1) / kDecKeys * kDecKeys;
-}
+int64_t decode_partials(const DecodeChunks& c, int64_t U) { return c.sums + c.most + U; }
 
 }  // namespace certkv

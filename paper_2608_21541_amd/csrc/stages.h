@@ -188,19 +188,26 @@ struct DecodeClusters {
   float* bound;                 // optional [L][B*tq][Hq] certificate (inf if it does not hold)
 };
 
+// How the packed rows are cut into chunks (see decode.hip).
+struct DecodeChunks {
+  int64_t cover;                // rows of a segment that are attended
+  int32_t most;                 // chunks the workspace has room for
+  int64_t sums;                 // and partials of a single segment of all the rows
+  int32_t keys_min;             // shortest chunk
+  int32_t parts;                // workgroups resident at once
+};
+
 struct DecodeArgs {
   Geo g;
   int64_t U;
   int32_t tq;                   // new queries per sequence
-  int32_t keys_min;             // shortest chunk the workspace has slots for
-  int64_t cover;                // rows of a segment that the chunks cover
-  int32_t nsplit;               // slots per unit: cover / keys_min + 1
+  DecodeChunks ck;
   certkv_tensor q;              // [L][B*tq][Hq][d] bf16
   const void* k_packed;         // [P][d] bf16
   const void* v_packed;
   const int64_t* packed_offsets;
-  float* part_o;                // [U][nsplit][mp][d]
-  float2* part_ml;              // [U][nsplit][mp]
+  float* part_o;                // [decode_partials()][mp][d]
+  float2* part_ml;              // [decode_partials()][mp]
   float* out;                   // [L][B*tq][Hq][d]
   float* lse;                   // optional [L][B*tq][Hq]
   DecodeClusters cl;
@@ -212,9 +219,9 @@ inline int decode_nqt(int M) {
   return t;
 }
 certkv_status run_decode(const DecodeArgs& a, hipStream_t s);
-size_t decode_partial_rows(int64_t U, int nsplit, int tq, int G);
-int decode_keys_min(int64_t U, int max_len, int tq, int G);
-int64_t decode_cover(int max_rows);
+// rows: of all segments together, at most; cover_rows: of one.
+DecodeChunks decode_chunks(int D, int tq, int G, int64_t cover_rows, int64_t rows);
+int64_t decode_partials(const DecodeChunks& c, int64_t U);  // partials of a call at most
 
 certkv_status run_packed_from_kept(int64_t U, int32_t slot, const int64_t* kept_offsets,
                                    int64_t* packed_offsets, hipStream_t s);

@@ -130,6 +130,22 @@ def test_workspaces_of_ragged_batches(L, seqlens, allocate, select, compress):
         assert lib.certkv_workspace_size(ctypes.byref(p), stage) <= mib * 2 ** 20, stage
 
 
+@pytest.mark.parametrize("L,seqlens,tq,mib", [
+    (1, (32768,), 1, 10), (1, (1024,), 1, 2), (1, (32768,), 32, 40),
+    (32, (4096,) * 8, 1, 80), (32, (131072,), 1, 145),
+    (32, (131072,) + (1024,) * 47, 1, 400),     # a long sequence beside many short ones
+    (1, (1 << 20,) + (512,) * 249, 32, 530),
+])
+def test_decode_workspace(L, seqlens, tq, mib):
+    # Partials for the pieces that a call can have, not for the longest segment's
+    # in every unit; less under a bound on the segments' rows.
+    lib = _lib.lib()
+    p = problem(L=L, seqlens=seqlens, H=8, G=4, w=64)
+    size = lib.certkv_decode_workspace_size(ctypes.byref(p), tq, 0)
+    assert size <= mib * 2 ** 20
+    assert lib.certkv_decode_workspace_size(ctypes.byref(p), tq, max(seqlens) // 8) < size
+
+
 def test_plan_of_a_ragged_batch_is_quick():
     # A call makes its plan on the host: a long sequence beside many short ones took
     # 160 us of one-by-one search for the curves' segments.

@@ -303,15 +303,19 @@ def test_hull_allocation_beside_the_full_search(layers):
                 assert np.array_equal(got[li, b], want), (steps, li, b)
 
 
-@pytest.mark.parametrize("dim,group,tq", [(128, 4, 1), (128, 4, 33), (64, 1, 1), (128, 8, 8)])
+@pytest.mark.parametrize("dim,group,tq", [(128, 4, 1), (128, 4, 33), (64, 1, 1), (128, 8, 8),
+                                          (128, 8, 40), (64, 8, 32)])
 @pytest.mark.parametrize("rows", [[1, 2, 31, 127, 128, 129, 4097, 700], [9000] * 4 + [3] * 5,
                                   [37] * 300, [150000, 10, 4096, 0, 65536],
                                   [128, 128, 256, 0, 0, 1, 127, 0], [0, 5, 300, 0] * 20,
-                                  [9001] * 8 + [0] * 60 + [33000] * 60])
+                                  [9001] * 8 + [0] * 60 + [33000] * 60,
+                                  [700001, 3, 0, 600000], [5100] * 30, [1100] * 230])
 def test_decode_chunks(rows, dim, group, tq):
     # Chunk lengths from 128 to over 4096 keys, chunks that end with a unit and
-    # inside one, segments of a row to many chunks and empty ones, up to 64 units
-    # and more, both combines.  Rows within 1e-4 of fp64 attention, as the decode tests.
+    # inside one, pieces of one partial and of several, segments of a row to many
+    # chunks and empty ones, up to 64 units and more, every piece with a workgroup of
+    # its own and not, both combines.  Rows within 1e-4 of fp64 attention, as the
+    # decode tests; the same bits under a loose bound on the segments' rows.
     if len(rows) == 300 and dim == 64:
         rows = rows * 30                       # many rows: the row combine
     n = max(max(rows), 16)
@@ -321,6 +325,9 @@ def test_decode_chunks(rows, dim, group, tq):
     kp, vp = (torch.randn((sum(rows), dim), generator=gen, device=DEV).bfloat16() for _ in range(2))
     q = torch.randn((1, len(rows) * tq, group, dim), generator=gen, device=DEV).bfloat16()
     out, lse = ck.decode(spec, q, kp, vp, off, tq, with_lse=True, max_rows=max(rows))
+    loose = ck.ProblemSpec(1, 1, group, dim, 16, [2 * n + 5000] * len(rows))
+    wide = ck.decode(loose, q, kp, vp, off, tq)
+    assert torch.equal(wide.nan_to_num(), out.nan_to_num())  # (an empty segment: 0 / 0)
     for u in range(0, len(rows), 1 if len(rows) < 200 else 97):
         a, b = int(off[u]), int(off[u + 1])
         if a == b:
@@ -332,6 +339,31 @@ def test_decode_chunks(rows, dim, group, tq):
         assert ((got - ref).norm(dim=1) <= 1e-4 * ref.norm(dim=1)).all(), u
         err = lse[0, u * tq:(u + 1) * tq].double().reshape(-1) - torch.logsumexp(z, 1)
         assert err.abs().max() <= 1e-4
+
+
+@pytest.mark.parametrize("tq", [1, 40])
+def test_decode_beside_other_units(tq):
+    # One sequence's segments alone and inside a ragged batch: other chunks, and so
+    # sums grouped otherwise.  Each side applies its weights in 16 bits or better,
+    # which bounds the difference at 2 2^-16 of the weighted magnitudes.
+    rows, dim, group = [700, 9000, 33, 4100], 128, 4
+    more = rows + [20000, 1, 650] * 40
+    gen = torch.Generator(device=DEV).manual_seed(7)
+    off = torch.tensor([0] + list(np.cumsum(more)), dtype=torch.int64, device=DEV)
+    kp, vp = (torch.randn((sum(more), dim), generator=gen, device=DEV).bfloat16() for _ in range(2))
+    q = torch.randn((1, len(more) * tq, group, dim), generator=gen, device=DEV).bfloat16()
+    got = []
+    for r in (rows, more):
+        spec = ck.ProblemSpec(1, 1, group, dim, 16, [max(r)] * len(r))
+        got.append(ck.decode(spec, q[:, :len(r) * tq].contiguous(), kp[:sum(r)], vp[:sum(r)],
+                             off[:len(r) + 1].contiguous(), tq, with_lse=True))
+    for u in range(len(rows)):
+        a, b = int(off[u]), int(off[u + 1])
+        x = q[0, u * tq:(u + 1) * tq].double().reshape(tq * group, dim)
+        w = torch.softmax((x @ kp[a:b].double().t().contiguous()) / dim ** 0.5, 1)
+        out = [g[0][0, u * tq:(u + 1) * tq].double().reshape(tq * group, dim) for g in got]
+        assert ((out[0] - out[1]).abs() <= 2 * 2.0 ** -16 * (w @ vp[a:b].double().abs())).all()
+        assert (got[0][1][0, u * tq:(u + 1) * tq] - got[1][1][0, u * tq:(u + 1) * tq]).abs().max() <= 2e-5
 
 
 @pytest.mark.parametrize("dim,group,window,lens,heads", [
