@@ -58,6 +58,15 @@ __device__ __forceinline__ uint32_t dec_pack_bf16(float a, float b) {
 }
 
 
+// 16 bytes at addresses aligned to an element only: the caller's cluster summaries
+// and outputs (a row count or an offset of its own may come before them).
+typedef uint32_t dec_u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
+typedef float dec_f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ uint4 dec_load_any(const uint16_t* p) {
+  const dec_u32x4_any x = *reinterpret_cast<const dec_u32x4_any*>(p);
+  return make_uint4(x[0], x[1], x[2], x[3]);
+}
+
 // Workgroup shape: every wave takes one 32-row query tile and all keys; with
 // fewer than four query tiles, DS waves share a query tile and split the
 // output dims (each computes the tile's scores and softmax, and P V for its
@@ -601,8 +610,8 @@ __global__ __launch_bounds__(kCombThreads) void decode_combine_kernel(
     };
     for (int g0 = 0; g0 < cl.m; g0 += kCombThreads / LC) {
       const int gi = min(g0 + (int)threadIdx.x / LC, cl.m - 1);
-      const uint4 kv = reinterpret_cast<const uint4*>(cl.kbar + (u * cl.m + gi) * D)[threadIdx.x % LC];
-      const uint4 vv = reinterpret_cast<const uint4*>(cl.vbar + (u * cl.m + gi) * D)[threadIdx.x % LC];
+      const int64_t at = (u * cl.m + gi) * D + 8 * (threadIdx.x % LC);
+      const uint4 kv = dec_load_any(cl.kbar + at), vv = dec_load_any(cl.vbar + at);
       float dot = 0.f, nv2 = 0.f, nq2 = 0.f;
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
@@ -741,7 +750,8 @@ __global__ __launch_bounds__(kCombThreads) void decode_combine_rows_kernel(
   acc.w /= L;
   if (!(isfinite(acc.x) && isfinite(acc.y) && isfinite(acc.z) && isfinite(acc.w)))
     report_nonfinite(g);
-  reinterpret_cast<float4*>(out + orow * D)[c4] = acc;
+  *reinterpret_cast<dec_f32x4_any*>(out + orow * D + 4 * c4) =
+      (dec_f32x4_any){acc.x, acc.y, acc.z, acc.w};
   if (lse && c4 == 0) lse[orow] = (m + __builtin_amdgcn_logf(L)) * kDecLn2;
 }
 

@@ -341,6 +341,38 @@ def test_decode_chunks(rows, dim, group, tq):
         assert err.abs().max() <= 1e-4
 
 
+def test_decode_of_odd_addresses():
+    # Cluster summaries and outputs aligned to an element only, in both combines:
+    # the same bits as at aligned addresses.
+    def shifted(x):
+        y = torch.empty(x.numel() + 1, dtype=x.dtype, device=DEV)[1:].reshape(x.shape)
+        return y.copy_(x)
+    dim, group, m, rows = 128, 4, 5, [300, 41, 2000]
+    gen = torch.Generator(device=DEV).manual_seed(3)
+    rnd = lambda *s: torch.randn(s, generator=gen, device=DEV)  # noqa: E731
+    off = torch.tensor([0] + list(np.cumsum(rows)), dtype=torch.int64, device=DEV)
+    kp, vp = rnd(sum(rows), dim).bfloat16(), rnd(sum(rows), dim).bfloat16()
+    spec = ck.ProblemSpec(1, 1, group, dim, 16, [2000] * 3, slot=False)
+    cl = dict(kbar=(0.1 * rnd(3, m, dim)).bfloat16(), vbar=(0.1 * rnd(3, m, dim)).bfloat16(),
+              count=torch.full((3, m), 40, dtype=torch.int32, device=DEV),
+              rk=rnd(3, m).abs() * 0.01, rv=rnd(3, m).abs(), vmax_kept=rnd(3).abs() + 15)
+    q = rnd(1, 3 * 2, group, dim).bfloat16()
+    want = ck.decode_clustered(spec, q, kp, vp, off, 2, cl)
+    got = ck.decode_clustered(spec, q, kp, vp, off, 2,
+                              dict(cl, kbar=shifted(cl["kbar"]), vbar=shifted(cl["vbar"])))
+    assert all(torch.equal(a, b) for a, b in zip(got, want))
+    # 8192 rows and more: the combine of several rows to a workgroup
+    units, tq = 64, 40
+    off = torch.arange(units + 1, device=DEV) * 30
+    spec = ck.ProblemSpec(1, 1, group, dim, 16, [30] * units)
+    q = rnd(1, units * tq, group, dim).bfloat16()
+    bufs = ck.DecodeBuffers(spec, tq, torch.device(DEV))
+    want = ck.decode(spec, q, kp[:units * 30], vp[:units * 30], off, tq, bufs=bufs).clone()
+    bufs.out = shifted(torch.zeros_like(bufs.out))
+    assert bufs.out.data_ptr() % 16 == 4
+    assert torch.equal(ck.decode(spec, q, kp[:units * 30], vp[:units * 30], off, tq, bufs=bufs), want)
+
+
 @pytest.mark.parametrize("tq", [1, 40])
 def test_decode_beside_other_units(tq):
     # One sequence's segments alone and inside a ragged batch: other chunks, and so
