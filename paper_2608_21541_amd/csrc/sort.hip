@@ -341,7 +341,7 @@ __global__ __launch_bounds__(kSortThreads) void seg_sort_kernel(
 struct RankLds {
   uint32_t start[256];  // digit-major start of each digit among the elements
   uint32_t tot[256];    // elements of each digit
-  uint32_t wave_cnt[kSortWaves][256];
+  alignas(16) uint32_t wave_cnt[kSortWaves][256];  // also read and written 16 bytes at a time
 };
 constexpr int kRunRounds = kSortRun / kSortThreads;
 
