@@ -545,7 +545,7 @@ static certkv_status launch_curves(const CurveArgs& a, const SeqTab& st, hipStre
 certkv_status run_curves(const CurveArgs& a, const SeqTab& st, hipStream_t s) {
   if (a.dtype == CERTKV_BF16)
     return a.g.D == 128 ? launch_curves<128, true>(a, st, s) : launch_curves<64, true>(a, st, s);
-  return a.g.D == 128 ? launch_curves<128, false>(a, st, s) : launch_curves<64, false>(a, st, s);
+  return launch_curves<64, false>(a, st, s);  // fp32 rows of 128 are refused before
 }
 
 }  // namespace certkv

@@ -1,4 +1,4 @@
-"""Register budgets of the kernels the benchmark's pass launches, checked on
+"""Register budgets of the kernels that the pass and decode launch, checked on
 the compiler's own resource report (the device assembly's .num_vgpr and
 .private_seg_size symbols): none of them may spill to scratch memory, whose
 reloads wait for every outstanding load, and each must fit the VGPR budget of
@@ -36,11 +36,30 @@ KERNELS = [
     ("curves.hip", "_ZN6certkv13curves_kernelILi128ELb1ELi1E", 128),         # uncentered
     ("curves.hip", "_ZN6certkv13curves_kernelILi128ELb1ELi2E", 128),         # tail mass
     ("curves.hip", "_ZN6certkv13curves_kernelILi64ELb0ELi0E", 128),          # fp32, d = 64
+    ("curves.hip", "_ZN6certkv19curve_totals_kernelI", 64),                  # two workgroups of 1024
+    ("allocate.hip", "_ZN6certkv23curve_blockstats_kernelILb1ELi8E", 128),
+    ("allocate.hip", "_ZN6certkv23curve_blockstats_kernelILb1ELi2E", 64),
+    ("allocate.hip", "_ZN6certkv23curve_blockstats_kernelILb0ELi8E", 64),
+    ("allocate.hip", "_ZN6certkv17hull_merge_kernel", 128),
+    ("allocate.hip", "_ZN6certkv20allocate_hull_kernel", 128),
     ("allocate.hip", "_ZN6certkv15allocate_kernel", 128),
     ("select.hip", "_ZN6certkv13select_kernel", 128),
-    ("tail.hip", "_ZN6certkv18tail_gather_kernelILi128EtLb1ELb1E", 128),
+    ("select.hip", "_ZN6certkv15coverage_kernel", 64),
+    ("tail.hip", "_ZN6certkv18tail_gather_kernelI", 128),
+    ("tail.hip", "_ZN6certkv20tail_finalize_kernelI", 64),
     ("clusters.hip", "_ZN6certkv19cluster_tail_kernelILi128EtE", 102),       # five waves per SIMD
+    # the workgroups per compute unit that decode_parts counts on (not listed: sixteen
+    # query tiles, whose 1024 threads have 128 VGPRs and spill)
+    ("decode.hip", "_ZN6certkv13decode_kernelILi128ELi1EE", 256),
+    ("decode.hip", "_ZN6certkv13decode_kernelILi128ELi2EE", 256),
     ("decode.hip", "_ZN6certkv13decode_kernelILi128ELi4EE", 256),
+    ("decode.hip", "_ZN6certkv13decode_kernelILi128ELi8EE", 256),
+    ("decode.hip", "_ZN6certkv13decode_kernelILi64ELi1EE", 256),
+    ("decode.hip", "_ZN6certkv13decode_kernelILi64ELi2EE", 128),
+    ("decode.hip", "_ZN6certkv13decode_kernelILi64ELi4EE", 168),
+    ("decode.hip", "_ZN6certkv13decode_kernelILi64ELi8EE", 256),
+    ("decode.hip", "_ZN6certkv21decode_combine_kernelI", 64),
+    ("decode.hip", "_ZN6certkv26decode_combine_rows_kernelI", 64),
 ]
 
 
