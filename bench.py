@@ -32,8 +32,9 @@ VALU_PEAK_TSLOTS = 256 * 4 * 16 * 2.4e9 / 1e12
 COPY_BYTES = 1 << 30           # calibration copy: 1 GiB read, 1 GiB written
 
 KERNEL_SOURCES = {
-    "score_": "score.hip", "sort_segments": "sort.hip", "curves": "curves.hip",
-    "curve_blockstats": "allocate.hip", "allocate": "allocate.hip", "select": "select.hip",
+    "score_": "score.hip", "sort_": "sort.hip", "curves": "curves.hip",
+    "curve_totals": "curves.hip", "curve_blockstats": "allocate.hip", "hull_merge": "allocate.hip",
+    "allocate": "allocate.hip", "select": "select.hip",
     "kept_offsets": "select.hip", "clamp_budgets": "select.hip", "packed_offsets": "select.hip",
     "coverage_budget": "select.hip", "tail_": "tail.hip", "compact_": "tail.hip",
     "kept_bitmap": "tail.hip", "decode": "decode.hip",
@@ -48,13 +49,14 @@ def algorithmic_model(cfg, n_keep, lse_in=False):
       kernel                bytes                                   MFMA flops  VALU slots
       score pass 1          K read: d*e                              2*M*d       4*M
       score pass 2          K read + score write: d*e + 4            2*M*d       4*M
-      sort                  score read + order write: 8
+      sort (all its kernels) score read + order write: 8
       curves                V gathered + order + key + curve: d*e+12             9*d
       curve block stats     curve read: 4
-      allocate              curve read: 4
       select                score read + kept index + bitmap: 4+4f+1/8
       tail+compact gather   kept index, score, K, V read; K, V and
                             position written: f*(4*d*e + 12)
+    The allocation reads the hull points that the block statistics leave and a
+    few blocks of each curve, which bounds nothing.
     A VALU slot is one full-rate lane operation: per softmax term the passes
     spend one multiply (or fma), one exp2 (half rate: 2 slots) and one add;
     the fp64 curves spend per (rank, dim) two conversions and two fma in the
@@ -70,10 +72,9 @@ def algorithmic_model(cfg, n_keep, lse_in=False):
     per = {
         "score_pass1_mfma": (D * e, 2 * M * D, 4 * M),
         "score_pass2_mfma": (D * e + 4, 2 * M * D, 4 * M),
-        "sort_segments": (8, 0, 0),
+        "sort": (8, 0, 0),
         "curves": (D * e + 12, 0, 9 * D),
         "curve_blockstats": (4, 0, 0),
-        "allocate": (4, 0, 0),
         "select": (4 + 4 * f + 0.125, 0, 0),
         "tail_compact_gather": (f * (4 * D * e + 12), 0, 0),
     }
@@ -650,7 +651,13 @@ def main():
                 r = roofline_of(name, model, kk["avg_ms"], args.config)
                 kk.update({"bound": r["bound"], "frac": r["frac"]})
         dom = max(kernels, key=lambda n_: kernels[n_]["avg_ms"] * kernels[n_]["launches_per_step"])
-        return roofline_of(dom, model, kernels[dom]["avg_ms"], args.config)
+        roof = roofline_of(dom, model, kernels[dom]["avg_ms"], args.config)
+        sort_ms = sum(kk["avg_ms"] * kk["launches_per_step"] for name, kk in kernels.items()
+                      if name.startswith("sort_"))
+        r = roofline_of("sort", model, sort_ms, args.config)
+        kernels["sort"] = {"launches_per_step": 1.0, "avg_ms": sort_ms, "bound": r["bound"],
+                           "frac": r["frac"], "note": "the sort_ kernels together"}
+        return roof
 
     roof = summarize(kernels, model)
     pass_bytes = sum(b for b, _, _ in model.values())
