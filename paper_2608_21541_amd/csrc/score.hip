@@ -539,7 +539,8 @@ __global__ __launch_bounds__(kScoreThreads) __attribute__((amdgpu_waves_per_eu((
 #pragma unroll
     for (int e = 0; e < PER; ++e) red_lds[wave * D + hh * HD + c32 * PER + e] = v[e];
     __syncthreads();
-    const int64_t row = kpart_row(g, st, keys_per_block, l, bl, h, kb);
+    const int64_t row =
+        part_base_of(g, l, blockIdx.x, kb, score_blocks(st, bl, keys_per_block)) + kb;
     for (int dd = threadIdx.x; dd < D; dd += kScoreThreads) {
       float s = 0.f;
       for (int wv = 0; wv < NW; ++wv) s += red_lds[wv * D + dd];
@@ -813,7 +814,8 @@ __global__ __launch_bounds__(kP2Threads) __attribute__((amdgpu_waves_per_eu(4, 8
     for (int sg = 0; sg < NSTG; ++sg)
       red_lds[wave * D + 64 * sg + lane] = kacc[sg][0] + kacc[sg][1] + kacc[sg][2];
     __syncthreads();
-    const int64_t row = kpart_row(g, st, keys_per_block, l, bl, h, kb);
+    const int64_t row =
+        part_base_of(g, l, blockIdx.x, kb, score_blocks(st, bl, keys_per_block)) + kb;
     for (int dd = threadIdx.x; dd < D; dd += kP2Threads) {
       float s = 0.f;
       for (int wv = 0; wv < kP2Waves; ++wv) s += red_lds[wv * D + dd];

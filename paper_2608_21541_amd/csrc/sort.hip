@@ -694,8 +694,6 @@ __global__ __launch_bounds__(kSortThreads) void sort_count_kernel(
   const int e0 = tile * kSortRun;
   const int nb = sort_nb(n);
   const int64_t base = lht_base(g, l, h, st.start[bl]);
-  const int64_t b0 = part_base(g, st, l, bl, h, [&](int i) { return sort_nb(st.len[i]); });
-  const int64_t t0 = part_base_of(g, l, blockIdx.x, tile, sort_tiles(n));
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wkeep = n - g.keep_w;
   const BufRsrc srs = make_rsrc(scores + base, (uint32_t)n * 4u);
@@ -703,6 +701,9 @@ __global__ __launch_bounds__(kSortThreads) void sort_count_kernel(
 #pragma unroll
   for (int r = 0; r < kRunRounds; ++r)
     raw[r] = buf_load_u32(srs, (uint32_t)(e0 + r * kSortThreads + tid) * 4u);
+  // (while the scores are on their way)
+  const int64_t b0 = part_base(g, st, l, bl, h, [&](int i) { return sort_nb(st.len[i]); });
+  const int64_t t0 = part_base_of(g, l, blockIdx.x, tile, sort_tiles(n));
   if (tid < nb) {
     sp[tid] = tid < nb - 1 ? splitters[b0 + tid] : ~0ull;
     cnt_s[tid] = 0u;
