@@ -585,7 +585,7 @@ def main():
 
     if args.gpus != 1:
         print(json.dumps({"error": "this build runs on exactly one GPU; "
-                                   "--gpus must be 1 (sharding is described in DESIGN.md)"}))
+                                   "--gpus must be 1"}))
         sys.exit(2)
 
     import torch

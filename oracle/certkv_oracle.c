@@ -9,7 +9,7 @@
  * Arithmetic is IEEE binary64, built with -ffp-contract=off so that every
  * a*b+c is two roundings unless fma() is written out.
  *
- * Readings of points the paper leaves open (each is listed in the design doc):
+ * Readings of points the paper leaves open:
  *   - GQA: the scores of the query heads of one KV head are summed.
  *   - Causal window rows: row q at position p sees keys j <= p.
  *   - Sort key: the fp32 score s itself, descending; equal s keep ascending
